@@ -266,3 +266,41 @@ def test_rollout_argument_checks():
     wd.wdc_rollout(env.handle, ring.data_ptr(), 2, 1, None)  # a single iteration, nothing recorded
     assert wd.wdc_get_step(env.handle) == 1
     env.close()
+
+
+BLOCK = [  # envs of more than 64 agents run in a workgroup each (block_kernel): edges of its sizes and of its searches
+    dict(num_agents=65, num_taggers=1, world_size=9.0, obs_k=1),                        # one agent in the second wave
+    dict(num_agents=128, num_taggers=127, world_size=14.0, obs_k=2),                    # whole waves; one runner
+    dict(num_agents=129, num_taggers=64, world_size=14.0, obs_k=3, tag_r2=0.05),        # odd K: rows leave lane by lane
+    dict(num_agents=300, num_taggers=90, world_size=25.0, obs_k=5, tag_r2=9.0),
+    dict(num_agents=1024, num_taggers=1, world_size=30.0, obs_k=8, tag_r2=-1.0),        # largest env, no tagging
+    dict(num_agents=150, num_taggers=40, world_size=12.0, obs_k=6, tag_r2=400.0),       # every tagger reaches everybody
+    dict(num_agents=200, num_taggers=20, world_size=1.0, obs_k=4, tag_r2=-1.0, num_headings=4, accel=2.0,
+         max_speed_tagger=5.0, max_speed_runner=5.0),                                    # crowds at equal distances: corners
+    dict(num_agents=400, num_taggers=300, world_size=20.0, obs_k=7, tag_r2=0.5),         # most agents are taggers
+    dict(num_agents=100, num_taggers=50, world_size=3.0, obs_k=4, tag_r2=0.6),           # lists shrink to a few dozen
+    dict(num_agents=96, num_taggers=2, world_size=2e6, obs_k=4),                         # beyond the kernel's world sizes
+]
+
+
+@pytest.mark.parametrize("n", range(len(BLOCK)))
+def test_env_per_workgroup(n):
+    """Against the oracle through separate and fused calls, over two episodes; then a start state that
+    lies partly outside the world, which a caller may write."""
+    kw = dict(dict(num_envs=3, episode_length=7, seed=300 + n, env_offset=n), **BLOCK[n])
+    lockstep(kw, 17, 300 + n)
+    gpu, orc = wd.CTagEnvs(device="cuda:0", **kw), ctag_oracle.CTagOracle(**kw)
+    gpu.reset(wd.WD_RESET_ALL), orc.reset()
+    rng = np.random.default_rng(n)
+    for name in ("x0", "y0"):
+        start = getattr(orc, name)
+        start[:2, ::3] += (rng.integers(-2, 3, start[:2, ::3].shape) * kw["world_size"]).astype(np.float32)
+        getattr(gpu, name).copy_(torch.from_numpy(start))
+    gpu.done.fill_(1)
+    orc.done[:] = 1
+    gpu.reset(wd.WD_RESET_DONE), orc.reset(ctag_oracle.RESET_DONE)
+    got = gpu.to_host()
+    err = np.abs(got["obs"].astype(np.float64) - orc.obs) / np.maximum(1.0, np.abs(orc.obs))
+    assert err.max() <= TOL  # (features beyond 1 here: the bound of one rounded reciprocal is relative)
+    assert np.array_equal(got["live"], orc.live) and np.array_equal(got["t"], orc.t)
+    gpu.close()
