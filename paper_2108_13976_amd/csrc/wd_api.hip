@@ -45,6 +45,11 @@ constexpr int kSpreadMinAgents = 1024;
 // 46.9 / 41.3, 20000 x 64 58.1 / 39.0 and 50000 x 5 38.5 / 32.8 (a wave for five agents)
 constexpr int kWaveEnvsMaxBatch = 8192;
 
+// full observations: from this many agents per env on, or from a wave's agents and this many bytes of rows on,
+// the rows have a kernel of their own
+constexpr int kFullSplitAgents = 100;
+constexpr int64_t kFullSplitBytes = 64 << 20;
+
 int bits_for(uint32_t v) {  // bits needed to hold values 0..v
   int b = 1;
   while ((uint64_t(1) << b) <= v) ++b;
@@ -431,6 +436,14 @@ int fill_params(const wd_config& c, const wd_buffers& b, wd::Params* p) {
   p->K = c.obs_mode == WD_OBS_PARTIAL ? c.obs_k : 0;
   p->D = obs_dim(&c);
   p->obs_mode = c.obs_mode;
+  // Full observations: a second launch for the rows (about 4 us, 8 where step and reset are called one by one)
+  // pays once the rows are long or many.  Measured, us per iteration, rows written by env_kernel -> by their own
+  // kernel: 20 envs x 70 agents 16.7 -> 20.5 (three separate calls 22.1 -> 29.4), 400 x 70 19.8 -> 25.3, 20 x 130
+  // 27.9 -> 21.5 (34.2 -> 30.4), 100 x 100 54.2 -> 22.2, 2000 x 64 (134 MB of rows) 78.4 -> 52.1, 200 x 500 359 -> 69.4,
+  // 2000 x 1000 (in mid-training) 2640 -> 1798.
+  const int64_t row_bytes = int64_t(c.num_envs) * c.num_agents * p->D * 4;
+  if (c.obs_mode == WD_OBS_FULL && (c.num_agents >= kFullSplitAgents || (c.num_agents >= wd::kWaveSize && row_bytes >= kFullSplitBytes)))
+    p->obs_mode = wd::kObsFullSplit;
   p->env_offset = uint32_t(c.env_offset);
   p->seed_lo = uint32_t(c.seed);
   p->seed_hi = uint32_t(c.seed >> 32);

@@ -43,6 +43,9 @@ constexpr int strip_pad(int k) {
 }
 constexpr int kStripScanAll = 64;  // lists up to this length are scanned whole instead of through windows
 constexpr int kStripQueue2 = 32;  // agents per env that may wait for the third, exact block search
+// Params.obs_mode: 0 partial, 1 full, and full with the rows written by a kernel of their own (full_rows_kernel)
+constexpr int kObsFullSplit = 2;
+constexpr uint32_t kRowWanted = 0x7FD5A3C1u;  // first feature of a row that full_rows_kernel is to write (a NaN: never a feature)
 constexpr uint32_t kStreamAction = 0;   // random streams (low byte of the fourth counter word)
 constexpr uint32_t kStreamInit = 1;
 

@@ -9,6 +9,7 @@
 // in LDS, the pairwise passes (tag check, K-nearest search) run over a bucket-sorted copy
 // of the live agents instead of over all pairs, and observation rows leave through an LDS
 // transpose so that HBM sees whole lines.
+#include <algorithm>
 #include <cstring>
 #include <type_traits>
 
@@ -771,7 +772,21 @@ __device__ __forceinline__ void env_body(KernargParams pk, const StepOut out, co
     }
   } else {
     __syncthreads();
-    if (p.obs_mode == 1) {
+    if (p.obs_mode == kObsFullSplit) {
+      // Full observations of larger envs: full_rows_kernel writes the rows.  Here each row to be written whole
+      // is marked in its first feature; one that is kept gets its time feature.
+      if (out_act) {
+        float* const env_obs = out.obs + abase * p.D;
+        const float tf = static_cast<float>(t_out) * p.inv_T;
+        for (int i = lt; i < N; i += ts) {
+          float* const row = env_obs + int64_t(i) * p.D;
+          if (p.rows_kept && (L.pl[i] & kStaleBit))
+            row[4] = tf;
+          else
+            row[0] = __uint_as_float(kRowWanted);
+        }
+      }
+    } else if (p.obs_mode == 1) {
       // Full observations (the second observation mode of Sec. 5.1): row i holds the own
       // features and one slot per agent j in index order, zeros unless both are in play.  The
       // team walks the N * N slots of its env; consecutive lanes write consecutive 16-byte
@@ -939,6 +954,101 @@ __device__ __forceinline__ void env_body(KernargParams pk, const StepOut out, co
 
 #undef p
 #undef WD_NEW_PHASE
+
+// ----------------------------------------------------------------------------------
+// Rows of full observations (the second observation mode of Sec. 5.1), for envs of kFullSplitAgents and
+// more.  Workgroup (e, s) writes those of the rows s, s + slices, s + 2 slices, ... of env e that env_kernel
+// has marked (the taggers' rows come first and are always written: slices of consecutive rows would have
+// unequal work): a wave per row, the env's positions in LDS.  A row starts 0..3 floats past a 16-byte
+// boundary and is written by itself: its own features and what lies before the second boundary behind
+// them, and the floats behind the last boundary, lane by lane; everything between as aligned 16-byte
+// pieces, each the tail of one slot and the head of the next at an offset that is uniform over the row.
+//
+// Bound: HBM stores.  With the rows written by env_kernel's own workgroup, one per env, a batch of a few
+// hundred envs had four waves on a compute unit to produce hundreds of megabytes: 200 envs x 500 agents took
+// 357 us per iteration with a quarter of the rows (200 MB) to be written; now 69 (17 of them the step).
+// Consecutive rows per workgroup instead of every slices-th: 87.
+// ----------------------------------------------------------------------------------
+constexpr int kFullRowsPerGroup = 32;  // at most
+constexpr int kFullGroups = 2048;       // workgroups aimed at
+
+__global__ __launch_bounds__(kWorkgroupSize) void full_rows_kernel(const Params p, const int slices) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  uint32_t* const pl = reinterpret_cast<uint32_t*>(smem);  // [N]
+  __shared__ int16_t wanted[kFullRowsPerGroup];  // rows to write, in the first `n_wanted` places
+  __shared__ int n_wanted;
+  static_assert(kFullRowsPerGroup <= kWaveSize, "the first wave looks at the marks");
+  const int tid = threadIdx.x, lane = tid & (kWaveSize - 1);
+  const int e = blockIdx.x / slices, s = blockIdx.x - e * slices;
+  const int N = p.N, N_tag = p.N_tag, D = p.D;
+  const int64_t abase = int64_t(e) * N;
+  float* const env_obs = p.obs + abase * D;
+  if (tid < kWaveSize) {
+    const int i = s + lane * slices;
+    const bool mine = lane < kFullRowsPerGroup && i < N && __float_as_uint(env_obs[int64_t(i) * D]) == kRowWanted;
+    const uint64_t votes = __ballot(mine);
+    if (mine) wanted[__popcll(votes & ((1ull << lane) - 1ull))] = int16_t(i);
+    if (lane == 0) n_wanted = __popcll(votes);
+  }
+  for (int j = tid; j < N; j += kWorkgroupSize)
+    pl[j] = pack_pos(p.pos_x[abase + j], p.pos_y[abase + j], p.live[abase + j] != 0);
+  const float tf = static_cast<float>(p.t[e]) * p.inv_T;
+  __syncthreads();
+  const int n = n_wanted;
+  for (int r = tid >> 6; r < n; r += kWorkgroupSize / kWaveSize) {
+    const int i = __builtin_amdgcn_readfirstlane(int(wanted[r]));
+    const uint32_t me = uint32_t(__builtin_amdgcn_readfirstlane(int(pl[i])));
+    float* const row = env_obs + int64_t(i) * D;
+    const int at = int((reinterpret_cast<uintptr_t>(row) >> 2) & 3);  // floats past a 16-byte boundary
+    const int c1 = ((4 - at) & 3) + 8;                                // first column of the aligned pieces: 8..11
+    const int pieces = max(D - c1, 0) >> 2, c2 = c1 + 4 * pieces;     // and the first column behind them
+    {
+      const int col = lane < 16 ? (lane < min(c1, D) ? lane : -1) : (c2 + lane - 16 < D ? c2 + lane - 16 : -1);
+      if (col >= 0) {
+        float f;
+        if (col < 5) {
+          f = col == 0   ? static_cast<float>(pos_x_of(me)) * p.inv_G
+              : col == 1 ? static_cast<float>(pos_y_of(me)) * p.inv_G
+              : col == 2 ? (i < N_tag ? 1.0f : 0.0f)
+              : col == 3 ? ((me & kDeadBit) ? 0.0f : 1.0f)
+                         : tf;
+        } else {
+          const int j = (col - 5) >> 2, comp = (col - 5) & 3;
+          const FullSlot S = full_slot(me, pl[j], j < N_tag, p.inv_G);
+          f = comp == 0 ? S.a : comp == 1 ? S.b : comp == 2 ? S.c : S.d;
+        }
+        row[col] = f;
+      }
+    }
+    float4* const out = reinterpret_cast<float4*>(row + c1);
+    const int j0 = (c1 - 5) >> 2, shift = (c1 - 5) & 3;  // slot and component that the first piece starts with
+    if (me & kDeadBit) {
+      for (int g = lane; g < pieces; g += kWaveSize) out[g] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      continue;
+    }
+    const auto write = [&](auto kShift) {
+      constexpr int sh = decltype(kShift)::value;
+      for (int g = lane; g < pieces; g += kWaveSize) {
+        const int ja = j0 + g;
+        const FullSlot A = full_slot(me, pl[ja], ja < N_tag, p.inv_G);
+        if constexpr (sh == 0) {
+          out[g] = make_float4(A.a, A.b, A.c, A.d);
+        } else {
+          const FullSlot B = full_slot(me, pl[ja + 1], ja + 1 < N_tag, p.inv_G);
+          if constexpr (sh == 1) out[g] = make_float4(A.b, A.c, A.d, B.a);
+          if constexpr (sh == 2) out[g] = make_float4(A.c, A.d, B.a, B.b);
+          if constexpr (sh == 3) out[g] = make_float4(A.d, B.a, B.b, B.c);
+        }
+      }
+    };
+    switch (shift) {  // uniform over the wave
+      case 0: write(std::integral_constant<int, 0>{}); break;
+      case 1: write(std::integral_constant<int, 1>{}); break;
+      case 2: write(std::integral_constant<int, 2>{}); break;
+      default: write(std::integral_constant<int, 3>{}); break;
+    }
+  }
+}
 
 template <int WIDE, int KX, bool CN, bool BIG, bool ONE>
 __global__ __launch_bounds__(BIG ? kBigEnvWorkgroupSize : kMaxEnvWorkgroupSize)
@@ -1723,6 +1833,13 @@ hipError_t launch_env_variant(const Params& p, int mode, const float* probs, uin
     err = hipGetLastError();
     if (pipe && err == hipSuccess) err = hipEventRecord(pipe->rows_done, pipe->stream);
   }
+  if constexpr (KX == -1) {
+    if (err != hipSuccess || p.obs_mode != kObsFullSplit) return err;
+    const int per_group = std::min<int64_t>(std::max<int64_t>(int64_t(p.E) * p.N / kFullGroups, 8), kFullRowsPerGroup);
+    const int slices = (p.N + per_group - 1) / per_group;
+    hipLaunchKernelGGL(full_rows_kernel, dim3(p.E * slices), dim3(kWorkgroupSize), size_t(4 * p.N), stream, p, slices);
+    err = hipGetLastError();
+  }
   return err;
 }
 
@@ -1746,7 +1863,7 @@ hipError_t launch_rollout_variant(const Params& p, const Roll& roll, const float
 // Which compiled variant serves K: 1..8 (K compiled in; 4 is the benchmark shape, the only one that every key
 // width and layout has), 0 (K <= 8 at run time), -2 (K <= 16), -1 (any K).
 int variant_of(const Params& p) {
-  if (p.obs_mode == 1) return -1;
+  if (p.obs_mode != 0) return -1;
   if (p.K == 4) return 4;
   if (p.K >= 1 && p.K <= kMaxRegisterK && !p.wide && !p.big) return p.K;  // 32-bit keys in the small layout
   if (p.K <= kMaxRegisterK) return 0;
@@ -1828,7 +1945,7 @@ hipError_t launch_rollout(const Params& p, const Roll& roll, const float* ring, 
   return launch_rollout_variant<true, 0, false>(p, roll, ring, g, stream);
 }
 
-bool env_kernel_available(const Params& p) { return !(p.big && (p.obs_mode == 1 || p.K > kMaxRegisterK2)); }
+bool env_kernel_available(const Params& p) { return !(p.big && (p.obs_mode != 0 || p.K > kMaxRegisterK2)); }
 
 hipError_t launch_sample(const Params& p, const float* probs, uint64_t g, hipStream_t stream) {
   const int64_t total = int64_t(p.E) * p.NG;

@@ -928,3 +928,28 @@ def test_edge_case(name, fused):
     steps = min(3 * kw["episode_length"], 60)
     work = kw["num_envs"] * kw["num_agents"] ** 2  # pairs the oracle looks at per step
     lockstep(kw, steps, 77, fused=fused, sharded=0 if work < 5e7 else min(16, kw["num_envs"]))
+
+
+@pytest.mark.parametrize("num_envs,num_agents", [(7, 100), (5, 101), (6, 102), (5, 103), (3, 353), (1100, 64), (1100, 67)])
+def test_full_observation_rows_in_a_launch_of_their_own(num_envs, num_agents):
+    """Full observations from the sizes on at which the rows have their own kernel: every remainder of the row
+    length, against the oracle in separate and fused calls, and recorded slices (which start on 4-byte
+    boundaries for odd counts) against single iterations."""
+    import torch
+
+    import paper_2108_13976_amd as wd
+
+    kw = dict(num_envs=num_envs, num_agents=num_agents, num_taggers=9, grid_size=int((12 * num_agents) ** 0.5),
+              episode_length=4, obs_mode=1, seed=91)
+    for fused in (False, True):
+        lockstep(kw, 9 if num_envs < 100 else 6, 91, fused=fused, sharded=0 if num_envs < 100 else 16)
+    k = 3
+    ring = upload(np.stack([probs_for_step(91, r, num_envs, num_agents) for r in range(k)]), "cuda:0")
+    a, b = make_gpu(kw), make_gpu(kw)
+    a.reset(wd.WD_RESET_ALL), b.reset(wd.WD_RESET_ALL)
+    for _ in range(2):
+        rec = a.rollout(ring, k)
+        for s in range(k):
+            b.iterate(ring[s])
+            assert torch.equal(rec["obs"][s], b.obs)
+    a.close(), b.close()
