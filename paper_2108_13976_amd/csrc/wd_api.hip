@@ -217,13 +217,20 @@ bool plan_env_kernels(const wd_config& c, wd::Params* p, bool big, bool big_tabl
     ++ts_log2;
   }
   p->wg_size = 256;
-  // An env of more than 1024 agents takes more LDS than lets eight 256-thread workgroups share
-  // a CU: wider workgroups keep the CU's wave slots filled.  Measured at E = 2000, us per
-  // iteration with 256 / 512 / 1024 threads: N = 1100 105 / 92 / -, N = 2000 249 / 218 / -,
-  // N = 3000 443 / 338 / 462, N = 3500 840 / 586 / 526, N = 4000 887 / 644 / 584.
-  if (!big && N > 1024) {
-    ts_log2 = N > 3072 ? 10 : 9;
-    p->wg_size = 1 << ts_log2;
+  // Wider workgroups.  A batch of up to a thousand envs of more than 256 agents is bound by one workgroup's
+  // chain of phases, which more lanes shorten; and an env of more than 1024 agents takes more LDS than lets
+  // eight 256-thread workgroups share a CU, so that wider ones keep the CU's wave slots filled.
+  // Measured, us per iteration, 256 / 512 / 1024 threads (K = 4, strips): 10 x 333 18.1 / 17.4 / -,
+  // 450 x 333 23.1 / 22.4, 777 x 333 25.3 / 25.4; 10 x 700 19.2 / 17.8 / 18.2, 300 x 1000 26.9 / 24.7 / 26.1,
+  // 777 x 1000 34.9 / 33.8; 200 x 1300 - / 25.5 / 24.6, 450 x 1300 - / 31.0 / 31.5; 200 x 2000 - / 30.1 / 28.5,
+  // 777 x 2000 - / 67.5 / 69.5; K = 8: 450 x 1000 38.6 / 35.8, 777 x 1000 49.2 / 62.6; 300 x 3000 - / 50.0 / 48.1, 1500 x 3000 - / 159 / 151.
+  if (!big && N > 256 && ts_log2 <= 8) {
+    if (N > 1024)
+      ts_log2 = (c.num_envs <= 256 || N > 2500) ? 10 : 9;
+    else if (c.obs_mode == WD_OBS_PARTIAL && p->K >= 1 && p->K <= wd::kMaxRegisterK &&
+             c.num_envs <= ((N <= 512 || p->K > 4 || p->K < 2) ? 512 : 1024))  // (those K: half the waves on a CU, for registers)
+      ts_log2 = 9;  // (bucket rings are slower so: 500 x 1000, K = 12 88 -> 112)
+    if (ts_log2 > 8) p->wg_size = 1 << ts_log2;
   }
   if (big) {  // one env per 1024-thread workgroup
     ts_log2 = 10;
@@ -293,16 +300,15 @@ bool plan_env_kernels(const wd_config& c, wd::Params* p, bool big, bool big_tabl
   // field 0x7FFF.  That needs room in 16 bits: the keys of such entries, at least (32767 - A)^2 with
   // A = (G - 1) << h, must lie above every key of a live pair, below 2 A^2 + 2^(2 h).  Larger grids
   // take 64-bit keys and the bucket rings.
-  if (narrow && !big && c.obs_mode == WD_OBS_PARTIAL && p->K >= 1 && p->K <= wd::kMaxRegisterK) {
+  if (!big && c.obs_mode == WD_OBS_PARTIAL && p->K >= 1 && p->K <= wd::kMaxRegisterK) {
     const int h = (p->idx_bits + 1) / 2;
     const int64_t A = int64_t(G - 1) << h;
     const int64_t dead_min = A < 32767 ? (32767 - A) * (32767 - A) : 0;
-    if (A < 32767 && 2 * A * A + (int64_t(1) << (2 * h)) <= dead_min) {
+    narrow = A < 32767 && 2 * A * A + (int64_t(1) << (2 * h)) <= dead_min;  // (the bucket form's bound does not matter here)
+    if (narrow) {
       p->pos_shift = h;
       p->key_shift = 2 * h;
       p->dead_key_min = uint32_t(dead_min);
-    } else {
-      narrow = false;
     }
   }
   // Else, in the large-env layout: keys that need all 32 bits, the dead mark moved into bit 15
@@ -423,7 +429,9 @@ void plan_spread(const wd_config& c, wd::Params* p) {
   p->g_stride_acc = (p->acc_tags + 1 + 3) / 4 * 4;
 }
 
-int fill_params(const wd_config& c, const wd_buffers& b, wd::Params* p) {
+// (`pair_as_ever`: the large-env pair wherever it served before the small layout's strip search: wd_iterate_static's
+// set of configurations with work tables, and so of those it refuses for want of room, stays what it was)
+int fill_params(const wd_config& c, const wd_buffers& b, wd::Params* p, bool pair_as_ever) {
   std::memset(p, 0, sizeof(*p));
   p->E = c.num_envs;
   p->N = c.num_agents;
@@ -464,16 +472,21 @@ int fill_params(const wd_config& c, const wd_buffers& b, wd::Params* p) {
   p->n_live_runners = b.n_live_runners;
   p->tags_step = b.tags_step;
   // Two layouts serve an env: one workgroup with every table in LDS, or the large-env pair of
-  // kernels (a 1024-thread workgroup for the step, then the neighbour search spread over many
-  // workgroups).  The pair costs a second launch and a round trip of the tables through device
-  // memory, but puts a whole chip on the search of a few envs, so it wins while the batch is too
-  // small to fill the chip with one workgroup per env.  Measured crossovers (partial
-  // observations, K = 4, us per iteration one workgroup -> pair): E = 10: N = 500 26 -> 22,
-  // N = 2000 64 -> 26, N = 6000 158 -> 36; E = 320: N = 1000 39 -> 45, N = 2000 82 -> 66,
-  // N = 4000 133 -> 114; E = 640: N = 2000 92 -> 106, N = 4000 215 -> 226, N = 6000 306 -> 381.
+  // kernels (the step, then the neighbour search spread over many workgroups).  The pair costs a second
+  // launch and a round trip of the tables through device memory, but puts a whole chip on the search of a
+  // few envs, so it wins while the batch is too small to fill the chip with one workgroup per env.
+  // Measured, K = 4, us per iteration, one workgroup -> pair.  With the strip search: N = 1000: E = 10 19.0 -> 22.4,
+  // 300 24.7 -> 38.0; N = 1300: E = 10 20.5 -> 20.8; N = 2000: E = 10 22.9 -> 21.2, 100 26.9 -> 27.8,
+  // 300 35.2 -> 46.0 (K = 8: E = 60 34.9 -> 31.3, 200 38.3 -> 39.1); N = 3000: E = 10 26.9 -> 22.9, 100 32.2 -> 32.5, 300 48.1 -> 68.5.  With bucket rings
+  // (64-bit keys, K > 8): E = 10: N = 500 26 -> 22, N = 2000 64 -> 26, N = 6000 158 -> 36; E = 320:
+  // N = 1000 39 -> 45, N = 2000 82 -> 66, N = 4000 133 -> 114; E = 640: N = 2000 92 -> 106.
   const bool pair_serves = c.obs_mode == WD_OBS_PARTIAL && p->K <= wd::kMaxRegisterK2;
   const int64_t pair_up_to = c.num_agents <= 1024 ? 3ll * c.num_agents / 10 : 450;  // envs
-  const bool prefer_pair = pair_serves && c.num_agents >= 384 && c.num_envs <= pair_up_to;
+  bool prefer_pair = pair_serves && c.num_agents >= 384 && c.num_envs <= pair_up_to;
+  if (prefer_pair && !pair_as_ever && c.num_envs > (c.num_agents - 1300) / (p->K > 4 ? 5 : 18)) {
+    wd::Params small = *p;
+    if (plan_env_kernels(c, &small, false) && small.strips) prefer_pair = false;
+  }
   const wd::Params filled = *p;
   bool planned = prefer_pair && plan_env_kernels(c, p, true, true);
   if (!planned && prefer_pair) {
@@ -583,7 +596,7 @@ int wd_create(const wd_config* cfg, const wd_buffers* bufs, wd_handle** out) {
   for (const void* ptr : ptrs)
     if (!aligned256(ptr)) return WD_E_ALIGN;
   wd::Params params;
-  rc = fill_params(*cfg, *bufs, &params);
+  rc = fill_params(*cfg, *bufs, &params, false);
   if (rc != WD_OK) return rc;
   wd_handle* h = new (std::nothrow) wd_handle();
   if (!h) return WD_E_NULL;
@@ -688,7 +701,7 @@ int wd_iterate_static(const wd_config* cfg, const wd_buffers* bufs, const float*
   for (const void* ptr : ptrs)
     if (!aligned256(ptr)) return WD_E_ALIGN;
   wd::Params params;
-  rc = fill_params(*cfg, *bufs, &params);
+  rc = fill_params(*cfg, *bufs, &params, true);
   if (rc != WD_OK) return rc;
   if (!probs_aligned(params, probs)) return WD_E_ALIGN;
   params.big_spread = 0;  // (its accumulators have to start clear; the pair with one workgroup per env needs nothing of the kind)

@@ -917,6 +917,16 @@ EDGE = {
     "beyond_wave_agents": dict(num_envs=300, num_agents=65, num_taggers=7, grid_size=25, episode_length=10, obs_k=4),
     "beyond_wave_grid": dict(num_envs=3, num_agents=40, num_taggers=4, grid_size=4097, episode_length=8, obs_k=4, tag_r2=10**6),
     "many_small_envs_k_two": dict(num_envs=8500, num_agents=30, num_taggers=3, grid_size=12, episode_length=8, obs_k=2),
+    # where the layouts meet: 512- and 1024-thread workgroups of small batches, strips up to the largest grid whose
+    # scaled positions fit 16 bits (N = 2049: 212 cells a side) and 64-bit keys beyond, few large envs in the pair
+    "wide_workgroup_257": dict(num_envs=3, num_agents=257, num_taggers=30, grid_size=50, episode_length=8),
+    "wide_workgroup_k_five": dict(num_envs=2, num_agents=600, num_taggers=60, grid_size=80, episode_length=6, obs_k=5),
+    "wide_workgroup_1025": dict(num_envs=3, num_agents=1025, num_taggers=100, grid_size=100, episode_length=4),
+    "strips_largest_grid": dict(num_envs=48, num_agents=2049, num_taggers=200, grid_size=212, episode_length=2),
+    "strips_grid_too_large": dict(num_envs=48, num_agents=2049, num_taggers=200, grid_size=213, episode_length=2),
+    "strips_three_thousand": dict(num_envs=100, num_agents=3000, num_taggers=300, grid_size=193, episode_length=2),
+    "pair_few_envs": dict(num_envs=2, num_agents=1400, num_taggers=140, grid_size=130, episode_length=4),
+    "pair_one_workgroup_step_64_bit_keys": dict(num_envs=110, num_agents=2100, num_taggers=100, grid_size=700, episode_length=2),
     "large_env_two_thousand": dict(num_envs=4, num_agents=2000, num_taggers=2000 - 1, grid_size=64, episode_length=3, obs_k=8),
 }
 
