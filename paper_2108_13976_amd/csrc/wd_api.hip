@@ -109,10 +109,11 @@ bool plan_strip_layout(const wd_config& c, wd::Params* p) {
   const int64_t NPAD = p->NPAD;
   const int tpw = p->teams_per_wg;
   // strips about 1.5 expected K-th-neighbour distances tall: G / R = 1.5 G sqrt(K / (pi n))
-  p->strip_scale = float(std::sqrt(3.14159265358979 / double(K)) / 1.5);
+  const int KS = wd::strip_list_size(K);
+  p->strip_scale = float(std::sqrt(3.14159265358979 / double(KS)) / 1.5);
   // the own window overhangs the list by up to its half width, and the window of a neighbouring strip then sits beyond it
-  p->pad_l = wd::strip_pad(K);
-  p->pad_r = wd::strip_pad(K);
+  p->pad_l = wd::strip_pad(KS);
+  p->pad_r = wd::strip_pad(KS);
   const int64_t slots = NPAD + p->pad_l + p->pad_r;
   const int r_want = std::min<int64_t>(G, int64_t(std::ceil(double(p->strip_scale) * std::sqrt(double(N)))) + 1);
   const int64_t waves = p->wg_size / wd::kWaveSize;
@@ -223,13 +224,14 @@ bool plan_env_kernels(const wd_config& c, wd::Params* p, bool big, bool big_tabl
   // Measured, us per iteration, 256 / 512 / 1024 threads (K = 4, strips): 10 x 333 18.1 / 17.4 / -,
   // 450 x 333 23.1 / 22.4, 777 x 333 25.3 / 25.4; 10 x 700 19.2 / 17.8 / 18.2, 300 x 1000 26.9 / 24.7 / 26.1,
   // 777 x 1000 34.9 / 33.8; 200 x 1300 - / 25.5 / 24.6, 450 x 1300 - / 31.0 / 31.5; 200 x 2000 - / 30.1 / 28.5,
-  // 777 x 2000 - / 67.5 / 69.5; K = 8: 450 x 1000 38.6 / 35.8, 777 x 1000 49.2 / 62.6; 300 x 3000 - / 50.0 / 48.1, 1500 x 3000 - / 159 / 151.
+  // 777 x 2000 - / 67.5 / 69.5; K = 8: 450 x 1000 38.6 / 35.8, 777 x 1000 49.2 / 62.6;
+  // K = 12: 200 x 1000 51.7 / 40.7, 500 x 1000 62.3 / 76.6; K = 4: 300 x 3000 - / 50.0 / 48.1, 1500 x 3000 - / 159 / 151.
   if (!big && N > 256 && ts_log2 <= 8) {
     if (N > 1024)
       ts_log2 = (c.num_envs <= 256 || N > 2500) ? 10 : 9;
-    else if (c.obs_mode == WD_OBS_PARTIAL && p->K >= 1 && p->K <= wd::kMaxRegisterK &&
-             c.num_envs <= ((N <= 512 || p->K > 4 || p->K < 2) ? 512 : 1024))  // (those K: half the waves on a CU, for registers)
-      ts_log2 = 9;  // (bucket rings are slower so: 500 x 1000, K = 12 88 -> 112)
+    else if (c.obs_mode == WD_OBS_PARTIAL && p->K >= 1 && p->K <= wd::kMaxRegisterK2 &&
+             c.num_envs <= (p->K > wd::kMaxRegisterK ? 256 : (N <= 512 || p->K > 4 || p->K < 2) ? 512 : 1024))
+      ts_log2 = 9;  // (K = 1 and K > 4: half the waves on a CU, for registers; K > 8: fewer still, for staged rows)
     if (ts_log2 > 8) p->wg_size = 1 << ts_log2;
   }
   if (big) {  // one env per 1024-thread workgroup
@@ -300,7 +302,7 @@ bool plan_env_kernels(const wd_config& c, wd::Params* p, bool big, bool big_tabl
   // field 0x7FFF.  That needs room in 16 bits: the keys of such entries, at least (32767 - A)^2 with
   // A = (G - 1) << h, must lie above every key of a live pair, below 2 A^2 + 2^(2 h).  Larger grids
   // take 64-bit keys and the bucket rings.
-  if (!big && c.obs_mode == WD_OBS_PARTIAL && p->K >= 1 && p->K <= wd::kMaxRegisterK) {
+  if (!big && c.obs_mode == WD_OBS_PARTIAL && p->K >= 1 && p->K <= wd::kMaxRegisterK2) {
     const int h = (p->idx_bits + 1) / 2;
     const int64_t A = int64_t(G - 1) << h;
     const int64_t dead_min = A < 32767 ? (32767 - A) * (32767 - A) : 0;
@@ -322,7 +324,7 @@ bool plan_env_kernels(const wd_config& c, wd::Params* p, bool big, bool big_tabl
   const bool register_path = c.obs_mode == WD_OBS_PARTIAL && p->K <= wd::kMaxRegisterK2;
   // The variants with 32-bit keys and K compiled in (small layout) sort by strip and column
   // instead of by square bucket (wd_dev_strips.h).
-  p->strips = (!big && p->wide == 0 && c.obs_mode == WD_OBS_PARTIAL && p->K >= 1 && p->K <= wd::kMaxRegisterK) ? 1 : 0;
+  p->strips = (!big && p->wide == 0 && c.obs_mode == WD_OBS_PARTIAL && p->K >= 1 && p->K <= wd::kMaxRegisterK2) ? 1 : 0;
   if (p->strips) return plan_strip_layout(c, p);
 
   int64_t off = 0;
@@ -477,13 +479,17 @@ int fill_params(const wd_config& c, const wd_buffers& b, wd::Params* p, bool pai
   // few envs, so it wins while the batch is too small to fill the chip with one workgroup per env.
   // Measured, K = 4, us per iteration, one workgroup -> pair.  With the strip search: N = 1000: E = 10 19.0 -> 22.4,
   // 300 24.7 -> 38.0; N = 1300: E = 10 20.5 -> 20.8; N = 2000: E = 10 22.9 -> 21.2, 100 26.9 -> 27.8,
-  // 300 35.2 -> 46.0 (K = 8: E = 60 34.9 -> 31.3, 200 38.3 -> 39.1); N = 3000: E = 10 26.9 -> 22.9, 100 32.2 -> 32.5, 300 48.1 -> 68.5.  With bucket rings
-  // (64-bit keys, K > 8): E = 10: N = 500 26 -> 22, N = 2000 64 -> 26, N = 6000 158 -> 36; E = 320:
+  // 300 35.2 -> 46.0 (K = 8: E = 60 34.9 -> 31.3, 200 38.3 -> 39.1; K = 12:
+  // N = 500: E = 60 41.7 -> 43.5; N = 1000: E = 60 39.2 -> 38.4, 200 40.7 -> 45.8; N = 2000: E = 200 63.8 -> 50.5); N = 3000: E = 10 26.9 -> 22.9, 100 32.2 -> 32.5, 300 48.1 -> 68.5.  With bucket rings
+  // (64-bit keys): E = 10: N = 500 26 -> 22, N = 2000 64 -> 26, N = 6000 158 -> 36; E = 320:
   // N = 1000 39 -> 45, N = 2000 82 -> 66, N = 4000 133 -> 114; E = 640: N = 2000 92 -> 106.
   const bool pair_serves = c.obs_mode == WD_OBS_PARTIAL && p->K <= wd::kMaxRegisterK2;
   const int64_t pair_up_to = c.num_agents <= 1024 ? 3ll * c.num_agents / 10 : 450;  // envs
   bool prefer_pair = pair_serves && c.num_agents >= 384 && c.num_envs <= pair_up_to;
-  if (prefer_pair && !pair_as_ever && c.num_envs > (c.num_agents - 1300) / (p->K > 4 ? 5 : 18)) {
+  // the largest batch that the pair serves faster than strips do
+  const int pair_envs = p->K > wd::kMaxRegisterK ? (c.num_agents - 500) / (p->K > wd::kMaxRegisterK3 ? 2 : 4)
+                                                    : (c.num_agents - 1300) / (p->K > 4 ? 5 : 18);
+  if (prefer_pair && !pair_as_ever && c.num_envs > pair_envs) {
     wd::Params small = *p;
     if (plan_env_kernels(c, &small, false) && small.strips) prefer_pair = false;
   }

@@ -22,9 +22,14 @@ constexpr int kSpreadTagSide = 64;       // its table of taggers: at most this m
 constexpr int kWaveSize = 64;
 constexpr int kNumActions = 5;
 constexpr int kMaxRegisterK = 8;        // K up to this keeps the candidate list in 8 registers,
-constexpr int kMaxRegisterK2 = 16;      // up to this in 16 (a variant of its own)
-// List size of a kernel variant KX (KX > 0: exactly K; 0: K <= 8; -2: K <= 16).
-constexpr int register_list_size(int kx) { return kx > 0 ? kx : (kx == -2 ? kMaxRegisterK2 : kMaxRegisterK); }
+constexpr int kMaxRegisterK2 = 16;      // up to this in 16 (a variant of its own),
+constexpr int kMaxRegisterK3 = 12;      // with strips up to this in 12
+// List size of a kernel variant KX (KX > 0: exactly K; 0: K <= 8; -3: K <= 12; -2: K <= 16).
+constexpr int register_list_size(int kx) {
+  return kx > 0 ? kx : kx == -2 ? kMaxRegisterK2 : kx == -3 ? kMaxRegisterK3 : kMaxRegisterK;
+}
+// Neighbours that the strip search of a configuration looks for.
+constexpr int strip_list_size(int k) { return k <= kMaxRegisterK ? k : k <= kMaxRegisterK3 ? kMaxRegisterK3 : kMaxRegisterK2; }
 // Window sizes of the strip search for K neighbours: entries on either side of the agent's slot in
 // its own strip, and on either side of its column in the strip above and the strip below; for
 // the agents that these do not settle, a second try with windows twice as wide and two more

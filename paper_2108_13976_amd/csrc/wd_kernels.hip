@@ -57,8 +57,8 @@ __global__ __launch_bounds__(kWorkgroupSize) void init_start_positions_kernel(co
 // ----------------------------------------------------------------------------------
 // The env-per-team kernel: step, reset, or a whole iteration (sample + step + reset).
 // KX > 0: K == KX known at compile time (1..8): the neighbour list and the row live in registers
-// and rows leave through the LDS transpose.  KX == 0: K <= 8 at run time, KX == -2: K <= 16 (the
-// list in registers, rows built in LDS).  KX == -1: any K, sixteen neighbours at a time, rows
+// and rows leave through the LDS transpose.  KX == 0: K <= 8 at run time, KX == -3: K <= 12, KX == -2:
+// K <= 16 (the list in registers, rows built in LDS).  KX == -1: any K, sixteen neighbours at a time, rows
 // written directly (slow path).
 // ----------------------------------------------------------------------------------
 // Where one iteration's outputs go: the in-place buffers, or a slice of a roll-out's arrays.
@@ -91,16 +91,22 @@ struct LoopState {
   bool last;      // the in-place state arrays are written in this iteration
 };
 
+template <int WIDE, int KX, bool BIG>
+constexpr bool has_strips() {
+  return WIDE == kKeys31 && !BIG && (KX > 0 || KX == -2 || KX == -3);
+}
+
 template <int WIDE, int KX, bool CN, bool BIG, bool LOOPED, bool ONE>
 __device__ __forceinline__ void env_body(KernargParams pk, const StepOut out, const int mode,
                                          const float* __restrict__ probs, uint32_t g_lo, uint32_t g_hi,
                                          unsigned char* smem, const int tid, LoopState& ls) {
   using SL = SortedList<WIDE>;
   using Key = typename SL::Key;
-  // 32-bit keys with K compiled in, small layout: the live agents are sorted by strip and column
+  // 32-bit keys and K = 1 .. 16, small layout: the live agents are sorted by strip and column
   // and the neighbour search reads fixed windows of that list; the other variants sort by
   // square buckets and search bucket rings
-  constexpr bool STRIP = WIDE == kKeys31 && !BIG && KX > 0;
+  constexpr bool STRIP = has_strips<WIDE, KX, BIG>();
+  constexpr int KS = register_list_size(KX);  // neighbours that the strip search looks for (K of them are wanted)
   // ONE: the launch has one team per workgroup, so everything that depends on the team (table
   // addresses, the env's scalars, the strip geometry) is uniform and lives in scalar registers
   const int ts = 1 << p.ts_log2;
@@ -512,9 +518,9 @@ __device__ __forceinline__ void env_body(KernargParams pk, const StepOut out, co
           if ((me >> 16) != kStripDeadY) {  // not tagged in this step
             Key keys[KT];
             if (few) {
-              strip_scan_all<KX>(keys, me, uint32_t(q), uint32_t(n_sorted), p.key_shift, Lt.sorted.pos, Lt.sorted.id);
+              strip_scan_all<KS>(keys, me, uint32_t(q), uint32_t(n_sorted), p.key_shift, Lt.sorted.pos, Lt.sorted.id);
               put_neighbours_of(Lt, Lt.sorted.id[q], keys);
-            } else if (strip_window_search<KX, strip_half_own(KX), strip_half_adj(KX), 0, false>(
+            } else if (strip_window_search<KS, strip_half_own(KS), strip_half_adj(KS), 0, false>(
                            keys, me, q, 0, st, p.key_shift, n_sorted, p.pad_l, Lt.sorted.pos, Lt.sorted.id, Lt.starts,
                            Lt.edges)) {
               put_neighbours_of(Lt, Lt.sorted.id[q], keys);
@@ -543,7 +549,7 @@ __device__ __forceinline__ void env_body(KernargParams pk, const StepOut out, co
         const int q = Lt.retry[j];
         const uint32_t me = Lt.sorted.pos[q];
         Key keys[KT];
-        bool ok = strip_window_search<KX, strip_half_own2(KX), strip_half_adj2(KX), strip_half_far2(KX), true>(
+        bool ok = strip_window_search<KS, strip_half_own2(KS), strip_half_adj2(KS), strip_half_far2(KS), true>(
             keys, me, q, side, st, p.key_shift, n_sorted, p.pad_l, Lt.sorted.pos, Lt.sorted.id, Lt.starts, Lt.edges);
         if (side) return;  // the even lane goes on for both
         if (!ok) {
@@ -551,7 +557,7 @@ __device__ __forceinline__ void env_body(KernargParams pk, const StepOut out, co
           if (at < kStripQueue2) {
             reinterpret_cast<uint16_t*>(Lt.misc + 4)[at] = uint16_t(q);  // (the scan scratch, idle by now)
           } else {  // the queue is full: search here and now
-            strip_block_search<KX>(keys, me, uint32_t(q), st, p.key_shift, G, Lt.sorted.pos, Lt.sorted.id, Lt.starts,
+            strip_block_search<KS>(keys, me, uint32_t(q), st, p.key_shift, G, Lt.sorted.pos, Lt.sorted.id, Lt.starts,
                                    Lt.edges);
             ok = true;
           }
@@ -612,7 +618,7 @@ __device__ __forceinline__ void env_body(KernargParams pk, const StepOut out, co
         for (int j = wave_lane; j < n_wait; j += wave_stride) {
           const uint32_t q = queue2[j];
           Key keys[KT];
-          strip_block_search<KX>(keys, Lt.sorted.pos[q], q, st, p.key_shift, G, Lt.sorted.pos, Lt.sorted.id, Lt.starts,
+          strip_block_search<KS>(keys, Lt.sorted.pos[q], q, st, p.key_shift, G, Lt.sorted.pos, Lt.sorted.id, Lt.starts,
                                  Lt.edges);
           put_neighbours_of(Lt, Lt.sorted.id[q], keys);
         }
@@ -1788,7 +1794,7 @@ hipError_t ensure_dynamic_lds(Kernel kernel, int bytes) {
 
 // (one team per workgroup gets the variant whose team-dependent values are uniform, where one is compiled)
 template <int WIDE, int KX, bool BIG>
-constexpr bool kHasOneTeamVariant = WIDE == 0 && !BIG && KX > 0;
+constexpr bool kHasOneTeamVariant = has_strips<WIDE, KX, BIG>();
 
 template <int WIDE, int KX, bool CN, bool BIG, bool ONE = false>
 hipError_t launch_env_variant(const Params& p, int mode, const float* probs, uint64_t g, hipStream_t stream,
@@ -1867,6 +1873,7 @@ int variant_of(const Params& p) {
   if (p.K == 4) return 4;
   if (p.K >= 1 && p.K <= kMaxRegisterK && !p.wide && !p.big) return p.K;  // 32-bit keys in the small layout
   if (p.K <= kMaxRegisterK) return 0;
+  if (p.strips && p.K <= kMaxRegisterK3) return -3;
   if (p.K <= kMaxRegisterK2) return -2;
   return -1;
 }
@@ -1902,6 +1909,7 @@ int variant_of(const Params& p) {
       if (kx == 2) return fn<false, 2, false, false>(p, ##__VA_ARGS__);                    \
       if (kx == 1) return fn<false, 1, false, false>(p, ##__VA_ARGS__);                    \
       if (kx == 0) return fn<false, 0, false, false>(p, ##__VA_ARGS__);                    \
+      if (kx == -3) return fn<false, -3, false, false>(p, ##__VA_ARGS__);                  \
       if (kx == -2) return fn<false, -2, false, false>(p, ##__VA_ARGS__);                  \
       return fn<false, -1, false, false>(p, ##__VA_ARGS__);                                \
     }                                                                                      \

@@ -925,6 +925,13 @@ EDGE = {
     "strips_largest_grid": dict(num_envs=48, num_agents=2049, num_taggers=200, grid_size=212, episode_length=2),
     "strips_grid_too_large": dict(num_envs=48, num_agents=2049, num_taggers=200, grid_size=213, episode_length=2),
     "strips_three_thousand": dict(num_envs=100, num_agents=3000, num_taggers=300, grid_size=193, episode_length=2),
+    # K = 9 .. 16 with strips: lists of 12 and 16 keys, one env and several envs per workgroup, fewer agents left than K
+    "k_nine_strips": dict(num_envs=3, num_agents=300, num_taggers=30, grid_size=40, episode_length=8, obs_k=9),
+    "k_twelve_strips_packed": dict(num_envs=300, num_agents=70, num_taggers=9, grid_size=18, episode_length=25, obs_k=12),
+    "k_thirteen_strips_crowded": dict(num_envs=3, num_agents=203, num_taggers=20, grid_size=5, episode_length=6, obs_k=13, tag_r2=0),
+    "k_sixteen_strips_packed": dict(num_envs=400, num_agents=67, num_taggers=7, grid_size=30, episode_length=6, obs_k=16),
+    "k_sixteen_strips_wide_workgroup": dict(num_envs=60, num_agents=600, num_taggers=60, grid_size=80, episode_length=3, obs_k=16),
+    "k_eleven_strips_wide": dict(num_envs=480, num_agents=1500, num_taggers=150, grid_size=130, episode_length=2, obs_k=11),
     "pair_few_envs": dict(num_envs=2, num_agents=1400, num_taggers=140, grid_size=130, episode_length=4),
     "pair_one_workgroup_step_64_bit_keys": dict(num_envs=110, num_agents=2100, num_taggers=100, grid_size=700, episode_length=2),
     "large_env_two_thousand": dict(num_envs=4, num_agents=2000, num_taggers=2000 - 1, grid_size=64, episode_length=3, obs_k=8),
