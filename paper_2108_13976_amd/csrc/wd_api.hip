@@ -40,9 +40,7 @@ constexpr int kMaxGrid = 32767;
 // spread form of the large-env pair: while its observation kernel has a compute unit per workgroup to spare
 constexpr int kSpreadMaxWorkgroups = 192;
 constexpr int kSpreadMinAgents = 1024;
-// envs: one round of waves on the chip (256 compute units x 32 waves).  Measured, us per wd_iterate, wave per env / general
-// kernel: 8192 envs x 50 agents 22.6 / 27.7, 8192 x 32 16.3 / 23.1; beyond one round 20000 x 16 20.5 / 26.4, but 20000 x 50
-// 46.9 / 41.3, 20000 x 64 58.1 / 39.0 and 50000 x 5 38.5 / 32.8 (a wave for five agents)
+// envs: one round of waves on the chip (256 compute units x 32 waves)
 constexpr int kWaveEnvsMaxBatch = 8192;
 
 // full observations: from this many agents per env on, or from a wave's agents and this many bytes of rows on,
@@ -519,6 +517,17 @@ int fill_params(const wd_config& c, const wd_buffers& b, wd::Params* p, bool pai
                   c.obs_mode == WD_OBS_PARTIAL && p->K <= wd::kMaxRegisterK2 && c.grid_size <= 4096)
                      ? 1
                      : 0;
+  // small_env_kernel, also a wave per env: envs of 65 to 128 agents at any batch size; of 32 and more once the batch
+  // has 128 000 agents (a wave then has others to wait with), and of 12 and more beyond wave_env_kernel's batches.
+  // Measured, K = 4, us per iteration: env_kernel -> small_env_kernel: 10 x 100 14.7 -> 11.7, 3000 x 100
+  // 26.8 -> 20.1, 20000 x 100 86.5 -> 70.7, 3000 x 128 28.9 -> 22.9, 15000 x 100, K = 8 105.8 -> 78.3; 20000 x 5 24.4 -> 28.0,
+  // 20000 x 12 27.8 -> 25.3, 20000 x 32 38.5 -> 30.7, 20000 x 64 52.3 -> 44.0.  wave_env_kernel -> small_env_kernel:
+  // 10 x 64 7.1 -> 7.7, 2000 x 64 10.7 -> 10.4, 8000 x 64 27.7 -> 20.8; 2000 x 50 9.7 -> 11.1, 5000 x 50 17.2 -> 16.3;
+  // 5000 x 32 12.3 -> 12.2, 8000 x 20 13.2 -> 14.8.
+  if (p->strips && c.num_agents <= wd::kSmallEnvAgents && p->K <= wd::kMaxRegisterK &&
+      (c.num_agents > wd::kWaveSize || (c.num_agents >= 32 && int64_t(c.num_envs) * c.num_agents >= 128000) ||
+       (c.num_agents >= 12 && c.num_envs > kWaveEnvsMaxBatch)))
+    p->wave_envs = wd::kSmallEnvs;
   return WD_OK;
 }
 

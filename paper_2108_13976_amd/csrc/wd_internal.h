@@ -46,6 +46,7 @@ constexpr int strip_pad(int k) {
   const int a = strip_half_own(k) + 2 * strip_half_adj(k), b = 2 * strip_half_adj2(k), c = strip_half_own2(k);
   return a > b ? (a > c ? a : c) : (b > c ? b : c);
 }
+constexpr int kSmallEnvAgents = 128, kSmallEnvs = 2;  // small_env_kernel: two agents per lane (Params.wave_envs)
 constexpr int kStripScanAll = 64;  // lists up to this length are scanned whole instead of through windows
 constexpr int kStripQueue2 = 32;  // agents per env that may wait for the third, exact block search
 // Params.obs_mode: 0 partial, 1 full, and full with the rows written by a kernel of their own (full_rows_kernel)
@@ -142,7 +143,8 @@ struct Params {
   uint32_t* g_acc;         // [2][E][g_stride_acc]: credits per tagger, number of tags
   int64_t g_stride_acc;
   int32_t acc_credits, acc_tags;  // word offsets inside one env's accumulators
-  int32_t wave_envs;     // 1: envs of at most 64 agents in a small batch run in wave_env_kernel, a wave per env
+  int32_t wave_envs;     // 1: envs of at most 64 agents in a small batch run in wave_env_kernel; kSmallEnvs: envs of up to
+                         // kSmallEnvAgents in small_env_kernel; a wave per env in both
   // device buffers (borrowed from the caller)
   int32_t *pos_x, *pos_y, *pos_x0, *pos_y0, *live, *action;
   float* reward;

@@ -1775,6 +1775,356 @@ hipError_t launch_wave_kernel(const Params& p, int mode, const Roll& roll, const
   return hipGetLastError();
 }
 
+// ----------------------------------------------------------------------------------
+// Envs of up to 128 agents: one wave per env, no workgroup barrier.  Lane g owns the group of agents
+// 4 g .. 4 g + 3 while it samples and moves (16-byte accesses, one random block), lanes own agents l and
+// l + 64 for the tag check, rewards and rows, and entries l and l + 64 of the list of agents in play for the
+// search; the wave's tables in LDS carry the state from one to the other.  The list holds the agents in play in
+// index order, so an entry's slot takes the place of its index in the keys, and it is scanned whole: a
+// candidate costs its scaled difference, its key (one dot product with the slot as accumulator) and the
+// insertion, and every lane reads the same four entries at once.  No sort, no windows, no second tries.
+//
+// Bound: vector ALU (28.6 M wave-instructions at 20000 envs x 100 agents) next to 272 MB of traffic.  env_kernel
+// spent as many, but its four waves waited for each other at a dozen barriers, half of them for the windows' later
+// tries: 86.5 us per iteration, 70.7 here (3.9 TB/s); 3000 x 100 26.8 -> 20.1.  At most 80 registers (six waves per
+// SIMD): with 64 the rows spill, 88.9 us.  Two or eight envs per workgroup: 70.8, 73.0.
+// ----------------------------------------------------------------------------------
+constexpr int kSmallWaves = 4;  // envs per workgroup
+
+template <int KC>
+struct SmallLds {
+  static constexpr int kWords = KC <= 4 ? 1 : 2;  // neighbour slots, eight bits each
+  alignas(16) uint32_t pl[kSmallEnvAgents];        // packed positions by agent
+  alignas(16) uint32_t list[kSmallEnvAgents + 8];  // scaled positions of the agents in play, and a pad
+  union {
+    int32_t credits[kSmallEnvAgents];
+    uint32_t nearest[kSmallEnvAgents * kWords];    // by list slot
+  };
+  alignas(16) float stage[32 * (5 + 4 * KC) + 4];
+};
+
+// Four floats of `row` (in LDS) into `rows` at a time: 32 rows that start `shift` floats past a 16-byte boundary in
+// memory are staged at the same offset from one, so that everything between the first and the last boundary leaves in
+// aligned pieces.
+template <int KC>
+__device__ __forceinline__ void store_staged(const float* stage, float* out, int floats, int shift, int lane) {
+  constexpr int kRounds = (32 * (5 + 4 * KC) / 4 + kWaveSize - 1) / kWaveSize;
+  const int head = min((4 - shift) & 3, floats), pieces = (floats - head) >> 2, tail = head + 4 * pieces;
+  const float4* const src = reinterpret_cast<const float4*>(stage + shift + head);
+  float4 q[kRounds];
+#pragma unroll
+  for (int k = 0; k < kRounds; ++k) q[k] = src[min(lane + k * kWaveSize, max(pieces - 1, 0))];
+  float4* const dst = reinterpret_cast<float4*>(out + head);
+#pragma unroll
+  for (int k = 0; k < kRounds; ++k)
+    if (lane + k * kWaveSize < pieces) dst[lane + k * kWaveSize] = q[k];
+  const int f = lane < 4 ? lane : tail + lane - 4;  // the floats in front of the first boundary and behind the last
+  if (lane < 4 ? f < head : f < floats) out[f] = stage[shift + f];
+}
+
+// (the arguments through a pointer that is opaque to the optimiser from phase to phase, as in env_kernel)
+typedef const __attribute__((address_space(4))) WaveArgs* KernargWave;
+#define WD_NEW_PHASE()             \
+  do {                             \
+    asm volatile("" : "+s"(ka));   \
+    asm volatile("" : "+v"(lane)); \
+  } while (0)
+#define p (((const WaveArgs*)ka)->p)
+#define roll (((const WaveArgs*)ka)->roll)
+#define agent(k) (lane + (k) * kWaveSize)
+#define exists(k) (agent(k) < N)
+
+template <int KC, int H>
+__global__ __launch_bounds__(kSmallWaves * kWaveSize) __attribute__((amdgpu_waves_per_eu(KC <= 4 ? 6 : 5, 8))) void
+small_env_kernel(const WaveArgs) {
+  __shared__ SmallLds<KC> tables[kSmallWaves];
+  KernargWave ka = (KernargWave)__builtin_amdgcn_kernarg_segment_ptr();
+  constexpr int D = 5 + 4 * KC;
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+  int lane = threadIdx.x & (kWaveSize - 1);
+  const int e = blockIdx.x * kSmallWaves + wave;
+  if (e >= p.E) return;
+  SmallLds<KC>& L = tables[wave];
+  const int mode = ka->mode, N = p.N, N_tag = p.N_tag, steps = roll.steps;
+  const bool vec = p.vec4 != 0, stepping_mode = mode == kModeStep || mode == kModeIterate;
+  const int64_t EN = int64_t(p.E) * N, abase = int64_t(e) * N;
+  int done = 0, t = 0, nlr = 0, tags_out = -1;  // (tags_out < 0: tags_step keeps its value)
+  GroupInput in;
+  if (mode != kModeResetAll) {
+    const int i0 = 4 * lane, n_group = min(4, N - i0);
+    if (i0 < N) {
+      if (mode == kModeIterate) load_group_probs(ka->probs + int64_t(roll.ring_pos % roll.ring_len) * EN * kNumActions, abase + i0, n_group, vec, in.f);
+      if (mode == kModeStep) load4(p.action, abase + i0, n_group, vec, in.act);
+      load4(p.pos_x, abase + i0, n_group, vec, in.x);
+      load4(p.pos_y, abase + i0, n_group, vec, in.y);
+      load4(p.live, abase + i0, n_group, vec, in.lv);
+    }
+    done = p.done[e];
+    t = p.t[e];
+    nlr = p.n_live_runners[e];
+    if ((mode == kModeStep && done) || (mode == kModeResetDone && !done)) return;  // this env keeps its state and rows
+  }
+  bool pos_dirty = false, live_dirty[H] = {};
+  for (int s = 0; s < steps; ++s) {
+    const bool last = s + 1 == steps;
+    const bool step_act = stepping_mode && !done;
+    WD_NEW_PHASE();
+    const int i0 = 4 * lane, n_group = min(4, N - i0);  // the group that this lane owns
+    const bool have = i0 < N;
+    if (have && stepping_mode) {
+      if (s > 0) {  // the state is in LDS; only the probabilities come from memory
+        load_group_probs(ka->probs + int64_t((roll.ring_pos + s) % roll.ring_len) * EN * kNumActions, abase + i0, n_group, vec, in.f);
+        const uint4 q4 = *reinterpret_cast<const uint4*>(L.pl + i0);
+        const uint32_t q[4] = {q4.x, q4.y, q4.z, q4.w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          in.x[j] = pos_x_of(q[j]);
+          in.y[j] = pos_y_of(q[j]);
+          in.lv[j] = (q[j] & kDeadBit) ? 0 : 1;
+        }
+      }
+      const uint64_t g = ka->g0 + uint64_t(s);
+      MovedGroup m;
+      move_group(p, mode, e, lane, uint32_t(g), uint32_t(g >> 32), step_act, in, m);
+      if (mode == kModeIterate) {
+        if (last) store4(p.action, abase + i0, n_group, vec, m.act);
+        if (roll.action) store4(roll.action + int64_t(s) * EN, abase + i0, n_group, vec, m.act);
+      }
+      if (step_act) {
+        uint32_t packed[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) packed[j] = pack_pos(m.x[j], m.y[j], m.lv[j] != 0);
+        *reinterpret_cast<uint4*>(L.pl + i0) = make_uint4(packed[0], packed[1], packed[2], packed[3]);
+        pos_dirty |= m.moved;
+      }
+    }
+    WD_NEW_PHASE();
+    if (step_act) {
+#pragma unroll
+      for (int k = 0; k < H; ++k) L.credits[agent(k)] = 0;
+      wave_sync_lds();
+      // ---- tag check: a runner's smallest (distance, tagger) key ------------------------------------
+      uint32_t me[H], best[H];
+      bool runner[H], tagged[H];
+#pragma unroll
+      for (int k = 0; k < H; ++k) {
+        me[k] = exists(k) ? L.pl[agent(k)] : kDeadBit;
+        best[k] = ~0u;
+        runner[k] = agent(k) >= N_tag && !(me[k] & kDeadBit);
+      }
+      if (p.tag_r2 >= 0)
+        for (int tg = 0; tg < N_tag; ++tg) {
+          const short2v at = __builtin_bit_cast(short2v, L.pl[tg] & ~kDeadBit);
+#pragma unroll
+          for (int k = 0; k < H; ++k) {
+            const uint32_t d2 = squared_length(at - __builtin_bit_cast(short2v, me[k] & ~kDeadBit));
+            best[k] = min(best[k], (d2 << 7) | uint32_t(tg));
+          }
+        }
+      int tags = 0;
+#pragma unroll
+      for (int k = 0; k < H; ++k) {
+        tagged[k] = runner[k] && best[k] != ~0u && int(best[k] >> 7) <= p.tag_r2;
+        tags += __popcll(__ballot(tagged[k]));
+        if (tagged[k]) {
+          L.pl[agent(k)] = me[k] | kDeadBit;
+          atomicAdd(&L.credits[best[k] & 127u], 1);
+          live_dirty[k] = true;
+        }
+      }
+      wave_sync_lds();
+#pragma unroll
+      for (int k = 0; k < H; ++k)
+        if (exists(k)) {
+          const int a = agent(k);
+          const float rew = a < N_tag ? static_cast<float>(L.credits[a]) * p.tag_reward : tagged[k] ? p.tag_penalty : 0.0f;
+          if (last) p.reward[abase + a] = rew;
+          if (roll.reward) roll.reward[int64_t(s) * EN + abase + a] = rew;
+        }
+      nlr -= tags;
+      t += 1;
+      done = (nlr == 0 || t >= p.T) ? 1 : 0;
+      tags_out = tags;
+    } else if (roll.reward && last) {  // (an env that entered the launch done: not stepped)
+#pragma unroll
+      for (int k = 0; k < H; ++k)
+        if (exists(k)) roll.reward[int64_t(s) * EN + abase + agent(k)] = p.reward[abase + agent(k)];
+    }
+    WD_NEW_PHASE();
+    if (mode != kModeStep) {
+      if (roll.done && lane == 0) roll.done[int64_t(s) * p.E + e] = done ? 1 : 0;  // the flag before the reset clears it
+      if (mode == kModeResetAll || done) {
+        if (have) {
+          const int G = p.G;
+          int x[4], y[4];
+          load4(p.pos_x0, abase + i0, n_group, vec, x);
+          load4(p.pos_y0, abase + i0, n_group, vec, y);
+          uint32_t packed[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            packed[j] = pack_pos(min(max(x[j], 0), G - 1), min(max(y[j], 0), G - 1), j < n_group);
+          *reinterpret_cast<uint4*>(L.pl + i0) = make_uint4(packed[0], packed[1], packed[2], packed[3]);
+        }
+        pos_dirty = true;
+#pragma unroll
+        for (int k = 0; k < H; ++k) live_dirty[k] = true;
+        t = 0;
+        nlr = N - N_tag;
+        done = 0;
+        tags_out = 0;
+      }
+    }
+    wave_sync_lds();
+    WD_NEW_PHASE();
+    const int h = p.pos_shift;
+    // ---- the agents in play, in index order ---------------------------------------------------------
+    uint32_t me[H];
+    int slot[H];
+    int n = 0, n_taggers = 0;
+#pragma unroll
+    for (int k = 0; k < H; ++k) {
+      me[k] = exists(k) ? L.pl[agent(k)] : kDeadBit;
+      const uint64_t in_play = __ballot(!(me[k] & kDeadBit));
+      slot[k] = n + __popcll(in_play & ((1ull << lane) - 1ull));
+      if (!(me[k] & kDeadBit)) L.list[slot[k]] = (uint32_t(pos_x_of(me[k])) << h) | (uint32_t(pos_y_of(me[k])) << (16 + h));
+      n += __popcll(in_play);
+      n_taggers += __popcll(__ballot(!(me[k] & kDeadBit) && agent(k) < N_tag));
+    }
+    if (lane < 8) L.list[n + lane] = kStripDeadY << 16;
+    wave_sync_lds();
+    // ---- the nearest of every agent in play -----------------------------------------------------------
+    for (int q0 = 0; q0 < n; q0 += kWaveSize) {
+      const int q = q0 + lane;
+      if (q < n) {
+        const short2v mine = __builtin_bit_cast(short2v, L.list[q]);
+        uint32_t all[KC + 1];  // the agent meets itself too: its own key is taken out at the end
+#pragma unroll
+        for (int k = 0; k <= KC; ++k) all[k] = ~0u;
+        for (int s0 = 0; s0 < n; s0 += 8) {
+          const uint4 a4 = *reinterpret_cast<const uint4*>(L.list + s0), b4 = *reinterpret_cast<const uint4*>(L.list + s0 + 4);
+          const uint32_t c[8] = {a4.x, a4.y, a4.z, a4.w, b4.x, b4.y, b4.z, b4.w};
+#pragma unroll
+          for (int j = 0; j < 8; ++j)
+            insert_key<KC + 1>(all, strip_key(__builtin_bit_cast(short2v, c[j]) - mine, uint32_t(s0 + j)));
+        }
+        uint32_t word[2] = {0u, 0u};
+        bool passed = false;
+#pragma unroll
+        for (int k = 0; k < KC; ++k) {
+          passed |= all[k] == uint32_t(q);
+          const uint32_t key = passed ? all[k + 1] : all[k];
+          const uint32_t near = key >= p.dead_key_min ? 255u : key & ((1u << p.key_shift) - 1u);
+          word[k >> 2] |= near << (8 * (k & 3));
+        }
+#pragma unroll
+        for (int w = 0; w < SmallLds<KC>::kWords; ++w) L.nearest[q * SmallLds<KC>::kWords + w] = word[w];
+      }
+    }
+    wave_sync_lds();
+    WD_NEW_PHASE();
+    // ---- rows ---------------------------------------------------------------------------------------------
+    const float t_frac = static_cast<float>(t) * p.inv_T;
+#pragma unroll
+    for (int k = 0; k < H; ++k) {
+      asm volatile("" : "+v"(lane));
+      const int a = agent(k), x = pos_x_of(me[k]), y = pos_y_of(me[k]);
+      const bool lv = !(me[k] & kDeadBit);
+      float row[D];
+      row[0] = static_cast<float>(x) * p.inv_G;
+      row[1] = static_cast<float>(y) * p.inv_G;
+      row[2] = a < N_tag ? 1.0f : 0.0f;
+      row[3] = lv ? 1.0f : 0.0f;
+      row[4] = t_frac;
+      uint32_t word[2] = {~0u, ~0u};
+#pragma unroll
+      for (int w = 0; w < SmallLds<KC>::kWords; ++w)
+        if (lv) word[w] = L.nearest[slot[k] * SmallLds<KC>::kWords + w];
+#pragma unroll
+      for (int kk = 0; kk < KC; ++kk) {
+        const uint32_t s1 = (word[kk >> 2] >> (8 * (kk & 3))) & 255u;
+        const bool none = s1 == 255u;
+        const uint32_t other = L.list[none ? 0u : s1];
+        row[5 + 4 * kk] = none ? 0.0f : static_cast<float>(int((other & 0xFFFFu) >> h) - x) * p.inv_G;
+        row[6 + 4 * kk] = none ? 0.0f : static_cast<float>(int(other >> (16 + h)) - y) * p.inv_G;
+        row[7 + 4 * kk] = (!none && int(s1) < n_taggers) ? 1.0f : 0.0f;
+        row[8 + 4 * kk] = none ? 0.0f : 1.0f;
+      }
+#pragma unroll
+      for (int d = 0; d < 2; ++d) {
+        float* const rows = d ? (roll.obs ? roll.obs + (int64_t(s) * EN + abase) * D : nullptr) : (last ? p.obs + abase * D : nullptr);
+        if (!rows) continue;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+          const int first = k * kWaveSize + half * 32;
+          float* const out = rows + int64_t(first) * D;
+          const int shift = int((reinterpret_cast<uintptr_t>(out) >> 2) & 3);
+          if ((lane >> 5) == half) {
+            float* const dst = L.stage + shift + (lane & 31) * D;
+#pragma unroll
+            for (int c = 0; c < D; ++c) dst[c] = row[c];
+          }
+          wave_sync_lds();
+          const int floats = min(max(N - first, 0), 32) * D;
+          if (floats > 0) store_staged<KC>(L.stage, out, floats, shift, lane);
+          wave_sync_lds();
+        }
+      }
+    }
+  }
+  WD_NEW_PHASE();
+  const int i0 = 4 * lane, n_group = min(4, N - i0);
+  // ---- the state, once per launch: what has changed ------------------------------------------------------
+  if (i0 < N && pos_dirty) {
+    const uint4 q4 = *reinterpret_cast<const uint4*>(L.pl + i0);
+    const int x[4] = {pos_x_of(q4.x), pos_x_of(q4.y), pos_x_of(q4.z), pos_x_of(q4.w)};
+    const int y[4] = {pos_y_of(q4.x), pos_y_of(q4.y), pos_y_of(q4.z), pos_y_of(q4.w)};
+    store4(p.pos_x, abase + i0, n_group, vec, x);
+    store4(p.pos_y, abase + i0, n_group, vec, y);
+  }
+#pragma unroll
+  for (int k = 0; k < H; ++k)
+    if (exists(k) && live_dirty[k]) p.live[abase + agent(k)] = (L.pl[agent(k)] & kDeadBit) ? 0 : 1;
+  if (lane == 0) {
+    p.t[e] = t;
+    p.n_live_runners[e] = nlr;
+    p.done[e] = done;
+    if (tags_out >= 0) p.tags_step[e] = tags_out;
+  }
+}
+
+#undef WD_NEW_PHASE
+#undef p
+#undef roll
+#undef agent
+#undef exists
+
+template <int KC, int H>
+hipError_t launch_small_variant(const WaveArgs& args, hipStream_t stream) {
+  hipLaunchKernelGGL((small_env_kernel<KC, H>), dim3((args.p.E + kSmallWaves - 1) / kSmallWaves), dim3(kSmallWaves * kWaveSize), 0,
+                     stream, args);
+  return hipGetLastError();
+}
+
+hipError_t launch_small_kernel(const Params& p, int mode, const Roll& roll, const float* probs, uint64_t g,
+                               hipStream_t stream) {
+  WaveArgs args;
+  args.p = p;
+  args.roll = roll;
+  args.probs = probs;
+  args.g0 = g;
+  args.mode = mode;
+  switch (p.K) {
+    case 1: return p.N > kWaveSize ? launch_small_variant<1, 2>(args, stream) : launch_small_variant<1, 1>(args, stream);
+    case 2: return p.N > kWaveSize ? launch_small_variant<2, 2>(args, stream) : launch_small_variant<2, 1>(args, stream);
+    case 3: return p.N > kWaveSize ? launch_small_variant<3, 2>(args, stream) : launch_small_variant<3, 1>(args, stream);
+    case 4: return p.N > kWaveSize ? launch_small_variant<4, 2>(args, stream) : launch_small_variant<4, 1>(args, stream);
+    case 5: return p.N > kWaveSize ? launch_small_variant<5, 2>(args, stream) : launch_small_variant<5, 1>(args, stream);
+    case 6: return p.N > kWaveSize ? launch_small_variant<6, 2>(args, stream) : launch_small_variant<6, 1>(args, stream);
+    case 7: return p.N > kWaveSize ? launch_small_variant<7, 2>(args, stream) : launch_small_variant<7, 1>(args, stream);
+    default: return p.N > kWaveSize ? launch_small_variant<8, 2>(args, stream) : launch_small_variant<8, 1>(args, stream);
+  }
+}
+
 // The limit on a kernel's dynamic LDS is a property of the kernel function on a device, not of a
 // handle: it is raised whenever a launch needs more than any launch before it on that device.
 constexpr int kMaxDevicesTracked = 64;
@@ -1927,7 +2277,8 @@ hipError_t launch_env_kernel(const Params& p, int mode, const float* probs, uint
     one.steps = 1;
     one.ring_len = 1;
     one.done = p.done_log;
-    return launch_wave_kernel(p, mode, one, probs, g, stream);
+    return p.wave_envs == kSmallEnvs ? launch_small_kernel(p, mode, one, probs, g, stream)
+                                     : launch_wave_kernel(p, mode, one, probs, g, stream);
   }
   WD_DISPATCH(launch_env_variant, mode, probs, g, stream, pipe);
 }
@@ -1935,6 +2286,7 @@ hipError_t launch_env_kernel(const Params& p, int mode, const float* probs, uint
 bool rollout_available(const Params& p) { return p.wave_envs || (!p.big && p.obs_mode == 0 && p.K <= kMaxRegisterK); }
 
 hipError_t launch_rollout(const Params& p, const Roll& roll, const float* ring, uint64_t g, hipStream_t stream) {
+  if (p.wave_envs == kSmallEnvs) return launch_small_kernel(p, kModeIterate, roll, ring, g, stream);
   if (p.wave_envs) return launch_wave_kernel(p, kModeIterate, roll, ring, g, stream);
   const int kx = variant_of(p);
   if (!p.wide) {

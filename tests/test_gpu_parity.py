@@ -970,3 +970,53 @@ def test_full_observation_rows_in_a_launch_of_their_own(num_envs, num_agents):
             b.iterate(ring[s])
             assert torch.equal(rec["obs"][s], b.obs)
     a.close(), b.close()
+
+
+SMALL = [  # up to 128 agents in a wave per env, two agents per lane (small_env_kernel): edges of its sizes
+    dict(num_envs=5, num_agents=65, num_taggers=64, grid_size=14, obs_k=1, tag_r2=5),
+    dict(num_envs=9, num_agents=66, num_taggers=1, grid_size=20, obs_k=2),
+    dict(num_envs=3, num_agents=67, num_taggers=9, grid_size=30, obs_k=3, tag_r2=-1),
+    dict(num_envs=1, num_agents=96, num_taggers=20, grid_size=6, obs_k=4, tag_r2=0),
+    dict(num_envs=6, num_agents=127, num_taggers=126, grid_size=849, obs_k=5, tag_r2=40000),     # largest grid of its keys
+    dict(num_envs=6, num_agents=127, num_taggers=12, grid_size=850, obs_k=5, tag_r2=40000),      # env_kernel takes over
+    dict(num_envs=7, num_agents=128, num_taggers=13, grid_size=40, obs_k=6, tag_r2=2 * 40 * 40), # everybody tagged at once
+    dict(num_envs=4, num_agents=128, num_taggers=127, grid_size=1, obs_k=7),                     # one cell
+    dict(num_envs=10, num_agents=101, num_taggers=10, grid_size=33, obs_k=8),
+    dict(num_envs=2001, num_agents=64, num_taggers=7, grid_size=25, obs_k=4),                    # one agent per lane
+    dict(num_envs=8193, num_agents=12, num_taggers=2, grid_size=11, obs_k=4),
+    dict(num_envs=4001, num_agents=33, num_taggers=3, grid_size=16, obs_k=8),
+]
+
+
+@pytest.mark.parametrize("n", range(len(SMALL)))
+def test_env_per_wave(n):
+    """Against the oracle in separate and fused calls over episode ends; recorded multi-step launches (slices on
+    4-byte boundaries for odd sizes), entered with envs that are done, against single iterations byte for byte."""
+    import torch
+
+    import paper_2108_13976_amd as wd
+
+    kw = dict(SMALL[n], seed=500 + n, episode_length=5)
+    E, N = kw["num_envs"], kw["num_agents"]
+    for fused in (False, True):
+        lockstep(kw, 8, 500 + n, fused=fused)
+    k = 4
+    ring = upload(np.stack([probs_for_step(500 + n, r, E, N) for r in range(3)]), "cuda:0")
+    a, b = make_gpu(kw), make_gpu(kw)
+    for env in (a, b):
+        env.reset(wd.WD_RESET_ALL)
+        env.done[::2] = 1  # (marked by the caller: such an env is reset by the next iteration without a step)
+        env.reward.fill_(7.0)
+    for launch in range(3):
+        rec = a.rollout(ring, k if launch else 1)
+        for s in range(k if launch else 1):
+            b.iterate(ring[b.global_step % 3])
+            where = (launch, s)
+            if launch:
+                assert torch.equal(rec["reward"][s], b.reward), where
+            assert torch.equal(rec["action"][s], b.action), where
+            assert torch.equal(rec["obs"][s], b.obs), where
+        got, want = a.to_host(), b.to_host()
+        for name in got:
+            assert got[name].tobytes() == want[name].tobytes(), (launch, name)
+    a.close(), b.close()
