@@ -1596,6 +1596,13 @@ __global__ __launch_bounds__(kMaxEnvWorkgroupSize)
 // are counted by votes), the K nearest a loop over the agents in play with the same sorted
 // insertion as elsewhere; rows go to memory straight from registers.  Several iterations per launch
 // (wd_rollout) keep the whole state in registers in between.  Same results as env_kernel.
+//
+// Bound: the issue of one wave's instructions, one after the other.  A candidate of the search costs a lane
+// read, a packed difference, a dot product, its key and K + 1 insertions (the agent's own key is taken out at the
+// end, which is cheaper than a test per candidate), four candidates per round of the loop: 100 envs x 50 agents, twenty
+// recorded iterations 92.2 -> 68.8 us (3.4 us each; with positions in two registers, multiplies by 24 bits and
+// the test it was 4.6).  The arguments stay in scalar registers here, spills included: reading them anew in every
+// iteration through an opaque pointer, as rollout_kernel does, took 78.
 // ----------------------------------------------------------------------------------
 struct WaveArgs {
   Params p;
@@ -1633,20 +1640,22 @@ __global__ __launch_bounds__(kWaveSize) void wave_env_kernel(const WaveArgs args
   }
   // (the first four probabilities decide a draw, the fifth action is the fall-through; those of the
   // next iteration are requested while this one runs)
-  const auto load_probs = [&](int s, float (&f)[4]) {
-    const float* pr = args.probs + int64_t((roll.ring_pos + s) % roll.ring_len) * EN * kNumActions + ai * kNumActions;
+  int ring_at = roll.ring_pos;
+  const auto load_probs = [&](float (&f)[4]) {
+    const float* pr = args.probs + int64_t(ring_at) * EN * kNumActions + ai * kNumActions;
+    ring_at = ring_at + 1 == roll.ring_len ? 0 : ring_at + 1;
 #pragma unroll
     for (int c = 0; c < 4; ++c) f[c] = active ? pr[c] : 0.0f;
   };
   float f_next[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  if (mode == kModeIterate) load_probs(0, f_next);
+  if (mode == kModeIterate) load_probs(f_next);
   for (int s = 0; s < roll.steps; ++s) {
     const bool last = s + 1 == roll.steps;
     const uint64_t g = args.g0 + uint64_t(s);
     int act = 0;
     if (mode == kModeIterate) {
       const float f[4] = {f_next[0], f_next[1], f_next[2], f_next[3]};
-      if (!last) load_probs(s + 1, f_next);
+      if (!last) load_probs(f_next);
       const Block4 r = random_block(p, uint32_t(e), uint32_t(a >> 2), uint32_t(g), uint32_t(g >> 32), kStreamAction);
       const uint32_t w = (a & 2) ? ((a & 1) ? r.w[3] : r.w[2]) : ((a & 1) ? r.w[1] : r.w[0]);
       act = sample_action(f[0], f[1], f[2], f[3], w);
@@ -1663,14 +1672,15 @@ __global__ __launch_bounds__(kWaveSize) void wave_env_kernel(const WaveArgs args
         x = min(max(x + (act == 4) - (act == 3), 0), G - 1);
         y = min(max(y + (act == 1) - (act == 2), 0), G - 1);
       }
+      const uint32_t here = pack_pos(x, y, true);
       uint32_t best = ~0u;
       if (p.tag_r2 >= 0)
         for (int tg = 0; tg < N_tag; ++tg) {
-          const int dx = __builtin_amdgcn_readlane(x, tg) - x, dy = __builtin_amdgcn_readlane(y, tg) - y;
-          const uint32_t d2 = uint32_t(__mul24(dx, dx)) + uint32_t(__mul24(dy, dy));
-          if (d2 <= uint32_t(p.tag_r2)) best = min(best, (d2 << 6) | uint32_t(tg));
+          const uint32_t at = uint32_t(__builtin_amdgcn_readlane(int(here), tg));
+          const uint32_t d2 = squared_length(__builtin_bit_cast(short2v, at) - __builtin_bit_cast(short2v, here));
+          best = min(best, (d2 << 6) | uint32_t(tg));
         }
-      const bool tagged = active && a >= N_tag && lv && best != ~0u;
+      const bool tagged = active && a >= N_tag && lv && p.tag_r2 >= 0 && int(best >> 6) <= p.tag_r2;
       const int tags = __popcll(__ballot(tagged));
       int credit = 0;
       if (tags)
@@ -1708,16 +1718,33 @@ __global__ __launch_bounds__(kWaveSize) void wave_env_kernel(const WaveArgs args
     if (!out_act) continue;  // this env keeps its rows
     // ---- observations: the K nearest agents in play, by (squared distance, index) ----
     const uint64_t in_play = __ballot(active && lv);
-    uint32_t keys[KT];
+    const uint32_t here = pack_pos(x, y, true);
+    uint32_t all[KT + 1];  // the agent meets itself too: its own key (distance 0, its index) is taken out at the end
 #pragma unroll
-    for (int kk = 0; kk < KT; ++kk) keys[kk] = ~0u;
-    if (K > 0)
-      for (uint64_t left = in_play; left != 0; left &= left - 1) {  // the agents in play, in index order
-        const int j = __builtin_ctzll(left);
-        const int dx = __builtin_amdgcn_readlane(x, j) - x, dy = __builtin_amdgcn_readlane(y, j) - y;
-        const uint32_t key = ((uint32_t(__mul24(dx, dx)) + uint32_t(__mul24(dy, dy))) << 6) | uint32_t(j);
-        insert_key<KT>(keys, j == a ? ~0u : key);
+    for (int kk = 0; kk <= KT; ++kk) all[kk] = ~0u;
+    const auto meet = [&](int j) {
+      const uint32_t at = uint32_t(__builtin_amdgcn_readlane(int(here), j));
+      const uint32_t d2 = squared_length(__builtin_bit_cast(short2v, at) - __builtin_bit_cast(short2v, here));
+      insert_key<KT + 1>(all, (d2 << 6) | uint32_t(j));
+    };
+    if (K > 0) {  // the agents in play, in index order
+      uint64_t left = in_play;
+      for (int n = __popcll(in_play); n >= 4; n -= 4) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          meet(__builtin_ctzll(left));
+          left &= left - 1;
+        }
       }
+      for (; left != 0; left &= left - 1) meet(__builtin_ctzll(left));
+    }
+    uint32_t keys[KT];
+    bool passed = false;
+#pragma unroll
+    for (int kk = 0; kk < KT; ++kk) {
+      passed |= all[kk] == uint32_t(a);
+      keys[kk] = passed ? all[kk + 1] : all[kk];
+    }
     float* const rows[2] = {last ? p.obs + ai * D : nullptr, roll.obs ? roll.obs + (int64_t(s) * EN + ai) * D : nullptr};
     const float t_frac = static_cast<float>(t) * p.inv_T;
     const float own[5] = {static_cast<float>(x) * p.inv_G, static_cast<float>(y) * p.inv_G, a < N_tag ? 1.0f : 0.0f,
@@ -1735,8 +1762,8 @@ __global__ __launch_bounds__(kWaveSize) void wave_env_kernel(const WaveArgs args
         // no branch: an empty slot looks up the agent itself, whose offsets are zero
         const bool none = !lv || keys[kk] == ~0u;
         const int j = none ? a : int(keys[kk] & 63u);
-        const int ox = __shfl(x, j), oy = __shfl(y, j);
-        const float slot[4] = {static_cast<float>(ox - x) * p.inv_G, static_cast<float>(oy - y) * p.inv_G,
+        const uint32_t other = uint32_t(__shfl(int(here), j));
+        const float slot[4] = {static_cast<float>(pos_x_of(other) - x) * p.inv_G, static_cast<float>(pos_y_of(other) - y) * p.inv_G,
                                (!none && j < N_tag) ? 1.0f : 0.0f, none ? 0.0f : 1.0f};
 #pragma unroll
         for (int r = 0; r < 2; ++r)
