@@ -1,13 +1,12 @@
 // wdc.hip — continuous Tag: the C ABI of include/wdc.h and its kernels (gfx950).
 //
-// One thread per agent.  Envs of at most 64 agents (the paper's own continuous-Tag training runs have 5
-// to 45): a workgroup of `bd` threads holds floor(bd / N) envs; the moved positions and velocities of the
-// workgroup's envs are staged in LDS, where the runner-side tag test and the brute-force K-nearest search
-// read them (env_kernel, rollout_kernel).  Larger envs have a workgroup each, sort their agents by strip
-// and column and search windows of that list (block_kernel).  Every float32 operation that feeds a comparison is
-// written as its own statement and the file is compiled without contraction, so that the state is
-// reproducible to the bit (arXiv 2108.13976, Sec. 5.1, continuous variant; the numbers are this
-// build's reading, stated in wdc.h).
+// One thread per agent.  Envs of at most 32 agents: a workgroup of `bd` threads holds floor(bd / N) envs; the
+// moved positions and velocities of the workgroup's envs are staged in LDS, where the runner-side tag test
+// and the brute-force K-nearest search read them (env_kernel, rollout_kernel).  Larger envs have a
+// workgroup each, sort their agents by strip and column and search windows of that list (block_kernel).
+// Every float32 operation that feeds a comparison is written as its own statement and the file is
+// compiled without contraction, so that the state is reproducible to the bit (arXiv 2108.13976, Sec. 5.1,
+// continuous variant; the numbers are this build's reading, stated in wdc.h).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -493,7 +492,7 @@ __global__ __launch_bounds__(kMaxThreads) void rollout_kernel(const Params p, co
 
 
 // ----------------------------------------------------------------------------------
-// Envs of more than a wave's agents: one workgroup per env, one thread per agent, any mode, one or more
+// Envs of more than 32 agents: one workgroup per env, one thread per agent, any mode, one or more
 // iterations per launch.  The agents in play are sorted by strip and column every iteration
 // (wdc_dev_strips.h); the search runs in list order over fixed windows, and the few agents that
 // these do not settle are served by sixteen lanes each.  Between the iterations of a launch an
@@ -589,7 +588,7 @@ __device__ __forceinline__ int build_list(float world, int threads, const BlockL
     L.ids[slot] = uint16_t(tid);
   }
   constexpr int pad = list_pad(KT);
-  static_assert(2 * pad <= 2 * wd::kWaveSize, "two waves write the pads");
+  static_assert(2 * pad <= wd::kWaveSize, "one wave writes the pads");
   if (tid < 2 * pad) L.list[tid < pad ? -1 - tid : n + (tid - pad)] = make_float2(0.0f, kGone);
   __syncthreads();
   return n;
@@ -1092,13 +1091,17 @@ int fail_hip(wdc_handle* h, hipError_t err, const char* what) {
 // four float and two int arrays of one element per thread, one int per env of the workgroup
 size_t lds_bytes(const wdc::Params& p) { return size_t(p.threads) * 24 + size_t(p.threads / 2) * 4; }
 
-// One workgroup per env (block_kernel) serves envs of more than a wave's agents: geometry of the list,
-// form of the tag check, LDS map.  Up to 64 agents several envs share a workgroup and comparing all
-// pairs is the shorter chain; without neighbours there is nothing to search; and outside a world of
-// ordinary size the search's bounds (squares of distances as float32) have no room.
+constexpr int kBlockAbove = 32;  // agents per env
+
+// One workgroup per env (block_kernel) serves envs of more than 32 agents: geometry of the list, form of the
+// tag check, LDS map.  Smaller envs share a workgroup, and comparing all pairs is the shorter chain; without
+// neighbours there is nothing to search; and outside a world of ordinary size the search's bounds (squares
+// of distances as float32) have no room.  Measured, us per iteration, all pairs -> block_kernel (K = 4):
+// 300 x 20 8.1 -> 9.7, 4000 x 20 12.6 -> 14.6; 10 x 33 9.6 -> 8.9, 4000 x 33 16.4 -> 16.0 (four recorded iterations of
+// 300 x 33 40.4 -> 29.5); 2000 x 48 16.1 -> 14.8, K = 8 22.5 -> 17.5; 10 x 64 13.8 -> 10.1, 4000 x 64 26.5 -> 20.1.
 void plan_block(const wdc::Params& p, wdc::BlockPlan* b) {
   *b = wdc::BlockPlan{};
-  if (p.N <= wd::kWaveSize || p.K < 1 || p.L < 1e-3f || p.L > 1e6f) return;
+  if (p.N <= kBlockAbove || p.K < 1 || p.L < 1e-3f || p.L > 1e6f) return;
   b->threads = (p.N + 63) / 64 * 64;
   b->kt = p.K <= 2 ? 2 : p.K <= 4 ? 4 : p.K <= 6 ? 6 : 8;
   const int nt = b->threads, waves = nt / wd::kWaveSize, pad = wdc::list_pad(b->kt);

@@ -268,7 +268,10 @@ def test_rollout_argument_checks():
     env.close()
 
 
-BLOCK = [  # envs of more than 64 agents run in a workgroup each (block_kernel): edges of its sizes and of its searches
+BLOCK = [  # envs of more than 32 agents run in a workgroup each (block_kernel): edges of its sizes and of its searches
+    dict(num_agents=32, num_taggers=3, world_size=12.0, obs_k=4),                       # the largest that share a workgroup
+    dict(num_agents=33, num_taggers=3, world_size=12.0, obs_k=8),                       # one wave, pads of 62 entries
+    dict(num_agents=64, num_taggers=30, world_size=18.0, obs_k=6),
     dict(num_agents=65, num_taggers=1, world_size=9.0, obs_k=1),                        # one agent in the second wave
     dict(num_agents=128, num_taggers=127, world_size=14.0, obs_k=2),                    # whole waves; one runner
     dict(num_agents=129, num_taggers=64, world_size=14.0, obs_k=3, tag_r2=0.05),        # odd K: rows leave lane by lane
