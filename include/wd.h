@@ -199,9 +199,9 @@ typedef struct wd_rollout_buffers {
  * (g + s) mod ring_len.  Results equal k calls of wd_iterate with those probabilities:
  * the in-place buffers end in the state after the last iteration, `out` (may be NULL)
  * receives every iteration's outputs, g advances by k.  Configurations that use the
- * large-env layout, full observations or K > 8 have no multi-step kernel: for them the
- * call enqueues one launch per iteration (and device-to-device copies of the last slice),
- * with the same results.  In the large-env layout the observation kernel of an iteration
+ * large-env layout, full observations, K > 16, or K > 8 with a grid too large for 16-bit
+ * scaled positions, have no multi-step kernel: for them the call enqueues one launch per
+ * iteration (and device-to-device copies of the last slice), with the same results.  In the large-env layout the observation kernel of an iteration
  * then runs on a second stream that the handle owns (default priority), beside the step
  * kernel of the next iteration, ordered by events; cfg.stream waits for the last of them
  * before the call's work on it ends, so the caller sees one stream as before.  The first

@@ -761,7 +761,7 @@ int wd_rollout(wd_handle* h, const float* probs_ring, int ring_len, int k, const
   const int rows_kept = (h->rows_valid && !(out && out->obs)) ? 1 : 0;
   if (!wd::rollout_available(h->params)) {
     // Configurations without a multi-step kernel (large-env layout, full observations,
-    // K > 8): the same results from one launch of the iteration kernels per iteration,
+    // K > 16, K > 8 with 64-bit keys): the same results from one launch of the iteration kernels per iteration,
     // outputs redirected to the slices, the last slice copied from the in-place buffers.
     // In the large-env layout the observation kernel of iteration s runs on a second stream beside
     // the step kernel of iteration s + 1 (which needs the state, not the rows): two table images

@@ -2310,7 +2310,9 @@ hipError_t launch_env_kernel(const Params& p, int mode, const float* probs, uint
   WD_DISPATCH(launch_env_variant, mode, probs, g, stream, pipe);
 }
 
-bool rollout_available(const Params& p) { return p.wave_envs || (!p.big && p.obs_mode == 0 && p.K <= kMaxRegisterK); }
+bool rollout_available(const Params& p) {
+  return p.wave_envs || (!p.big && p.obs_mode == 0 && (p.K <= kMaxRegisterK || p.strips));
+}
 
 hipError_t launch_rollout(const Params& p, const Roll& roll, const float* ring, uint64_t g, hipStream_t stream) {
   if (p.wave_envs == kSmallEnvs) return launch_small_kernel(p, kModeIterate, roll, ring, g, stream);
@@ -2326,6 +2328,8 @@ hipError_t launch_rollout(const Params& p, const Roll& roll, const float* ring, 
     if (kx == 3) return launch_rollout_variant<false, 3, false>(p, roll, ring, g, stream);
     if (kx == 2) return launch_rollout_variant<false, 2, false>(p, roll, ring, g, stream);
     if (kx == 1) return launch_rollout_variant<false, 1, false>(p, roll, ring, g, stream);
+    if (kx == -3) return launch_rollout_variant<false, -3, false>(p, roll, ring, g, stream);
+    if (kx == -2) return launch_rollout_variant<false, -2, false>(p, roll, ring, g, stream);
     return launch_rollout_variant<false, 0, false>(p, roll, ring, g, stream);
   }
   if (kx == 4) return launch_rollout_variant<true, 4, false>(p, roll, ring, g, stream);

@@ -514,7 +514,9 @@ def test_multi_step_rollout_equals_single_iterations(name, k, rounds):
                                     ("k_one_packed_envs", 5), ("k_two_odd_agent_count", 4), ("k_three", 6),
                                     ("k_eight", 5), ("k_seven_packed_envs", 4), ("k_three_one_workgroup", 6),
                                     ("k_eight_one_workgroup", 5), ("wave_full", 5), ("wave_k_seven", 4), ("wave_two_agents", 7), ("wave_k_sixteen", 4),
-                                    ("beyond_wave_batch", 4), ("many_small_envs_k_two", 3)])
+                                    ("beyond_wave_batch", 4), ("many_small_envs_k_two", 3), ("k_nine_strips", 5),
+                                    ("k_twelve_strips_packed", 4), ("k_sixteen_strips_packed", 3),
+                                    ("k_thirteen_strips_crowded", 4), ("k_sixteen_strips_wide_workgroup", 3)])
 def test_multi_step_rollout_of_other_launch_shapes(name, k):
     """Large-env layout, full observations, K > 8 (wd_rollout runs one launch per iteration), the
     multi-step kernel in 512- and 1024-thread workgroups and its variants for other K than 4, the
