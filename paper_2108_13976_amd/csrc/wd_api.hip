@@ -447,8 +447,8 @@ int fill_params(const wd_config& c, const wd_buffers& b, wd::Params* p, bool pai
   // Full observations: a second launch for the rows (about 4 us, 8 where step and reset are called one by one)
   // pays once the rows are long or many.  Measured, us per iteration, rows written by env_kernel -> by their own
   // kernel: 20 envs x 70 agents 16.7 -> 20.5 (three separate calls 22.1 -> 29.4), 400 x 70 19.8 -> 25.3, 20 x 130
-  // 27.9 -> 21.5 (34.2 -> 30.4), 100 x 100 54.2 -> 22.2, 2000 x 64 (134 MB of rows) 78.4 -> 52.1, 200 x 500 359 -> 69.4,
-  // 2000 x 1000 (in mid-training) 2640 -> 1798.
+  // 27.9 -> 21.5 (34.2 -> 30.4), 100 x 100 54.2 -> 22.2, 2000 x 64 (134 MB of rows) 78.4 -> 52.1, 200 x 500 359 -> 71.7;
+  // 2000 x 1000 2640 -> 1782 in mid-training, 6227 -> 6354 with every agent in play.
   const int64_t row_bytes = int64_t(c.num_envs) * c.num_agents * p->D * 4;
   if (c.obs_mode == WD_OBS_FULL && (c.num_agents >= kFullSplitAgents || (c.num_agents >= wd::kWaveSize && row_bytes >= kFullSplitBytes)))
     p->obs_mode = wd::kObsFullSplit;

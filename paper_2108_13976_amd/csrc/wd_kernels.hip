@@ -963,22 +963,27 @@ __device__ __forceinline__ void env_body(KernargParams pk, const StepOut out, co
 
 // ----------------------------------------------------------------------------------
 // Rows of full observations (the second observation mode of Sec. 5.1), for envs of kFullSplitAgents and
-// more.  Workgroup (e, s) writes those of the rows s, s + slices, s + 2 slices, ... of env e that env_kernel
-// has marked (the taggers' rows come first and are always written: slices of consecutive rows would have
-// unequal work): a wave per row, the env's positions in LDS.  A row starts 0..3 floats past a 16-byte
-// boundary and is written by itself: its own features and what lies before the second boundary behind
-// them, and the floats behind the last boundary, lane by lane; everything between as aligned 16-byte
-// pieces, each the tail of one slot and the head of the next at an offset that is uniform over the row.
+// more.  Workgroup (e, s) looks at every slices-th run of eight consecutive rows of env e and writes those that
+// env_kernel has marked: a wave per row, the env's positions in LDS.  (The taggers' rows come first and are
+// always written, so consecutive runs would give the slices unequal work; single rows instead of runs
+// cost the memory locality.)  A row starts 0..3 floats past a 16-byte boundary and is written by itself: its
+// own features and what lies before the second boundary behind them, and the floats behind the last boundary,
+// lane by lane; everything between as aligned 16-byte pieces, each the tail of one slot and the head of the
+// next at an offset that is uniform over the row.
 //
 // Bound: HBM stores.  With the rows written by env_kernel's own workgroup, one per env, a batch of a few
 // hundred envs had four waves on a compute unit to produce hundreds of megabytes: 200 envs x 500 agents took
-// 357 us per iteration with a quarter of the rows (200 MB) to be written; now 69 (17 of them the step).
-// Consecutive rows per workgroup instead of every slices-th: 87.
+// 359 us per iteration with a quarter of the rows (200 MB) to be written; now 72 (17 of them the step), and 364 -> 193
+// with every row (800 MB).  2000 x 1000: 2640 -> 1782 in mid-training, but 6.23 -> 6.35 ms with every agent in play
+// (32 GB).  Runs of 1 / 4 / 8 / 32 rows: 200 x 500 68.5 / 70.6 / 71.7 / 88.0 us, 2000 x 1000 with every row 6.88 / 6.54 / 6.35 /
+// 6.36 ms; a wave's rows one behind the other instead of in turns: no gain.
 // ----------------------------------------------------------------------------------
 constexpr int kFullRowsPerGroup = 32;  // at most
 constexpr int kFullGroups = 2048;       // workgroups aimed at
+constexpr int kFullRun = 8;             // consecutive rows
 
-__global__ __launch_bounds__(kWorkgroupSize) void full_rows_kernel(const Params p, const int slices) {
+__global__ __launch_bounds__(kWorkgroupSize) void full_rows_kernel(const Params p, const int slices,
+                                                                   const int per_group) {
   extern __shared__ __align__(16) unsigned char smem[];
   uint32_t* const pl = reinterpret_cast<uint32_t*>(smem);  // [N]
   __shared__ int16_t wanted[kFullRowsPerGroup];  // rows to write, in the first `n_wanted` places
@@ -990,8 +995,9 @@ __global__ __launch_bounds__(kWorkgroupSize) void full_rows_kernel(const Params 
   const int64_t abase = int64_t(e) * N;
   float* const env_obs = p.obs + abase * D;
   if (tid < kWaveSize) {
-    const int i = s + lane * slices;
-    const bool mine = lane < kFullRowsPerGroup && i < N && __float_as_uint(env_obs[int64_t(i) * D]) == kRowWanted;
+    // runs of kFullRun consecutive rows, every slices-th of the env's
+    const int i = (s + lane / kFullRun * slices) * kFullRun + lane % kFullRun;
+    const bool mine = lane < per_group && i < N && __float_as_uint(env_obs[int64_t(i) * D]) == kRowWanted;
     const uint64_t votes = __ballot(mine);
     if (mine) wanted[__popcll(votes & ((1ull << lane) - 1ull))] = int16_t(i);
     if (lane == 0) n_wanted = __popcll(votes);
@@ -2218,9 +2224,11 @@ hipError_t launch_env_variant(const Params& p, int mode, const float* probs, uin
   }
   if constexpr (KX == -1) {
     if (err != hipSuccess || p.obs_mode != kObsFullSplit) return err;
-    const int per_group = std::min<int64_t>(std::max<int64_t>(int64_t(p.E) * p.N / kFullGroups, 8), kFullRowsPerGroup);
-    const int slices = (p.N + per_group - 1) / per_group;
-    hipLaunchKernelGGL(full_rows_kernel, dim3(p.E * slices), dim3(kWorkgroupSize), size_t(4 * p.N), stream, p, slices);
+    const int runs = std::min<int64_t>(std::max<int64_t>(int64_t(p.E) * p.N / (kFullGroups * kFullRun), 8 / kFullRun),
+                                       kFullRowsPerGroup / kFullRun);  // of a workgroup
+    const int slices = ((p.N + kFullRun - 1) / kFullRun + runs - 1) / runs;
+    hipLaunchKernelGGL(full_rows_kernel, dim3(p.E * slices), dim3(kWorkgroupSize), size_t(4 * p.N), stream, p, slices,
+                       runs * kFullRun);
     err = hipGetLastError();
   }
   return err;
