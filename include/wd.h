@@ -134,10 +134,10 @@ int wd_query_layout(const wd_config* cfg, wd_layout* out);
  * WD_E_UNSUPPORTED if no kernel of this build covers the configuration (an env whose
  * tables exceed one workgroup's LDS: beyond about 13 900 agents with 32-bit keys, 11 500
  * with 64-bit keys, 8192 for full observations or K > 16).  Envs too large for one
- * workgroup's LDS, and batches of few envs of more than 1300 agents (of 384 with wide views,
- * K > 8, or grids too large for 16-bit scaled positions), run in the large-env layout, whose
- * work tables (about 20 bytes per agent) the library allocates here with hipMalloc: WD_E_HIP
- * if that fails. */
+ * workgroup's LDS (for K = 15 and 16 from about 2600 agents on), and batches of few envs of
+ * more than 1300 agents (of 384 with wide views, K > 8, or grids too large for 16-bit scaled
+ * positions), run in the large-env layout, whose work tables (about 20 bytes per agent) the
+ * library allocates here with hipMalloc: WD_E_HIP if that fails. */
 int wd_create(const wd_config* cfg, const wd_buffers* bufs, wd_handle** out);
 
 /* Environment reset (Sec. 4.5 item 5, the automatic reset of done envs).
@@ -175,12 +175,15 @@ int wd_iterate(wd_handle* h, const float* probs);
  * the same configuration, or earlier calls of this function).  Same arguments otherwise:
  * cfg (host), bufs (DEVICE pointers, 256-byte aligned), probs (device [E][N][5]); the
  * kernels are enqueued on cfg->stream and not synchronised; results equal wd_iterate's.
- * Every observation row is written whole.  The work tables that a large-env configuration
- * needs (see wd_create) live in a static device array of WD_STATIC_SCRATCH_BYTES that every
- * call on a GPU shares (each GPU the library runs on holds it until the process ends):
- * WD_E_SCRATCH if the configuration needs more; calls that overlap in time on one GPU, on
- * any streams, race on that array and must be serialised by the caller.  Calls no
- * hipMalloc / hipFree. */
+ * Every observation row is written whole.  The work tables of the large-env layout live in a
+ * static device array of WD_STATIC_SCRATCH_BYTES that every call on a GPU shares (each GPU
+ * the library runs on holds it until the process ends): WD_E_SCRATCH if the configuration
+ * needs more; calls that overlap in time on one GPU, on any streams, race on that array and
+ * must be serialised by the caller.  Here that layout serves (a wider choice than that of
+ * wd_create, kept so that what a configuration needs does not change) partial observations
+ * with K <= 16 of 384 agents and more per env in batches of at most 0.3 N envs (N <= 1024)
+ * or 450 envs, and envs too large for one workgroup's LDS: beyond 3072 agents as in
+ * wd_create, up to there none.  Calls no hipMalloc / hipFree. */
 #define WD_STATIC_SCRATCH_BYTES (8u << 20)
 int wd_iterate_static(const wd_config* cfg, const wd_buffers* bufs, const float* probs, uint64_t g);
 

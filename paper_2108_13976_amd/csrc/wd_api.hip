@@ -190,11 +190,30 @@ bool plan_strip_layout(const wd_config& c, wd::Params* p) {
   return true;
 }
 
+// The strip search keeps the positions of its list scaled by 2^h per axis (2 h >= idx_bits), so that the
+// squared length of a packed 16-bit difference is the key's distance part where it belongs; an entry out of
+// play has y field 0x7FFF.  That needs room in 16 bits: the keys of such entries, at least (32767 - A)^2 with
+// A = (G - 1) << h, must lie above every key of a live pair, below 2 A^2 + 2^(2 h).
+bool strip_positions_fit(int idx_bits, int G, int* h, uint32_t* dead_key_min) {
+  *h = (idx_bits + 1) / 2;
+  const int64_t A = int64_t(G - 1) << *h;
+  const int64_t dead_min = A < 32767 ? (32767 - A) * (32767 - A) : 0;
+  *dead_key_min = uint32_t(dead_min);
+  return A < 32767 && 2 * A * A + (int64_t(1) << (2 * *h)) <= dead_min;
+}
+
 // Launch geometry and LDS map of the env-per-team kernels.  Returns false if an env does
 // not fit one workgroup's LDS.
-// (`big_tables_in_lds`: a large env also keeps slots, tag keys and credits in LDS when they fit)
-bool plan_env_kernels(const wd_config& c, wd::Params* p, bool big, bool big_tables_in_lds = false) {
+// (`big_tables_in_lds`: a large env also keeps slots, tag keys and credits in LDS when they fit; `max_log2`:
+// the widest workgroup of the small layout)
+bool plan_env_kernels(const wd_config& c, wd::Params* p, bool big, bool big_tables_in_lds = false, int max_log2 = 10) {
   const int N = c.num_agents, G = c.grid_size;
+  // the variants with K = 1 .. 16, small layout, sort by strip where the scaled positions fit
+  p->idx_bits = bits_for(uint32_t(N - 1));
+  int strip_h = 0;
+  uint32_t strip_dead_key_min = 0;
+  const bool strips = !big && c.obs_mode == WD_OBS_PARTIAL && p->K >= 1 && p->K <= wd::kMaxRegisterK2 &&
+                      strip_positions_fit(p->idx_bits, G, &strip_h, &strip_dead_key_min);
   p->NG = (N + 3) / 4;
   p->big = big ? 1 : 0;
   int ts_log2 = 3;
@@ -219,17 +238,41 @@ bool plan_env_kernels(const wd_config& c, wd::Params* p, bool big, bool big_tabl
   // Wider workgroups.  A batch of up to a thousand envs of more than 256 agents is bound by one workgroup's
   // chain of phases, which more lanes shorten; and an env of more than 1024 agents takes more LDS than lets
   // eight 256-thread workgroups share a CU, so that wider ones keep the CU's wave slots filled.
-  // Measured, us per iteration, 256 / 512 / 1024 threads (K = 4, strips): 10 x 333 18.1 / 17.4 / -,
+  // Measured, us per iteration, 256 / 512 / 1024 threads.  Strips: K = 4: 10 x 333 18.1 / 17.4 / -,
   // 450 x 333 23.1 / 22.4, 777 x 333 25.3 / 25.4; 10 x 700 19.2 / 17.8 / 18.2, 300 x 1000 26.9 / 24.7 / 26.1,
   // 777 x 1000 34.9 / 33.8; 200 x 1300 - / 25.5 / 24.6, 450 x 1300 - / 31.0 / 31.5; 200 x 2000 - / 30.1 / 28.5,
-  // 777 x 2000 - / 67.5 / 69.5; K = 8: 450 x 1000 38.6 / 35.8, 777 x 1000 49.2 / 62.6;
-  // K = 12: 200 x 1000 51.7 / 40.7, 500 x 1000 62.3 / 76.6; K = 4: 300 x 3000 - / 50.0 / 48.1, 1500 x 3000 - / 159 / 151.
+  // 777 x 2000 - / 67.5 / 69.5; 460 x 2600 - / 93.4 / 49.3, 1500 x 2600 - / 178 / 130; K = 8: 450 x 1000 38.6 / 35.8,
+  // 777 x 1000 49.2 / 62.6; K = 12: 200 x 1000 51.7 / 40.7, 500 x 1000 62.3 / 76.6.
+  // Bucket rings (larger grids): K = 4: 250 x 300 36.5 / 30.7, 500 x 500 45.2 / 42.7, 1000 x 700 70.5 / 80.4,
+  // 460 x 1100 - / 62.0 / 83.8, 460 x 2800 - / 113 / 130; K = 16: 250 x 300 170 / 131, 500 x 500 225 / 295.
+  // No list in registers: K = 17: 20 x 300 99.7 / 81.9 (not taken), 200 x 1100 - / 154 / 129, 800 x 1100 - / 284 / 300,
+  // 500 x 3000 (K = 20) - / 1897 / 1789; K = 0: 600 x 2600 - / 42.8 / 48.2; full views 20 x 1100 - / 32.0 / 33.0.
   if (!big && N > 256 && ts_log2 <= 8) {
-    if (N > 1024)
-      ts_log2 = (c.num_envs <= 256 || N > 2500) ? 10 : 9;
-    else if (c.obs_mode == WD_OBS_PARTIAL && p->K >= 1 && p->K <= wd::kMaxRegisterK2 &&
-             c.num_envs <= (p->K > wd::kMaxRegisterK ? 256 : (N <= 512 || p->K > 4 || p->K < 2) ? 512 : 1024))
-      ts_log2 = 9;  // (K = 1 and K > 4: half the waves on a CU, for registers; K > 8: fewer still, for staged rows)
+    const bool partial = c.obs_mode == WD_OBS_PARTIAL;
+    const int K = p->K;
+    if (N > 3072) {
+      ts_log2 = 10;
+    } else if (N > 1024) {
+      ts_log2 = 9;
+      if (strips || (partial && K > wd::kMaxRegisterK2)) {
+        if (c.num_envs <= 256) ts_log2 = 10;
+        // a CU holds three 512-thread workgroups of such an env at most, but two of 1024 threads.  Only where the
+        // kernel's registers leave room for more waves than two workgroups of 512 threads have: K = 2 .. 4, not
+        // K = 1 and K > 4 (1500 x 2600, 512 / 1024 threads: K = 1 92.2 / 124, K = 6 168 / 188)
+        if (N > 2500 && ((K >= 2 && K <= 4) || K > wd::kMaxRegisterK2)) ts_log2 = 10;
+      }
+      // and of the others where LDS holds one workgroup per CU anyway (1500 x 2600: K = 8 235 / 216, K = 10
+      // 346 / 280; bucket rings 460 x 2800, K = 8 283 / 253, K = 10 552 / 509)
+      if (N > 2500 && ts_log2 == 9 && max_log2 > 9 && partial && K >= 1) {
+        wd::Params narrow = *p;
+        if (plan_env_kernels(c, &narrow, false, false, 9) && 2 * int64_t(narrow.lds_bytes) > kLdsLimitBytes) ts_log2 = 10;
+      }
+    } else if (partial && K >= 1 && K <= wd::kMaxRegisterK2) {
+      // (K = 1 and K > 4: half the waves on a CU, for registers; K > 8: fewer still, for staged rows)
+      const int envs = K > wd::kMaxRegisterK ? 256 : (!strips || N <= 512 || K > 4 || K < 2) ? 512 : 1024;
+      if (c.num_envs <= envs) ts_log2 = 9;
+    }
+    ts_log2 = std::min(ts_log2, max_log2);
     if (ts_log2 > 8) p->wg_size = 1 << ts_log2;
   }
   if (big) {  // one env per 1024-thread workgroup
@@ -276,7 +319,6 @@ bool plan_env_kernels(const wd_config& c, wd::Params* p, bool big, bool big_tabl
   p->div_NG = wd::make_fastdiv(uint32_t(p->NG));
 
   // (distance, index) keys and bucket entries: 32 bits when they fit, else 64
-  p->idx_bits = bits_for(uint32_t(N - 1));
   p->xy_bits = bits_for(uint32_t(G - 1));
   const uint64_t d2max = 2ull * uint64_t(G - 1) * uint64_t(G - 1);
   // 32-bit form: live keys stay below 2^31, and a dead mark (x + dead_dx) exists that puts the
@@ -294,21 +336,12 @@ bool plan_env_kernels(const wd_config& c, wd::Params* p, bool big, bool big_tabl
       p->dead_dx = int32_t(shift);
     }
   }
-  // The variants with 32-bit keys and K = 1 .. 8 compiled in (small layout) sort by strip and keep the
-  // positions of that list scaled by 2^h per axis (2 h >= idx_bits), so that the squared length of a
-  // packed 16-bit difference is the key's distance part where it belongs; an entry out of play has y
-  // field 0x7FFF.  That needs room in 16 bits: the keys of such entries, at least (32767 - A)^2 with
-  // A = (G - 1) << h, must lie above every key of a live pair, below 2 A^2 + 2^(2 h).  Larger grids
-  // take 64-bit keys and the bucket rings.
   if (!big && c.obs_mode == WD_OBS_PARTIAL && p->K >= 1 && p->K <= wd::kMaxRegisterK2) {
-    const int h = (p->idx_bits + 1) / 2;
-    const int64_t A = int64_t(G - 1) << h;
-    const int64_t dead_min = A < 32767 ? (32767 - A) * (32767 - A) : 0;
-    narrow = A < 32767 && 2 * A * A + (int64_t(1) << (2 * h)) <= dead_min;  // (the bucket form's bound does not matter here)
+    narrow = strips;  // (these variants search by strip with 32-bit keys, on larger grids by bucket rings with 64-bit keys)
     if (narrow) {
-      p->pos_shift = h;
-      p->key_shift = 2 * h;
-      p->dead_key_min = uint32_t(dead_min);
+      p->pos_shift = strip_h;
+      p->key_shift = 2 * strip_h;
+      p->dead_key_min = strip_dead_key_min;
     }
   }
   // Else, in the large-env layout: keys that need all 32 bits, the dead mark moved into bit 15
@@ -320,9 +353,9 @@ bool plan_env_kernels(const wd_config& c, wd::Params* p, bool big, bool big_tabl
   p->wide = flagged32 ? 2 : (narrow ? 0 : 1);
   const int key_bytes = narrow ? 4 : 8;
   const bool register_path = c.obs_mode == WD_OBS_PARTIAL && p->K <= wd::kMaxRegisterK2;
-  // The variants with 32-bit keys and K compiled in (small layout) sort by strip and column
+  // The variants with 32-bit keys and K = 1 .. 16 (small layout) sort by strip and column
   // instead of by square bucket (wd_dev_strips.h).
-  p->strips = (!big && p->wide == 0 && c.obs_mode == WD_OBS_PARTIAL && p->K >= 1 && p->K <= wd::kMaxRegisterK2) ? 1 : 0;
+  p->strips = strips ? 1 : 0;
   if (p->strips) return plan_strip_layout(c, p);
 
   int64_t off = 0;
@@ -429,9 +462,9 @@ void plan_spread(const wd_config& c, wd::Params* p) {
   p->g_stride_acc = (p->acc_tags + 1 + 3) / 4 * 4;
 }
 
-// (`pair_as_ever`: the large-env pair wherever it served before the small layout's strip search: wd_iterate_static's
-// set of configurations with work tables, and so of those it refuses for want of room, stays what it was)
-int fill_params(const wd_config& c, const wd_buffers& b, wd::Params* p, bool pair_as_ever) {
+// (`own_tables`: the handle's, allocated for it.  wd_iterate_static has a fixed array for them and refuses what exceeds
+// it, so the set of configurations that need tables there is a rule of its own: see wd.h)
+int fill_params(const wd_config& c, const wd_buffers& b, wd::Params* p, bool own_tables) {
   std::memset(p, 0, sizeof(*p));
   p->E = c.num_envs;
   p->N = c.num_agents;
@@ -487,7 +520,7 @@ int fill_params(const wd_config& c, const wd_buffers& b, wd::Params* p, bool pai
   // the largest batch that the pair serves faster than strips do
   const int pair_envs = p->K > wd::kMaxRegisterK ? (c.num_agents - 500) / (p->K > wd::kMaxRegisterK3 ? 2 : 4)
                                                     : (c.num_agents - 1300) / (p->K > 4 ? 5 : 18);
-  if (prefer_pair && !pair_as_ever && c.num_envs > pair_envs) {
+  if (prefer_pair && own_tables && c.num_envs > pair_envs) {
     wd::Params small = *p;
     if (plan_env_kernels(c, &small, false) && small.strips) prefer_pair = false;
   }
@@ -500,6 +533,13 @@ int fill_params(const wd_config& c, const wd_buffers& b, wd::Params* p, bool pai
   if (!planned) {
     *p = filled;
     planned = plan_env_kernels(c, p, false);
+  }
+  // The rows that sixteen waves stage may be what does not fit (K = 15 and 16, about 2600 to 3072 agents).  The pair is
+  // faster there than eight waves are (460 x 2600, K = 16: 216 -> 126 us with strips; 460 x 2800 791 -> 216 with bucket
+  // rings), but eight waves need no tables.
+  if (!planned && !prefer_pair && !own_tables && c.num_agents <= 3072) {
+    *p = filled;
+    planned = plan_env_kernels(c, p, false, false, 9);
   }
   if (!planned && !prefer_pair) {
     *p = filled;
@@ -611,7 +651,7 @@ int wd_create(const wd_config* cfg, const wd_buffers* bufs, wd_handle** out) {
   for (const void* ptr : ptrs)
     if (!aligned256(ptr)) return WD_E_ALIGN;
   wd::Params params;
-  rc = fill_params(*cfg, *bufs, &params, false);
+  rc = fill_params(*cfg, *bufs, &params, true);
   if (rc != WD_OK) return rc;
   wd_handle* h = new (std::nothrow) wd_handle();
   if (!h) return WD_E_NULL;
@@ -716,7 +756,7 @@ int wd_iterate_static(const wd_config* cfg, const wd_buffers* bufs, const float*
   for (const void* ptr : ptrs)
     if (!aligned256(ptr)) return WD_E_ALIGN;
   wd::Params params;
-  rc = fill_params(*cfg, *bufs, &params, true);
+  rc = fill_params(*cfg, *bufs, &params, false);
   if (rc != WD_OK) return rc;
   if (!probs_aligned(params, probs)) return WD_E_ALIGN;
   params.big_spread = 0;  // (its accumulators have to start clear; the pair with one workgroup per env needs nothing of the kind)

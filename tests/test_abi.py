@@ -5,6 +5,7 @@ import os
 import re
 
 import pytest
+import torch
 
 import paper_2108_13976_amd as wd
 from paper_2108_13976_amd import binding
@@ -160,6 +161,21 @@ def test_static_entry_point_checks_its_arguments_before_any_launch():
         wd.wd_iterate_static(big, bufs, 0x40000, 0)
     assert ei.value.status == binding.WD_E_SCRATCH
     assert "static scratch" in wd.wd_strerror(binding.WD_E_SCRATCH)
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="on a GPU the call would run on the made-up buffers")
+@pytest.mark.parametrize("num_envs", [451, 1000])
+@pytest.mark.parametrize("num_agents,obs_k,grid_size", [
+    (2575, 16, 161), (2575, 16, 900), (2800, 16, 400), (3072, 16, 60), (3072, 16, 2000),
+    (2850, 15, 160), (2850, 15, 900), (3072, 15, 173), (2700, 14, 400), (3072, 8, 300), (3000, 17, 300),
+])
+def test_static_entry_point_needs_no_tables_up_to_three_thousand_agents(num_envs, num_agents, obs_k, grid_size):
+    """Batches beyond those of the large-env layout run in one workgroup per env, which needs no work tables, also
+    where sixteen waves' staged rows do not fit LDS: such a call gets as far as the launch, which fails without a GPU."""
+    cfg = binding.make_config(num_envs, num_agents, 200, grid_size, 10, obs_k=obs_k)
+    with pytest.raises(wd.WdError) as ei:
+        wd.wd_iterate_static(cfg, fake_buffers(), 0x40000, 0)
+    assert ei.value.status == binding.WD_E_HIP
 
 
 def test_missing_library_fails_loudly(tmp_path, monkeypatch):

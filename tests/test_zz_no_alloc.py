@@ -51,3 +51,10 @@ def test_static_entry_point_equals_wd_iterate_two_calls_in_a_row():
     run_both(SMALLER, 12)  # smaller input on the same static array, which still holds the first run's tables
     run_both(PLAIN, 16)
     run_both(WAVE, 14)
+
+
+@pytest.mark.parametrize("grid_size", [165, 400], ids=["strips", "64-bit keys"])
+def test_static_entry_point_without_tables_where_a_handle_has_them(grid_size):
+    """K = 16 and 2600 agents: the rows that sixteen waves stage do not fit LDS.  A handle runs the large-env layout
+    there, the static call eight waves per env and no tables."""
+    run_both(dict(num_envs=451, num_agents=2600, num_taggers=260, grid_size=grid_size, episode_length=2, obs_k=16, seed=15), 3)
