@@ -831,6 +831,7 @@ int wd_rollout(wd_handle* h, const float* probs_ring, int ring_len, int k, const
       if (out && s + 1 < k) {
         if (out->action) q.action = out->action + int64_t(s) * EN;
         if (out->reward) q.reward = out->reward + int64_t(s) * EN;
+        if (out->reward && s == 0) q.kept_reward = h->params.reward;
         if (out->obs) q.obs = out->obs + int64_t(s) * EN * D;
       }
       q.done_log = (out && out->done) ? out->done + int64_t(s) * h->cfg.num_envs : nullptr;

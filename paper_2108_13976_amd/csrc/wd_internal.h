@@ -151,6 +151,8 @@ struct Params {
   float* obs;
   int32_t *t, *done, *n_live_runners, *tags_step;
   int32_t* done_log;     // optional [E]: done flags of an iteration before its reset (roll-outs)
+  const float* kept_reward;  // optional: `reward` is a slice that holds nothing yet, and what an env that is not
+                             // stepped keeps stands here (the first iteration of a roll-out launched one by one)
   int32_t rows_kept;     // 1: the obs buffer this launch writes still holds the rows this library wrote for
                          // the state the step starts from (a row whose agent was already out of play then
                          // differs from it in the time feature only)

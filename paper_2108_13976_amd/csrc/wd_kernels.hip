@@ -339,6 +339,11 @@ __device__ __forceinline__ void env_body(KernargParams pk, const StepOut out, co
         L.misc[kMiscStripMul] = int32_t(sg.mul);
         L.misc[kMiscStripRows] = sg.R;
       }
+    } else if constexpr (LOOPED || !STRIP) {  // (strips have a multi-step kernel: never one launch per iteration)
+      // an env that entered the roll-out done: its reward's slice holds nothing yet
+      const float* const kept = !LOOPED ? p.kept_reward : out.reward != p.reward ? p.reward : nullptr;
+      if (valid && kept)
+        for (int i = lt; i < N; i += ts) out.reward[abase + i] = kept[abase + i];
     }
     __syncthreads();  // tag keys and credits are read; the neighbour lists may overlay them
   }
@@ -1375,9 +1380,13 @@ __global__ __launch_bounds__(kSpreadObsThreads) void spread_obs_kernel(const Par
   }
   const bool reset_act = mode != kModeStep && (mode == kModeResetAll || done_now);
   if (mode != kModeStep && p.done_log && s == 0 && tid == 0) p.done_log[e] = done_now ? 1 : 0;
-  if (!stepped && !reset_act) return;  // this env keeps its state and its rows
   const int i_chunk = (N + p.big_slices - 1) / p.big_slices;
   const int i_begin = s * i_chunk, i_end = min(N, i_begin + i_chunk);
+  if (!stepped) {
+    if (!reset_act) return;  // this env keeps its state and its rows
+    if (stepping && p.kept_reward)  // (an env that entered the roll-out done: `reward` is a slice that holds nothing yet)
+      for (int i = i_begin + tid; i < i_end; i += ts) p.reward[abase + i] = p.kept_reward[abase + i];
+  }
   if (stepped) {
     // rewards of this slice and the positions of the groups that hold a tagger, from the quads this
     // thread has just put into LDS itself
@@ -1655,6 +1664,7 @@ __global__ __launch_bounds__(kWaveSize) void wave_env_kernel(const WaveArgs args
   };
   float f_next[4] = {0.0f, 0.0f, 0.0f, 0.0f};
   if (mode == kModeIterate) load_probs(f_next);
+  if (done && roll.reward && active) roll.reward[ai] = p.reward[ai];  // (an env that enters done: the first iteration does not step it)
   for (int s = 0; s < roll.steps; ++s) {
     const bool last = s + 1 == roll.steps;
     const uint64_t g = args.g0 + uint64_t(s);
@@ -1897,6 +1907,11 @@ small_env_kernel(const WaveArgs) {
     nlr = p.n_live_runners[e];
     if ((mode == kModeStep && done) || (mode == kModeResetDone && !done)) return;  // this env keeps its state and rows
   }
+  if (done && roll.reward) {  // (an env that enters done: the first iteration does not step it)
+#pragma unroll
+    for (int k = 0; k < H; ++k)
+      if (exists(k)) roll.reward[abase + agent(k)] = p.reward[abase + agent(k)];
+  }
   bool pos_dirty = false, live_dirty[H] = {};
   for (int s = 0; s < steps; ++s) {
     const bool last = s + 1 == steps;
@@ -1978,10 +1993,6 @@ small_env_kernel(const WaveArgs) {
       t += 1;
       done = (nlr == 0 || t >= p.T) ? 1 : 0;
       tags_out = tags;
-    } else if (roll.reward && last) {  // (an env that entered the launch done: not stepped)
-#pragma unroll
-      for (int k = 0; k < H; ++k)
-        if (exists(k)) roll.reward[int64_t(s) * EN + abase + agent(k)] = p.reward[abase + agent(k)];
     }
     WD_NEW_PHASE();
     if (mode != kModeStep) {

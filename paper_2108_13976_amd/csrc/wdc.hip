@@ -400,6 +400,8 @@ __global__ __launch_bounds__(kMaxThreads) void rollout_kernel(const Params p, co
     done = p.done[e] != 0;
   }
   float2 dir = p.table[h];
+  // (an env that enters done: the first iteration does not step it; the last slice is copied from the in-place arrays)
+  if (done && roll.reward && roll.steps > 1) roll.reward[a] = p.reward[a];
 
   for (int s = 0; s < roll.steps; ++s) {
     const bool last = s + 1 == roll.steps;
@@ -878,6 +880,7 @@ __global__ __launch_bounds__(kMaxThreads) __attribute__((amdgpu_waves_per_eu(KT 
     nlr = p.n_live_runners[e];
     tags_last = p.tags_step[e];
     if ((mode == kStep && done) || (mode == kResetDone && !done)) return;  // this env keeps its state and rows
+    if (done && roll.reward && valid) roll.reward[a] = p.reward[a];  // (an env that enters done: the first iteration does not step it)
   }
   float2 dir = make_float2(1.0f, 0.0f);
   if (live != 1) dir = p.table[wrap_heading(h, p.H)];  // (an agent in play looks its direction up when it moves)
@@ -954,8 +957,6 @@ __global__ __launch_bounds__(kMaxThreads) __attribute__((amdgpu_waves_per_eu(KT 
       nlr -= tags_last;
       t += 1;
       done = nlr == 0 || t >= p.T;
-    } else if (roll.reward && last && valid) {
-      roll.reward[int64_t(s) * EN + a] = p.reward[a];  // (an env that entered the launch done: not stepped)
     }
     if (roll.done && tid == 0) roll.done[int64_t(s) * p.E + e] = done ? 1 : 0;  // the flag before the reset
     if ((mode & (kResetDone | kResetAll)) && done) {  // back to the start state

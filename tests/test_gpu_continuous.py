@@ -307,3 +307,38 @@ def test_env_per_workgroup(n):
     assert err.max() <= TOL  # (features beyond 1 here: the bound of one rounded reciprocal is relative)
     assert np.array_equal(got["live"], orc.live) and np.array_equal(got["t"], orc.t)
     gpu.close()
+
+
+@pytest.mark.parametrize("num_agents,obs_k", [(5, 4), (32, 8), (33, 4), (105, 4), (300, 5)])
+@pytest.mark.parametrize("k", [1, 2, 4])
+def test_recorded_rewards_of_envs_that_enter_a_roll_out_done(num_agents, obs_k, k):
+    """The first iteration of a roll-out does not step an env that enters it done: the slice of its rewards then
+    holds what wdc_iterate leaves in the reward array.  Slices are filled with a mark before the call."""
+    E, N = 7, num_agents
+    kw = dict(num_envs=E, num_agents=N, num_taggers=max(1, N // 9), episode_length=5, world_size=(4.0 * N) ** 0.5,
+              obs_k=obs_k, seed=41)
+    ring = torch.from_numpy(np.stack([ctag_probs_for_step(41, r, E, N) for r in range(3)])).to("cuda:0")
+    a, b = wd.CTagEnvs(device="cuda:0", **kw), wd.CTagEnvs(device="cuda:0", **kw)
+    for env in (a, b):
+        env.reset(wd.WD_RESET_ALL)
+        env.iterate(ring[0])
+        env.done[::2] = 1
+        env.reward.copy_(torch.arange(E * N, device="cuda:0").view(E, N) * 0.25)
+    action = torch.full((k, E, N, 2), -9, dtype=torch.int32, device="cuda:0")
+    reward = torch.full((k, E, N), -99.0, dtype=torch.float32, device="cuda:0")
+    done = torch.full((k, E), -9, dtype=torch.int32, device="cuda:0")
+    obs = torch.full((k, E, N, a.D), -99.0, dtype=torch.float32, device="cuda:0")
+    wd.wdc_rollout(a.handle, ring.data_ptr(), 3, k,
+                   wd.binding.wdc_rollout_buffers(action.data_ptr(), reward.data_ptr(), done.data_ptr(), obs.data_ptr()))
+    for s in range(k):
+        p = ring[wd.wdc_get_step(b.handle) % 3]
+        b.sample(p), b.step()
+        assert torch.equal(done[s], b.done), s
+        b.reset(wd.WD_RESET_DONE)
+        assert torch.equal(action[s], b.action), s
+        assert torch.equal(reward[s], b.reward), s
+        assert torch.equal(obs[s], b.obs), s
+    got, want = a.to_host(), b.to_host()
+    for n in got:
+        assert got[n].tobytes() == want[n].tobytes(), n
+    a.close(), b.close()

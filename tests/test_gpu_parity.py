@@ -974,6 +974,61 @@ def test_full_observation_rows_in_a_launch_of_their_own(num_envs, num_agents):
     a.close(), b.close()
 
 
+ENTERED_DONE = {  # one configuration for every way a roll-out can run
+    "wave_env_kernel": dict(num_envs=9, num_agents=30, num_taggers=4, grid_size=12, obs_k=4),
+    "small_env_kernel": dict(num_envs=9, num_agents=101, num_taggers=9, grid_size=30, obs_k=4),
+    "one_workgroup": dict(num_envs=5, num_agents=300, num_taggers=30, grid_size=50, obs_k=4),
+    "packed_envs": dict(num_envs=301, num_agents=130, num_taggers=13, grid_size=40, obs_k=5),
+    "packed_envs_k_run_time": dict(num_envs=33, num_agents=131, num_taggers=13, grid_size=3000, obs_k=3),
+    "k_twelve_strips": dict(num_envs=5, num_agents=300, num_taggers=30, grid_size=50, obs_k=12),
+    "k_twelve_64_bit_keys": dict(num_envs=5, num_agents=140, num_taggers=14, grid_size=3000, obs_k=12),
+    "any_k": dict(num_envs=5, num_agents=90, num_taggers=9, grid_size=30, obs_k=17),
+    "full_views": dict(num_envs=5, num_agents=50, num_taggers=9, grid_size=30, obs_mode=1),
+    "full_views_rows_apart": dict(num_envs=5, num_agents=110, num_taggers=9, grid_size=30, obs_mode=1),
+    "large_env_pair": dict(num_envs=5, num_agents=800, num_taggers=80, grid_size=1000, obs_k=4),
+    "large_env_spread": dict(num_envs=3, num_agents=2500, num_taggers=200, grid_size=160, obs_k=4),
+}
+
+
+@pytest.mark.parametrize("name", list(ENTERED_DONE))
+@pytest.mark.parametrize("k", [1, 2, 4])
+def test_recorded_rewards_of_envs_that_enter_a_roll_out_done(name, k):
+    """The first iteration of a roll-out does not step an env that enters it done: the slice of its rewards then
+    holds what wd_iterate leaves in the reward array, the rewards of the last step.  Slices are filled with a mark
+    before the call, so that none may be left unwritten."""
+    import torch
+
+    import paper_2108_13976_amd as wd
+    from paper_2108_13976_amd import binding
+
+    kw = dict(ENTERED_DONE[name], seed=31, episode_length=5)
+    E, N = kw["num_envs"], kw["num_agents"]
+    ring = upload(np.stack([probs_for_step(31, r, E, N) for r in range(3)]), "cuda:0")
+    a, b = make_gpu(kw), make_gpu(kw)
+    for env in (a, b):
+        env.reset(wd.WD_RESET_ALL)
+        env.iterate(ring[0])
+        env.done[::2] = 1
+        env.reward.copy_(torch.arange(E * N, device="cuda:0").view(E, N) * 0.25)
+    action = torch.full((k, E, N), -9, dtype=torch.int32, device="cuda:0")
+    reward = torch.full((k, E, N), -99.0, dtype=torch.float32, device="cuda:0")
+    done = torch.full((k, E), -9, dtype=torch.int32, device="cuda:0")
+    obs = torch.full((k, E, N, a.D), -99.0, dtype=torch.float32, device="cuda:0")
+    wd.wd_rollout(a.handle, ring.data_ptr(), 3, k,
+                  binding.wd_rollout_buffers(action.data_ptr(), reward.data_ptr(), done.data_ptr(), obs.data_ptr()))
+    for s in range(k):
+        b.sample(ring[b.global_step % 3]), b.step()
+        assert torch.equal(done[s], b.done), s
+        b.reset(wd.WD_RESET_DONE)
+        assert torch.equal(action[s], b.action), s
+        assert torch.equal(reward[s], b.reward), s
+        assert torch.equal(obs[s], b.obs), s
+    got, want = a.to_host(), b.to_host()
+    for n in got:
+        assert got[n].tobytes() == want[n].tobytes(), n
+    a.close(), b.close()
+
+
 SMALL = [  # up to 128 agents in a wave per env, two agents per lane (small_env_kernel): edges of its sizes
     dict(num_envs=5, num_agents=65, num_taggers=64, grid_size=14, obs_k=1, tag_r2=5),
     dict(num_envs=9, num_agents=66, num_taggers=1, grid_size=20, obs_k=2),
@@ -1007,15 +1062,15 @@ def test_env_per_wave(n):
     a, b = make_gpu(kw), make_gpu(kw)
     for env in (a, b):
         env.reset(wd.WD_RESET_ALL)
-        env.done[::2] = 1  # (marked by the caller: such an env is reset by the next iteration without a step)
-        env.reward.fill_(7.0)
     for launch in range(3):
+        for env in (a, b):
+            env.done[launch::2] = 1  # (marked by the caller: such an env is reset by the next iteration without a step)
+            env.reward.fill_(7.0 + launch)
         rec = a.rollout(ring, k if launch else 1)
         for s in range(k if launch else 1):
             b.iterate(ring[b.global_step % 3])
             where = (launch, s)
-            if launch:
-                assert torch.equal(rec["reward"][s], b.reward), where
+            assert torch.equal(rec["reward"][s], b.reward), where
             assert torch.equal(rec["action"][s], b.action), where
             assert torch.equal(rec["obs"][s], b.obs), where
         got, want = a.to_host(), b.to_host()
