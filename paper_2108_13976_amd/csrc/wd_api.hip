@@ -553,7 +553,13 @@ int fill_params(const wd_config& c, const wd_buffers& b, wd::Params* p, bool own
   plan_spread(c, p);
   // Envs that fit a wave, in a batch that cannot fill the chip anyway: a wave per env, a lane per agent
   // (keys of 32 bits: squared distance << 6 | index).
-  p->wave_envs = (!p->big && c.num_agents <= wd::kWaveSize && c.num_envs <= kWaveEnvsMaxBatch &&
+  // With K > 8 also larger batches of envs of up to 32 agents, whose strips take longer than bucket rings did.  Measured, us per
+  // iteration, bucket rings / strips / wave_env_kernel: K = 12: 9000 x 20 37.2 / 40.6 / 21.2, 20000 x 20 64.3 / 71.6 / 54.4,
+  // 20000 x 32 93.3 / 87.6 / 85.2, 20000 x 40 88.1 / 76.3 / 101; K = 9: 20000 x 12 28.3 / 36.8 / 27.0, 20000 x 32 61.1 / 79.9 /
+  // 66.2, 20000 x 34 78.6 / 69.0 / 74.8 (bucket rings were faster yet around
+  // 20000 x 24 with K = 9 and 10: 45.0 / 47.3 / 50.8 and 46.3 / 71.1 / 56.0).
+  const bool small_wide_views = p->strips && p->K > wd::kMaxRegisterK && c.num_agents <= 32;
+  p->wave_envs = (!p->big && c.num_agents <= wd::kWaveSize && (c.num_envs <= kWaveEnvsMaxBatch || small_wide_views) &&
                   c.obs_mode == WD_OBS_PARTIAL && p->K <= wd::kMaxRegisterK2 && c.grid_size <= 4096)
                      ? 1
                      : 0;

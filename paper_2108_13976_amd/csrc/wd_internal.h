@@ -47,7 +47,10 @@ constexpr int strip_pad(int k) {
   return a > b ? (a > c ? a : c) : (b > c ? b : c);
 }
 constexpr int kSmallEnvAgents = 128, kSmallEnvs = 2;  // small_env_kernel: two agents per lane (Params.wave_envs)
-constexpr int kStripScanAll = 64;  // lists up to this length are scanned whole instead of through windows
+// Lists up to this length are scanned whole instead of through windows.  For K > 8 that is the number of entries
+// in the windows, which an env of 65 to 110 agents does not fill (us per iteration with 64 / with this: 5000 x 70, K = 16
+// 81.0 / 60.8, 2000 x 100, K = 12 45.6 / 42.1; bucket rings 77.7 and 55.6)
+constexpr int strip_scan_all_up_to(int k) { return k <= kMaxRegisterK ? 64 : 2 * strip_half_own(k) + 4 * strip_half_adj(k); }
 constexpr int kStripQueue2 = 32;  // agents per env that may wait for the third, exact block search
 // Params.obs_mode: 0 partial, 1 full, and full with the rows written by a kernel of their own (full_rows_kernel)
 constexpr int kObsFullSplit = 2;

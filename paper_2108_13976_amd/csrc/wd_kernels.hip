@@ -510,14 +510,14 @@ __device__ __forceinline__ void env_body(KernargParams pk, const StepOut out, co
       no_retries = __builtin_amdgcn_readfirstlane(L0.misc[2]) == 0;
       if (!no_retries) {
         const int rows = __builtin_amdgcn_readfirstlane(L0.misc[kMiscStripRows]);
-        no_retries = __builtin_amdgcn_readfirstlane(int(L0.starts[rows * p.strip_C])) <= kStripScanAll;
+        no_retries = __builtin_amdgcn_readfirstlane(int(L0.starts[rows * p.strip_C])) <= strip_scan_all_up_to(KS);
       }
     }
     bool queued = false;  // this lane has put an agent into a retry queue
     if constexpr (STRIP) {
       // the fixed windows of the strip-sorted list; what they do not settle is queued
       for_each_wave_team([&](const TeamLds<WIDE, BIG>& Lt, const Strips st, int n_sorted) {
-        const bool few = n_sorted <= kStripScanAll;  // (uniform: an env's whole list is cheaper than its windows)
+        const bool few = n_sorted <= strip_scan_all_up_to(KS);  // (uniform: an env's whole list is cheaper than its windows)
         for (int q = wave_lane; q < n_sorted; q += wave_stride) {
           const uint32_t me = Lt.sorted.pos[q];
           if ((me >> 16) != kStripDeadY) {  // not tagged in this step

@@ -1029,7 +1029,7 @@ def test_recorded_rewards_of_envs_that_enter_a_roll_out_done(name, k):
     a.close(), b.close()
 
 
-SMALL = [  # up to 128 agents in a wave per env, two agents per lane (small_env_kernel): edges of its sizes
+SMALL = [  # up to 128 agents, most of them in a wave per env, two agents per lane (small_env_kernel): edges of its sizes
     dict(num_envs=5, num_agents=65, num_taggers=64, grid_size=14, obs_k=1, tag_r2=5),
     dict(num_envs=9, num_agents=66, num_taggers=1, grid_size=20, obs_k=2),
     dict(num_envs=3, num_agents=67, num_taggers=9, grid_size=30, obs_k=3, tag_r2=-1),
@@ -1042,6 +1042,14 @@ SMALL = [  # up to 128 agents in a wave per env, two agents per lane (small_env_
     dict(num_envs=2001, num_agents=64, num_taggers=7, grid_size=25, obs_k=4),                    # one agent per lane
     dict(num_envs=8193, num_agents=12, num_taggers=2, grid_size=11, obs_k=4),
     dict(num_envs=4001, num_agents=33, num_taggers=3, grid_size=16, obs_k=8),
+    # K > 8 in more envs than a round of waves: wave_env_kernel up to 32 agents, strips beyond (lists of up to 86 and
+    # 110 entries are scanned whole)
+    dict(num_envs=8193, num_agents=32, num_taggers=4, grid_size=17, obs_k=12),
+    dict(num_envs=8193, num_agents=33, num_taggers=4, grid_size=17, obs_k=12),
+    dict(num_envs=3, num_agents=86, num_taggers=8, grid_size=28, obs_k=9, tag_r2=0),
+    dict(num_envs=3, num_agents=87, num_taggers=8, grid_size=4, obs_k=12, tag_r2=0),
+    dict(num_envs=40, num_agents=110, num_taggers=9, grid_size=32, obs_k=16, tag_r2=0),
+    dict(num_envs=3, num_agents=113, num_taggers=9, grid_size=32, obs_k=13, tag_r2=1),
 ]
 
 
