@@ -462,6 +462,49 @@ void plan_spread(const wd_config& c, wd::Params* p) {
   p->g_stride_acc = (p->acc_tags + 1 + 3) / 4 * 4;
 }
 
+// Envs that run in a wave each, without workgroup barriers: in wave_env_kernel (a lane per agent, everything in
+// registers; keys of 32 bits: squared distance << 6 | index) or in small_env_kernel (up to 128 agents, tables in LDS, a
+// lane per group of four while it samples and moves).  Measured, us per iteration:
+//   env_kernel -> small_env_kernel, K = 4: 10 x 100 14.7 -> 11.7, 3000 x 100 26.8 -> 20.1, 20000 x 100 86.5 -> 70.7,
+// 3000 x 128 28.9 -> 22.9; 15000 x 100, K = 8 105.8 -> 78.3; 20000 x 5 24.4 -> 28.0.
+//   wave_env_kernel / small_env_kernel, agent counts that are multiples of four: K = 4: 2000 x 64 9.4 / 10.0, 3000 x 64
+// 12.9 / 11.8, 8000 x 64 24.3 / 19.1, 4000 x 32 9.8 / 10.7, 4000 x 40 11.5 / 11.3; 9000 x 20 12.2 / 14.3, 9000 x 28
+// 15.2 / 15.9, 20000 x 28 33.6 / 28.8; K = 8: 9000 x 20 17.0 / 18.9, 9000 x 28 21.4 / 20.9.
+//   Other agent counts, whose groups of four small_env_kernel loads and stores one by one: K = 1: 4000 x 33 9.3 / 10.9,
+// 8000 x 63 16.9 / 19.6, 20000 x 50 30.8 / 35.7 (env_kernel 36.1); K = 4: 4000 x 33 10.5 / 12.8, 6000 x 50 17.0 / 16.5,
+// 9000 x 25 14.5 / 18.4, 9000 x 41 19.1 / 20.4 (four recorded iterations 86.7 / 72.3), 20000 x 34 39.1 / 38.7 (38.2);
+// K = 8: 4000 x 41 16.3 / 16.3, 8000 x 33 21.2 / 22.6, 9000 x 33 23.2 / 24.2 (four recorded 123.9 / 91.6),
+// 18000 x 25, K = 5 29.2 / 32.4 (35.3); 20000 x 25 48.1 / 45.2 (42.5).
+//   With K > 8 (bucket rings, which strips replaced / strips / wave_env_kernel): K = 12: 9000 x 20 37.2 / 40.6 / 21.2,
+// 20000 x 20 64.3 / 71.6 / 54.4, 20000 x 32 93.3 / 87.6 / 85.2, 20000 x 40 88.1 / 76.3 / 101; K = 9: 20000 x 12 28.3 /
+// 36.8 / 27.0, 20000 x 32 61.1 / 79.9 / 66.2, 20000 x 34 78.6 / 69.0 / 74.8 (bucket rings were faster yet around
+// 20000 x 24 with K = 9 and 10: 45.0 / 47.3 / 50.8 and 46.3 / 71.1 / 56.0).
+void plan_waves(const wd_config& c, wd::Params* p) {
+  const int N = c.num_agents, E = c.num_envs, K = p->K;
+  p->wave_envs = 0;
+  if (p->big || c.obs_mode != WD_OBS_PARTIAL) return;
+  const int64_t agents = int64_t(E) * N;
+  const bool one_round = E <= kWaveEnvsMaxBatch, fours = N % 4 == 0;
+  if (p->strips && N <= wd::kSmallEnvAgents && K <= wd::kMaxRegisterK) {
+    bool small = N > wd::kWaveSize;
+    if (!small && fours)  // (a wave then has others to wait with)
+      small = one_round ? N >= 32 && agents >= 128000 : N >= 24;
+    else if (!small)
+      small = one_round ? agents >= 128000 && ((K > 4 && N > 40) || (K > 2 && N >= 48 && E >= 5000))
+                        : (K > 4 && N > 32) || (K > 2 && N >= 40);
+    if (small) {
+      p->wave_envs = wd::kSmallEnvs;
+      return;
+    }
+  }
+  if (N > wd::kWaveSize || K > wd::kMaxRegisterK2 || c.grid_size > 4096) return;
+  bool wave = one_round;
+  if (!wave && p->strips)
+    wave = K > wd::kMaxRegisterK ? N <= 32
+                                 : N >= 12 && (N < 24 || (!fours && (K <= 3 || (K <= 6 && N <= 32) || E <= 2 * kWaveEnvsMaxBatch)));
+  if (wave) p->wave_envs = 1;
+}
+
 // (`own_tables`: the handle's, allocated for it.  wd_iterate_static has a fixed array for them and refuses what exceeds
 // it, so the set of configurations that need tables there is a rule of its own: see wd.h)
 int fill_params(const wd_config& c, const wd_buffers& b, wd::Params* p, bool own_tables) {
@@ -551,29 +594,7 @@ int fill_params(const wd_config& c, const wd_buffers& b, wd::Params* p, bool own
   }
   if (!planned || !wd::env_kernel_available(*p)) return WD_E_UNSUPPORTED;
   plan_spread(c, p);
-  // Envs that fit a wave, in a batch that cannot fill the chip anyway: a wave per env, a lane per agent
-  // (keys of 32 bits: squared distance << 6 | index).
-  // With K > 8 also larger batches of envs of up to 32 agents, whose strips take longer than bucket rings did.  Measured, us per
-  // iteration, bucket rings / strips / wave_env_kernel: K = 12: 9000 x 20 37.2 / 40.6 / 21.2, 20000 x 20 64.3 / 71.6 / 54.4,
-  // 20000 x 32 93.3 / 87.6 / 85.2, 20000 x 40 88.1 / 76.3 / 101; K = 9: 20000 x 12 28.3 / 36.8 / 27.0, 20000 x 32 61.1 / 79.9 /
-  // 66.2, 20000 x 34 78.6 / 69.0 / 74.8 (bucket rings were faster yet around
-  // 20000 x 24 with K = 9 and 10: 45.0 / 47.3 / 50.8 and 46.3 / 71.1 / 56.0).
-  const bool small_wide_views = p->strips && p->K > wd::kMaxRegisterK && c.num_agents <= 32;
-  p->wave_envs = (!p->big && c.num_agents <= wd::kWaveSize && (c.num_envs <= kWaveEnvsMaxBatch || small_wide_views) &&
-                  c.obs_mode == WD_OBS_PARTIAL && p->K <= wd::kMaxRegisterK2 && c.grid_size <= 4096)
-                     ? 1
-                     : 0;
-  // small_env_kernel, also a wave per env: envs of 65 to 128 agents at any batch size; of 32 and more once the batch
-  // has 128 000 agents (a wave then has others to wait with), and of 12 and more beyond wave_env_kernel's batches.
-  // Measured, K = 4, us per iteration: env_kernel -> small_env_kernel: 10 x 100 14.7 -> 11.7, 3000 x 100
-  // 26.8 -> 20.1, 20000 x 100 86.5 -> 70.7, 3000 x 128 28.9 -> 22.9, 15000 x 100, K = 8 105.8 -> 78.3; 20000 x 5 24.4 -> 28.0,
-  // 20000 x 12 27.8 -> 25.3, 20000 x 32 38.5 -> 30.7, 20000 x 64 52.3 -> 44.0.  wave_env_kernel -> small_env_kernel:
-  // 10 x 64 7.1 -> 7.7, 2000 x 64 10.7 -> 10.4, 8000 x 64 27.7 -> 20.8; 2000 x 50 9.7 -> 11.1, 5000 x 50 17.2 -> 16.3;
-  // 5000 x 32 12.3 -> 12.2, 8000 x 20 13.2 -> 14.8.
-  if (p->strips && c.num_agents <= wd::kSmallEnvAgents && p->K <= wd::kMaxRegisterK &&
-      (c.num_agents > wd::kWaveSize || (c.num_agents >= 32 && int64_t(c.num_envs) * c.num_agents >= 128000) ||
-       (c.num_agents >= 12 && c.num_envs > kWaveEnvsMaxBatch)))
-    p->wave_envs = wd::kSmallEnvs;
+  plan_waves(c, p);
   return WD_OK;
 }
 

@@ -1042,6 +1042,14 @@ SMALL = [  # up to 128 agents, most of them in a wave per env, two agents per la
     dict(num_envs=2001, num_agents=64, num_taggers=7, grid_size=25, obs_k=4),                    # one agent per lane
     dict(num_envs=8193, num_agents=12, num_taggers=2, grid_size=11, obs_k=4),
     dict(num_envs=4001, num_agents=33, num_taggers=3, grid_size=16, obs_k=8),
+    # which of the two kernels, and agents whose groups of four are not aligned
+    dict(num_envs=8193, num_agents=24, num_taggers=3, grid_size=15, obs_k=4),
+    dict(num_envs=8193, num_agents=23, num_taggers=3, grid_size=15, obs_k=7),
+    dict(num_envs=8193, num_agents=35, num_taggers=3, grid_size=18, obs_k=8),
+    dict(num_envs=3200, num_agents=41, num_taggers=4, grid_size=20, obs_k=5),
+    dict(num_envs=5001, num_agents=50, num_taggers=5, grid_size=22, obs_k=3),
+    dict(num_envs=16385, num_agents=27, num_taggers=3, grid_size=16, obs_k=5),
+    dict(num_envs=16385, num_agents=63, num_taggers=6, grid_size=25, obs_k=1),
     # K > 8 in more envs than a round of waves: wave_env_kernel up to 32 agents, strips beyond (lists of up to 86 and
     # 110 entries are scanned whole)
     dict(num_envs=8193, num_agents=32, num_taggers=4, grid_size=17, obs_k=12),
