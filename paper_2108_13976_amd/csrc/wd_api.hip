@@ -43,11 +43,6 @@ constexpr int kSpreadMinAgents = 1024;
 // envs: one round of waves on the chip (256 compute units x 32 waves)
 constexpr int kWaveEnvsMaxBatch = 8192;
 
-// full observations: from this many agents per env on, or from a wave's agents and this many bytes of rows on,
-// the rows have a kernel of their own
-constexpr int kFullSplitAgents = 100;
-constexpr int64_t kFullSplitBytes = 64 << 20;
-
 int bits_for(uint32_t v) {  // bits needed to hold values 0..v
   int b = 1;
   while ((uint64_t(1) << b) <= v) ++b;
@@ -462,6 +457,28 @@ void plan_spread(const wd_config& c, wd::Params* p) {
   p->g_stride_acc = (p->acc_tags + 1 + 3) / 4 * 4;
 }
 
+// Full observations: whether the rows have a launch of their own (full_rows_kernel, spread over the chip).  It costs about 4
+// us (8 where step and reset are called one by one) and pays once the rows are long or many and one workgroup per env
+// (or per few envs) does not write them as fast: batches that fill the chip do where every row is written, and the two
+// forms differ in which rows are (an agent out of play keeps its row).  Measured, us per iteration, rows written by
+// env_kernel -> apart, in mid-training (a fifth to a half of the agents in play) and with every agent in play:
+//   agent counts that are multiples of four: 20 x 70 16.7 -> 20.5 (three separate calls 22.1 -> 29.4); 1000 x 64 44.5 -> 24.9
+// and 45.3 -> 32.6, 8000 x 64 240 -> 92.7 and 246 -> 190, 16000 x 64 184 -> 187 and 259 -> 370; 100 x 100 54.2 -> 22.2,
+// 8000 x 100 373 -> 218 and 427 -> 420, 16000 x 100 366 -> 411 and 568 -> 813; 2000 x 220 252 -> 167 and 356 -> 406;
+// 200 x 500 364 -> 66.9 and 370 -> 189, 500 x 500 373 -> 157 and 384 -> 469, 2000 x 1000 2587 -> 1676 and 6085 -> 6162.
+//   others (env_kernel deals their slots to all lanes of a team, which serves small batches better): 1000 x 65 20.3 -> 25.9 and
+// 22.7 -> 33.6; 200 x 101 24.0 -> 19.6 and 24.6 -> 23.0, 1000 x 101 28.3 -> 34.2 and 46.3 -> 59.5; 200 x 150 36.3 -> 21.9
+// and 36.4 -> 27.0, 1000 x 150 44.0 -> 49.9 and 91.0 -> 110; 500 x 201 56.5 -> 39.4 and 83.5 -> 94.1, 5000 x 201 406 -> 329
+// and 681 -> 826; 2000 x 251 227 -> 221 and 516 -> 513; 1000 x 499 410 -> 301 and 1049 -> 908.
+bool full_rows_apart(const wd_config& c) {
+  const int N = c.num_agents, E = c.num_envs;
+  if (N % 4 == 0) {
+    const int64_t row_bytes = int64_t(E) * N * obs_dim(&c) * 4;
+    return (N >= 100 || (N >= wd::kWaveSize && row_bytes >= (64 << 20))) && E <= 8192;
+  }
+  return N >= 250 || (N >= 200 && E <= 512) || (N >= 100 && E <= 256);
+}
+
 // Envs that run in a wave each, without workgroup barriers: in wave_env_kernel (a lane per agent, everything in
 // registers; keys of 32 bits: squared distance << 6 | index) or in small_env_kernel (up to 128 agents, tables in LDS, a
 // lane per group of four while it samples and moves).  Measured, us per iteration:
@@ -520,14 +537,7 @@ int fill_params(const wd_config& c, const wd_buffers& b, wd::Params* p, bool own
   p->K = c.obs_mode == WD_OBS_PARTIAL ? c.obs_k : 0;
   p->D = obs_dim(&c);
   p->obs_mode = c.obs_mode;
-  // Full observations: a second launch for the rows (about 4 us, 8 where step and reset are called one by one)
-  // pays once the rows are long or many.  Measured, us per iteration, rows written by env_kernel -> by their own
-  // kernel: 20 envs x 70 agents 16.7 -> 20.5 (three separate calls 22.1 -> 29.4), 400 x 70 19.8 -> 25.3, 20 x 130
-  // 27.9 -> 21.5 (34.2 -> 30.4), 100 x 100 54.2 -> 22.2, 2000 x 64 (134 MB of rows) 78.4 -> 52.1, 200 x 500 359 -> 71.7;
-  // 2000 x 1000 2640 -> 1782 in mid-training, 6227 -> 6354 with every agent in play.
-  const int64_t row_bytes = int64_t(c.num_envs) * c.num_agents * p->D * 4;
-  if (c.obs_mode == WD_OBS_FULL && (c.num_agents >= kFullSplitAgents || (c.num_agents >= wd::kWaveSize && row_bytes >= kFullSplitBytes)))
-    p->obs_mode = wd::kObsFullSplit;
+  if (c.obs_mode == WD_OBS_FULL && full_rows_apart(c)) p->obs_mode = wd::kObsFullSplit;
   p->env_offset = uint32_t(c.env_offset);
   p->seed_lo = uint32_t(c.seed);
   p->seed_hi = uint32_t(c.seed >> 32);

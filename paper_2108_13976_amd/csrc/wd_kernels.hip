@@ -967,8 +967,8 @@ __device__ __forceinline__ void env_body(KernargParams pk, const StepOut out, co
 #undef WD_NEW_PHASE
 
 // ----------------------------------------------------------------------------------
-// Rows of full observations (the second observation mode of Sec. 5.1), for envs of kFullSplitAgents and
-// more.  Workgroup (e, s) looks at every slices-th run of eight consecutive rows of env e and writes those that
+// Rows of full observations (the second observation mode of Sec. 5.1), where the host chose a launch of their
+// own for them.  Workgroup (e, s) looks at every slices-th run of eight consecutive rows of env e and writes those that
 // env_kernel has marked: a wave per row, the env's positions in LDS.  (The taggers' rows come first and are
 // always written, so consecutive runs would give the slices unequal work; single rows instead of runs
 // cost the memory locality.)  A row starts 0..3 floats past a 16-byte boundary and is written by itself: its
