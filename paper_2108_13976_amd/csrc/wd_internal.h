@@ -51,7 +51,6 @@ constexpr int kSmallEnvAgents = 128, kSmallEnvs = 2;  // small_env_kernel: two a
 // in the windows, which an env of 65 to 110 agents does not fill (us per iteration with 64 / with this: 5000 x 70, K = 16
 // 81.0 / 60.8, 2000 x 100, K = 12 45.6 / 42.1; bucket rings 77.7 and 55.6)
 constexpr int strip_scan_all_up_to(int k) { return k <= kMaxRegisterK ? 64 : 2 * strip_half_own(k) + 4 * strip_half_adj(k); }
-constexpr int kStripQueue2 = 32;  // agents per env that may wait for the third, exact block search
 // Params.obs_mode: 0 partial, 1 full, and full with the rows written by a kernel of their own (full_rows_kernel)
 constexpr int kObsFullSplit = 2;
 constexpr uint32_t kRowWanted = 0x7FD5A3C1u;  // first feature of a row that full_rows_kernel is to write (a NaN: never a feature)

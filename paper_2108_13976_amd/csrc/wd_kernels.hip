@@ -148,7 +148,7 @@ __device__ __forceinline__ void env_body(KernargParams pk, const StepOut out, co
   if (lt == 0) {  // every mode passes a barrier before the neighbour search appends
     L.misc[2] = 0;  // set where the team's env is stepped or reset
     L.misc[3] = 0;
-    L.misc[kMiscQueue2] = 0;
+    L.misc[kMiscUnsettled] = 0;
   }
   // Two workgroup-wide votes: some env of the workgroup is being reset; some env gets no new
   // rows.  Inside the roll-out loop (LOOPED) they are flags in the first team's scalars, cleared
@@ -537,7 +537,7 @@ __device__ __forceinline__ void env_body(KernargParams pk, const StepOut out, co
         }
       });
       // second try, wider windows and two more strips, for the few that are queued; what is left
-      // after that (hardly ever anything) waits in a short queue of its own for the block search
+      // after that (hardly ever anything, but most agents of a crowd) is marked and waits for the block search
       // (two lanes per agent: an even lane takes what lies below the agent's slot, its odd neighbour
       // what lies above)
       // (no lane of the workgroup has queued anything: as good as no retries at all)
@@ -557,15 +557,15 @@ __device__ __forceinline__ void env_body(KernargParams pk, const StepOut out, co
         bool ok = strip_window_search<KS, strip_half_own2(KS), strip_half_adj2(KS), strip_half_far2(KS), true>(
             keys, me, q, side, st, p.key_shift, n_sorted, p.pad_l, Lt.sorted.pos, Lt.sorted.id, Lt.starts, Lt.edges);
         if (side) return;  // the even lane goes on for both
-        if (!ok) {
-          const int at = atomicAdd(&Lt.misc[kMiscQueue2], 1);
-          if (at < kStripQueue2) {
-            reinterpret_cast<uint16_t*>(Lt.misc + 4)[at] = uint16_t(q);  // (the scan scratch, idle by now)
-          } else {  // the queue is full: search here and now
-            strip_block_search<KS>(keys, me, uint32_t(q), st, p.key_shift, G, Lt.sorted.pos, Lt.sorted.id, Lt.starts,
-                                   Lt.edges);
-            ok = true;
-          }
+        if (!ok) {  // (the agent's place in the neighbour lists holds its radius until the block search)
+          const uint32_t id = Lt.sorted.id[q];
+          const int radius = strip_radius(keys, st, p.key_shift);
+          if constexpr (CN)
+            Lt.nbr_lo[id] = uint32_t(radius);
+          else
+            Lt.nbr[id * K] = uint16_t(radius);
+          Lt.retry[j] = uint16_t(q | kUnsettled);
+          Lt.misc[kMiscUnsettled] = 1;
         }
         if (ok) put_neighbours_of(Lt, Lt.sorted.id[q], keys);
       };
@@ -618,14 +618,18 @@ __device__ __forceinline__ void env_body(KernargParams pk, const StepOut out, co
     if constexpr (STRIP) {
       if (!no_retries)
       for_each_wave_team([&](const TeamLds<WIDE, BIG>& Lt, const Strips st, int) {
-        const int n_wait = min(__builtin_amdgcn_readfirstlane(Lt.misc[kMiscQueue2]), kStripQueue2);
-        const uint16_t* const queue2 = reinterpret_cast<const uint16_t*>(Lt.misc + 4);
-        for (int j = wave_lane; j < n_wait; j += wave_stride) {
-          const uint32_t q = queue2[j];
+        if (__builtin_amdgcn_readfirstlane(Lt.misc[kMiscUnsettled]) == 0) return;
+        const int n_retry = __builtin_amdgcn_readfirstlane(Lt.misc[3]);
+        for (int j = wave_lane; j < n_retry; j += wave_stride) {
+          uint32_t q = Lt.retry[j];
+          if (!(q & kUnsettled)) continue;
+          q -= kUnsettled;
+          const uint32_t id = Lt.sorted.id[q];
+          const int radius = CN ? int(Lt.nbr_lo[id]) : int(Lt.nbr[id * K]);
           Key keys[KT];
           strip_block_search<KS>(keys, Lt.sorted.pos[q], q, st, p.key_shift, G, Lt.sorted.pos, Lt.sorted.id, Lt.starts,
-                                 Lt.edges);
-          put_neighbours_of(Lt, Lt.sorted.id[q], keys);
+                                 Lt.edges, radius);
+          put_neighbours_of(Lt, id, keys);
         }
       });
     } else if (search) {

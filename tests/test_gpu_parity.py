@@ -1031,6 +1031,74 @@ def test_recorded_rewards_of_envs_that_enter_a_roll_out_done(name, k):
     a.close(), b.close()
 
 
+CROWDS = {  # strips in every form: one env and several envs per workgroup, 256 to 1024 threads, whole lists, lists of K + 1
+    "packed_k_one": dict(num_envs=37, num_agents=150, grid_size=40, obs_k=1),
+    "packed_k_five": dict(num_envs=40, num_agents=131, grid_size=36, obs_k=5),
+    "packed_k_eleven": dict(num_envs=300, num_agents=133, grid_size=36, obs_k=11),
+    "compact_ids": dict(num_envs=3, num_agents=600, grid_size=77, obs_k=4),
+    "wide_ids": dict(num_envs=9, num_agents=1100, grid_size=100, obs_k=4),
+    "k_two_wide_workgroup": dict(num_envs=60, num_agents=1301, grid_size=115, obs_k=2),
+    "k_eight": dict(num_envs=3, num_agents=300, grid_size=55, obs_k=8),
+    "k_twelve": dict(num_envs=3, num_agents=300, grid_size=55, obs_k=12),
+    "k_sixteen": dict(num_envs=4, num_agents=520, grid_size=5, obs_k=16),
+}
+
+
+@pytest.mark.parametrize("where", ["one_cell", "clusters", "walls", "one_row", "one_column", "far_corners"])
+@pytest.mark.parametrize("name", list(CROWDS))
+def test_crowds(name, where):
+    """Start positions that a caller wrote, with the agents of an env crowded in a few places, where neither try of the
+    strip search's windows settles most of them: rows against the oracle, then a few iterations in lockstep, and the
+    same iterations as one recorded roll-out."""
+    import torch
+
+    import paper_2108_13976_amd as wd
+    from oracle import tag_oracle
+
+    kw = dict(CROWDS[name], episode_length=3, seed=61, tag_r2=0)
+    E, N, G = kw["num_envs"], kw["num_agents"], kw["grid_size"]
+    kw["num_taggers"] = N // 12
+    rng = np.random.default_rng(sum(map(ord, name + where)))
+    x, y = rng.integers(0, G, (2, E, N))
+    if where == "one_cell":
+        x[:], y[:] = G // 2, G // 3
+        x[:, ::17] = rng.integers(0, G, x[:, ::17].shape)
+    elif where == "clusters":
+        at = rng.integers(0, G, (2, E, 3))
+        pick = rng.integers(0, 3, (E, N))
+        x, y = [np.clip(np.take_along_axis(a, pick, 1) + np.rint(rng.normal(0, 0.02 * G + 0.5, (E, N))), 0, G - 1) for a in at]
+    elif where == "walls":
+        side = rng.integers(0, 4, (E, N))
+        x = np.where(side == 0, 0, np.where(side == 1, G - 1, x))
+        y = np.where(side == 2, 0, np.where(side == 3, G - 1, y))
+    elif where == "one_row":
+        y[:, N // 9:] = G - 1
+    elif where == "one_column":
+        x[:, N // 9:] = 0
+    else:  # two crowds with nothing between them, one of them of fewer than K agents
+        x[:], y[:] = 0, 0
+        x[:, :5], y[:, :5] = G - 1, G - 1
+    gpu, rec, orc = make_gpu(kw), make_gpu(kw), make_oracle(kw)
+    for env in (gpu, rec):
+        env.reset(wd.WD_RESET_ALL)
+        env.pos_x0.copy_(torch.from_numpy(x.astype(np.int32))), env.pos_y0.copy_(torch.from_numpy(y.astype(np.int32)))
+        env.done.fill_(1)
+        env.reset(wd.WD_RESET_DONE)
+    orc.reset()
+    orc.pos_x0[:], orc.pos_y0[:], orc.done[:] = x, y, 1
+    orc.reset(tag_oracle.RESET_DONE)
+    assert_equal_state(gpu.to_host(), orc, "after the reset")
+    ring = np.stack([probs_for_step(61, g, E, N) for g in range(4)])
+    out = rec.rollout(upload(ring, "cuda:0"), 4)
+    for g in range(4):
+        gpu.iterate(upload(ring[g], gpu.device))
+        orc.iterate(ring[g], g)
+        got = gpu.to_host()
+        assert_equal_state(got, orc, f"after iterate {g}")
+        assert out["obs"][g].cpu().numpy().tobytes() == got["obs"].tobytes(), g
+    gpu.close(), rec.close()
+
+
 SMALL = [  # up to 128 agents, most of them in a wave per env, two agents per lane (small_env_kernel): edges of its sizes
     dict(num_envs=5, num_agents=65, num_taggers=64, grid_size=14, obs_k=1, tag_r2=5),
     dict(num_envs=9, num_agents=66, num_taggers=1, grid_size=20, obs_k=2),
