@@ -506,10 +506,15 @@ __global__ __launch_bounds__(kMaxThreads) void rollout_kernel(const Params p, co
 // 33.8 -> 18.2 us per iteration (46 MB: 2.5 TB/s); 250 x 820, four recorded iterations per launch: 1007 ->
 // 70.6 us (184 MB).  Five waves per SIMD: at 64 registers (eight) the windows spill, 26 us instead of 18.8.
 // ----------------------------------------------------------------------------------
-constexpr int kScanAll = 44;      // lists up to this length are compared whole: 11 instructions an entry against
-                                  // about 500 for the 38 window slots and their bounds (K = 4)
+constexpr int kScanAll = 64;      // lists up to this length (the most that six bits number) are compared whole: 11
+                                  // instructions an entry against about 500 for the 38 window slots and their bounds
+                                  // (K = 4), and hardly ever a second try.  us per iteration with 44 / 64: 500 x 64
+                                  // 12.6 / 11.2, in three clusters 20.4 / 11.1; 2000 x 48, K = 8 16.9 / 16.3, 25.6 / 15.8
+constexpr int kCrowdCost = 250;   // what a queued agent of a crowd costs a wave, in the instructions that a lane spends on
+                                  // 1 / (8 + 4 KT) list entries
 constexpr int kGroupLanes = 16, kGroups = wd::kWaveSize / kGroupLanes;  // lanes that serve a queued agent together
-enum Misc : int { kTags = 0, kQueued = 1, kStray = 2, kWaveTotals = 4, kMiscWords = 20 };
+enum Misc : int { kTags = 0, kQueued = 1, kStray = 2, kOpen = 3, kWaveTotals = 4, kMiscWords = 20 };
+constexpr float kOpenLimit = -1.0f;  // in limit[]: this queued agent is to be compared with the whole list
 
 struct BlockLds {
   float4* me;         // [threads] x, y and the velocity components after the move
@@ -695,11 +700,39 @@ __device__ __forceinline__ void search_by_wave(const BlockLds& L, int q, int n, 
   }
 }
 
+// One agent by its lane: every entry of the list.
+template <int KT>
+__device__ __forceinline__ void search_by_lane(const BlockLds& L, int q, int n) {
+  const float2 me = L.list[q];
+  uint64_t keys[KT];
+#pragma unroll
+  for (int k = 0; k < KT; ++k) keys[k] = ~0ull;
+  for (int s0 = 0; s0 < n; s0 += 4) {
+    uint64_t key[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) key[j] = exact_key(L, min(s0 + j, n - 1), q, me);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (s0 + j >= n) key[j] = ~0ull;
+      if (key[j] < keys[KT - 1]) {
+#pragma unroll
+        for (int k = 0; k < KT; ++k) {
+          const uint64_t lo = key[j] < keys[k] ? key[j] : keys[k];
+          key[j] = key[j] < keys[k] ? keys[k] : key[j];
+          keys[k] = lo;
+        }
+      }
+    }
+  }
+  uint32_t* const out = reinterpret_cast<uint32_t*>(L.nearest + uint32_t(L.ids[q]) * KT);
+#pragma unroll
+  for (int k = 0; k < KT / 2; ++k) out[k] = (uint32_t(keys[2 * k]) & 0xFFFFu) | (uint32_t(keys[2 * k + 1]) << 16);  // (~0: kNobody)
+}
+
 // The queued agents, four to a wave, sixteen lanes each.  No neighbour of such an agent is farther than its
 // limit, so only the bins that this radius touches are read, a strip at a time; the entries within the limit
 // are collected with their exact keys, and an entry's rank among them is its place.  An agent without a
-// limit, or with more entries in it than there is room for (agents crowded at one distance), is left to the
-// whole wave.
+// limit, or with more entries in it than there is room for (agents crowded at one distance), is marked open.
 template <int KT>
 __device__ __forceinline__ void search_queue(const BlockLds& L, const Strips& g, int n, int queued, int lane, int wave,
                                              int waves) {
@@ -707,7 +740,7 @@ __device__ __forceinline__ void search_queue(const BlockLds& L, const Strips& g,
   uint64_t* const found = L.found + wave * wd::kWaveSize + group * kGroupLanes;
   for (int w0 = wave * kGroups; w0 < queued; w0 += waves * kGroups) {
     const int w = w0 + group;
-    bool open = false;  // the whole wave has to serve this one
+    bool open = false;
     if (w < queued) {
       const int q = L.queue[w];
       const float limit = L.limit[w];
@@ -742,10 +775,26 @@ __device__ __forceinline__ void search_queue(const BlockLds& L, const Strips& g,
         }
       }
     }
-    const uint64_t rest = __ballot(open);
-    for (int k = 0; k < kGroups; ++k)
-      if ((rest >> (k * kGroupLanes)) & 1ull) search_by_wave<KT>(L, L.queue[w0 + k], n, lane);
+    if (open && sub == 0) {
+      L.limit[w] = kOpenLimit;
+      atomicAdd(&L.misc[kOpen], 1);
+    }
     wd::dev::wave_sync_lds();  // `found` is read before the next agents overwrite it
+  }
+}
+
+// The agents marked open: a few of them by a whole wave each; many (a crowd, whose distances the windows cannot tell
+// apart) by a lane each, which costs as much as comparing all pairs, but once for all of them.  With everybody on one spot
+// every one of them had a wave, one after the other: 2000 x 105 177 us per iteration -> 34.8 (comparing all pairs: 44.0),
+// 250 x 820, K = 8 1143 -> 402 (484); in three clusters 2000 x 105, K = 8 69.4 -> 45.9 (41.6), 250 x 820, K = 8 420 -> 225 (345).
+template <int KT>
+__device__ __forceinline__ void search_open(const BlockLds& L, int n, int queued, int open, int tid, int waves) {
+  // (instructions of a wave: KT passes over the list and reductions for an agent, or the list once for 64)
+  if (open * KT * (2 * n / 5 + 90) <= waves * n * (20 + 4 * KT)) {
+    for (int w = __builtin_amdgcn_readfirstlane(tid >> 6); w < queued; w += waves)
+      if (L.limit[w] == kOpenLimit) search_by_wave<KT>(L, L.queue[w], n, tid & (wd::kWaveSize - 1));
+  } else if (tid < queued && L.limit[tid] == kOpenLimit) {
+    search_by_lane<KT>(L, L.queue[tid], n);
   }
 }
 
@@ -991,8 +1040,19 @@ __global__ __launch_bounds__(kMaxThreads) __attribute__((amdgpu_waves_per_eu(KT 
     }
     __syncthreads();
     const int queued = L.misc[kQueued];
-    search_queue<KT>(L, g, n, queued, lane, wave, plan.threads / wd::kWaveSize);
+    const int waves = plan.threads / wd::kWaveSize;
+    // a crowd: a lane each is faster than groups of sixteen lanes one after the other (uniform)
+    const bool all_open = 2 * queued > n && queued * kCrowdCost > n * waves * (8 + 4 * KT);
+    if (!all_open) search_queue<KT>(L, g, n, queued, lane, wave, waves);
     __syncthreads();
+    const int open = all_open ? 0 : L.misc[kOpen];
+    if (all_open) {
+      if (tid < queued) search_by_lane<KT>(L, L.queue[tid], n);
+      __syncthreads();
+    } else if (open != 0) {
+      search_open<KT>(L, n, queued, open, tid, waves);
+      __syncthreads();
+    }
     WDC_NEW_PHASE();
     store_rows<KT>(p, L, last ? p.obs + int64_t(e) * N * p.D : nullptr,
                    roll.obs ? roll.obs + (int64_t(s) * EN + int64_t(e) * N) * p.D : nullptr, tid, x, y, v, dir, tagger,

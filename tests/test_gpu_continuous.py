@@ -342,3 +342,53 @@ def test_recorded_rewards_of_envs_that_enter_a_roll_out_done(num_agents, obs_k, 
     for n in got:
         assert got[n].tobytes() == want[n].tobytes(), n
     a.close(), b.close()
+
+
+@pytest.mark.parametrize("where", ["one_point", "few_points", "clusters", "corners", "one_edge", "off_the_world"])
+@pytest.mark.parametrize("num_agents,obs_k", [(33, 4), (45, 8), (64, 2), (65, 7), (105, 4), (200, 6), (820, 4), (1024, 8)])
+def test_crowds(num_agents, obs_k, where):
+    """Start states that a caller wrote, with the agents of an env crowded in a few places or at equal distances, where
+    the windows of block_kernel's search settle few of them and the rest are served by groups of lanes, by a wave or by
+    a lane each: against the oracle, over two iterations too, and those as one recorded roll-out."""
+    E, N, L = 3, num_agents, 12.0
+    kw = dict(num_envs=E, num_agents=N, num_taggers=N // 10, episode_length=5, world_size=L, obs_k=obs_k, seed=71,
+              tag_r2=0.0)
+    rng = np.random.default_rng(1000 * N + len(where))
+    x, y = rng.uniform(0, L, (2, E, N)).astype(np.float32)
+    if where == "one_point":
+        x[:], y[:] = L / 2, L / 3
+        x[1, ::5] = rng.uniform(0, L, x[1, ::5].shape)
+    elif where == "few_points":
+        x, y = [np.float32(L / 8) * rng.integers(0, 3, (E, N)).astype(np.float32) for _ in range(2)]
+    elif where == "clusters":
+        at = rng.uniform(0, L, (2, E, 3))
+        pick = rng.integers(0, 3, (E, N))
+        x, y = [np.clip(np.take_along_axis(a, pick, 1) + rng.normal(0, 0.02 * L, (E, N)), 0, L).astype(np.float32) for a in at]
+    elif where == "corners":
+        x, y = [np.float32(L) * rng.integers(0, 2, (E, N)).astype(np.float32) for _ in range(2)]
+        x[:, ::9] = rng.uniform(0, L, x[:, ::9].shape)
+    elif where == "one_edge":
+        x[:, N // 7:] = 0
+    else:
+        x[:, ::3] += 2 * np.float32(L)
+    gpu, rec = wd.CTagEnvs(device="cuda:0", **kw), wd.CTagEnvs(device="cuda:0", **kw)
+    orc = ctag_oracle.CTagOracle(**kw)
+    for env in (gpu, rec):
+        env.reset(wd.WD_RESET_ALL)
+        env.x0.copy_(torch.from_numpy(x)), env.y0.copy_(torch.from_numpy(y))
+        env.done.fill_(1)
+        env.reset(wd.WD_RESET_DONE)
+    orc.reset()
+    orc.x0[:], orc.y0[:], orc.done[:] = x, y, 1
+    orc.reset(ctag_oracle.RESET_DONE)
+    got = gpu.to_host()
+    err = np.abs(got["obs"].astype(np.float64) - orc.obs) / np.maximum(1.0, np.abs(orc.obs))
+    assert err.max() <= TOL  # (features beyond 1 off the world: the bound of one rounded reciprocal is relative)
+    ring = np.stack([ctag_probs_for_step(71, g, E, N) for g in range(2)])
+    out = rec.rollout(torch.from_numpy(ring).to("cuda:0"), 2)
+    for g in range(2):
+        gpu.iterate(torch.from_numpy(ring[g]).to("cuda:0"))
+        orc.iterate(ring[g], g)
+        assert_same(gpu, orc, f"after iterate {g}")
+        assert out["obs"][g].cpu().numpy().tobytes() == gpu.to_host()["obs"].tobytes(), g
+    gpu.close(), rec.close()
