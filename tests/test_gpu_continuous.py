@@ -392,3 +392,43 @@ def test_crowds(num_agents, obs_k, where):
         assert_same(gpu, orc, f"after iterate {g}")
         assert out["obs"][g].cpu().numpy().tobytes() == gpu.to_host()["obs"].tobytes(), g
     gpu.close(), rec.close()
+
+
+MULTI = [  # block_kernel as a multi-step kernel: rows lane by lane (odd K) and staged, one to sixteen waves, more than 64 KB of
+           # LDS, the tag check from the runners' and from the taggers' side
+    dict(num_agents=33, num_taggers=3, obs_k=1),
+    dict(num_agents=33, num_taggers=20, obs_k=8),
+    dict(num_agents=129, num_taggers=3, obs_k=3),
+    dict(num_agents=129, num_taggers=90, obs_k=6, tag_r2=0.05),
+    dict(num_agents=820, num_taggers=40, obs_k=6, tag_r2=0.02),
+    dict(num_agents=820, num_taggers=4, obs_k=4, tag_r2=-1.0),
+    dict(num_agents=1024, num_taggers=60, obs_k=8, tag_r2=0.02),
+    dict(num_agents=1024, num_taggers=2, obs_k=3),
+]
+
+
+@pytest.mark.parametrize("n", range(len(MULTI)))
+def test_multi_step_env_per_workgroup(n):
+    """Recorded roll-outs entered with envs that are done, over episode ends, against single iterations byte for byte."""
+    kw = dict(dict(num_envs=5, episode_length=6, world_size=18.0, seed=80 + n, tag_r2=1.0), **MULTI[n])
+    E, N, k = kw["num_envs"], kw["num_agents"], 4
+    ring = torch.from_numpy(np.stack([ctag_probs_for_step(80 + n, r, E, N) for r in range(3)])).to("cuda:0")
+    a, b = wd.CTagEnvs(device="cuda:0", **kw), wd.CTagEnvs(device="cuda:0", **kw)
+    for env in (a, b):
+        env.reset(wd.WD_RESET_ALL)
+    for launch in range(3):
+        for env in (a, b):
+            env.done[launch::2] = 1  # (such an env is reset by the next iteration without a step)
+            env.reward.fill_(3.0 + launch)
+        rec = a.rollout(ring, k if launch else 1)
+        for s in range(k if launch else 1):
+            b.sample(ring[wd.wdc_get_step(b.handle) % 3]), b.step()
+            where = (launch, s)
+            assert torch.equal(rec["done"][s], b.done), where
+            b.reset(wd.WD_RESET_DONE)
+            for name in ("action", "reward", "obs"):
+                assert torch.equal(rec[name][s], getattr(b, name)), (name, where)
+        got, want = a.to_host(), b.to_host()
+        for name in got:
+            assert got[name].tobytes() == want[name].tobytes(), (launch, name)
+    a.close(), b.close()
