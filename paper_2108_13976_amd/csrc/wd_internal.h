@@ -86,7 +86,7 @@ struct Params {
   // thread lt of a team owns groups lt, lt + ts, ... (gpt of them).
   int32_t NG;            // groups per env = ceil(N / 4)
   int32_t NPAD;          // 4 * NG rounded up to 8: per-agent LDS arrays are padded to this
-  int32_t wg_size;       // 256; 512 or 1024 for one env of more than 1024 or 3072 agents
+  int32_t wg_size;       // 256; 512 or 1024 for one larger env (see plan_env_kernels)
   int32_t stage_rows_log2;  // rows a wave transposes through LDS per flush: 32 or 16
   int32_t ts_log2, teams_per_wg, gpt;
   int32_t vec4;          // N % 4 == 0: a group's global slices are 16-byte aligned
@@ -100,7 +100,7 @@ struct Params {
   int32_t wide, idx_bits, xy_bits;
   int32_t dead_dx;       // 32-bit form: y offset that marks a runner tagged in this step
   FastDiv div_N, div_NG;
-  // Strip-sorted list (32-bit keys, K = 1 .. 8 compiled in, small layout): strips of the grid times
+  // Strip-sorted list (32-bit keys, K = 1 .. 16, small layout): strips of the grid times
   // columns of 2^cshift cells; the table of bin starts takes the place of the bucket tables.
   int32_t strips;        // 1: this configuration runs the strip variant of the env kernels
   int32_t cshift, strip_C;  // column of cell x = x >> cshift; columns per strip
@@ -145,8 +145,8 @@ struct Params {
   uint32_t* g_acc;         // [2][E][g_stride_acc]: credits per tagger, number of tags
   int64_t g_stride_acc;
   int32_t acc_credits, acc_tags;  // word offsets inside one env's accumulators
-  int32_t wave_envs;     // 1: envs of at most 64 agents in a small batch run in wave_env_kernel; kSmallEnvs: envs of up to
-                         // kSmallEnvAgents in small_env_kernel; a wave per env in both
+  int32_t wave_envs;     // 1: wave_env_kernel (envs of at most 64 agents); kSmallEnvs: small_env_kernel (of up to
+                         // kSmallEnvAgents); a wave per env in both (see plan_waves)
   // device buffers (borrowed from the caller)
   int32_t *pos_x, *pos_y, *pos_x0, *pos_y0, *live, *action;
   float* reward;

@@ -501,10 +501,10 @@ __global__ __launch_bounds__(kMaxThreads) void rollout_kernel(const Params p, co
 // agent's state stays in its thread's registers.
 //
 // Bound: comparing all pairs was bound by the vector ALUs; now a launch is the latency of one workgroup's
-// chain (about 23 000 cycles at 105 agents: 8 000 for the first loads, 3 000 the list, 4 000 the search,
-// 4 000 the rows) between a burst of loads and a burst of row stores.  2000 envs x 105 agents, K = 4:
-// 33.8 -> 18.2 us per iteration (46 MB: 2.5 TB/s); 250 x 820, four recorded iterations per launch: 1007 ->
-// 70.6 us (184 MB).  Five waves per SIMD: at 64 registers (eight) the windows spill, 26 us instead of 18.8.
+// chain (about 23 000 cycles at 105 agents: 7 800 for the first loads and draws, 5 200 the list, 2 100 the tag
+// check, 4 700 the search, 4 000 the rows) between a burst of loads and a burst of row stores.  2000 envs x 105
+// agents, K = 4: 33.8 -> 18.0 us per iteration (46 MB: 2.5 TB/s); 250 x 820, four recorded iterations per launch:
+// 1007 -> 70.4 us (184 MB).  Five waves per SIMD: at 64 registers (eight) the windows spill, 26 us instead of 18.8.
 // ----------------------------------------------------------------------------------
 constexpr int kScanAll = 64;      // lists up to this length (the most that six bits number) are compared whole: 11
                                   // instructions an entry against about 500 for the 38 window slots and their bounds

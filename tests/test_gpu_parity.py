@@ -518,10 +518,9 @@ def test_multi_step_rollout_equals_single_iterations(name, k, rounds):
                                     ("k_twelve_strips_packed", 4), ("k_sixteen_strips_packed", 3),
                                     ("k_thirteen_strips_crowded", 4), ("k_sixteen_strips_wide_workgroup", 3)])
 def test_multi_step_rollout_of_other_launch_shapes(name, k):
-    """Large-env layout, full observations, K > 8 (wd_rollout runs one launch per iteration), the
-    multi-step kernel in 512- and 1024-thread workgroups and its variants for other K than 4, the
-    kernel with a wave per env: slices
-    and final state against k calls of wd_iterate."""
+    """Large-env layout, full observations, K > 8 without strips (wd_rollout runs one launch per iteration), the
+    multi-step kernel in 512- and 1024-thread workgroups and its variants for other K than 4 (up to 16 with strips),
+    the kernels with a wave per env: slices and final state against k calls of wd_iterate."""
     import paper_2108_13976_amd as wd
 
     kw = dict(EDGE[name], seed=77)
