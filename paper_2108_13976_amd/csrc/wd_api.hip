@@ -42,6 +42,8 @@ constexpr int kSpreadMaxWorkgroups = 192;
 constexpr int kSpreadMinAgents = 1024;
 // envs: one round of waves on the chip (256 compute units x 32 waves)
 constexpr int kWaveEnvsMaxBatch = 8192;
+// threads that a launch may have at most (one more and their number wraps, without an error)
+constexpr int64_t kMaxLaunchThreads = (int64_t(1) << 32) - 1;
 
 int bits_for(uint32_t v) {  // bits needed to hold values 0..v
   int b = 1;
@@ -500,6 +502,7 @@ void plan_waves(const wd_config& c, wd::Params* p) {
   const int N = c.num_agents, E = c.num_envs, K = p->K;
   p->wave_envs = 0;
   if (p->big || c.obs_mode != WD_OBS_PARTIAL) return;
+  if ((int64_t(E) + 3) * wd::kWaveSize > kMaxLaunchThreads) return;  // (beyond 67 million envs; fewer lanes per env then)
   const int64_t agents = int64_t(E) * N;
   const bool one_round = E <= kWaveEnvsMaxBatch, fours = N % 4 == 0;
   if (p->strips && N <= wd::kSmallEnvAgents && K <= wd::kMaxRegisterK) {

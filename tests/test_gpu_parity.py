@@ -1162,3 +1162,35 @@ def test_env_per_wave(n):
         for name in got:
             assert got[name].tobytes() == want[name].tobytes(), (launch, name)
     a.close(), b.close()
+
+
+@pytest.mark.parametrize("num_agents", [12, 13])
+def test_more_envs_than_a_launch_has_waves(num_agents):
+    """Batches of 2^26 envs and more: a wave per env would be 2^32 threads, more than one launch can have.  Envs from both
+    ends and around the place where such a number wraps, against the oracle (about 90 GB of device memory)."""
+    import torch
+
+    import paper_2108_13976_amd as wd
+    from oracle import tag_oracle
+
+    if torch.cuda.mem_get_info()[0] < 120 << 30:
+        pytest.skip("needs 120 GB of free device memory")
+    E = (1 << 26) + 5
+    kw = dict(num_envs=E, num_agents=num_agents, num_taggers=2, grid_size=11, episode_length=9, obs_k=1, seed=3)
+    gpu = make_gpu(kw)
+    gpu.reset(wd.WD_RESET_ALL)
+    probs = torch.rand((E, num_agents, 5), device=gpu.device)
+    probs /= 2.5
+    places = [(0, 8), ((1 << 25) - 4, (1 << 25) + 4), ((1 << 26) - 4, E)]
+    oracles = [tag_oracle.TagOracle(**dict(kw, num_envs=hi - lo, env_offset=lo)) for lo, hi in places]
+    for orc in oracles:
+        orc.reset()
+    for g in range(2):
+        gpu.iterate(probs)
+        gpu.torch_stream.synchronize()
+        for (lo, hi), orc in zip(places, oracles):
+            orc.iterate(probs[lo:hi].cpu().numpy(), g)
+            assert_equal_state({n: t[lo:hi].cpu().numpy() for n, t in gpu.tensors.items()}, orc, f"envs {lo}.. after iterate {g}")
+    gpu.close()
+    del gpu, probs
+    torch.cuda.empty_cache()
