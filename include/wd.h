@@ -133,7 +133,8 @@ int wd_query_layout(const wd_config* cfg, wd_layout* out);
  * chooses the launch geometry and returns a handle in *out.  Enqueues nothing; the buffers' contents are not read.
  * WD_E_UNSUPPORTED if no kernel of this build covers the configuration (an env whose
  * tables exceed one workgroup's LDS: beyond about 13 900 agents with 32-bit keys, 11 500
- * with 64-bit keys, 8192 for full observations or K > 16).  Envs too large for one
+ * with 64-bit keys, 8192 for full observations or K > 16; or more envs than a launch has teams of
+ * eight threads: 2^29, possible with 2 and 3 agents only).  Envs too large for one
  * workgroup's LDS (for K = 15 and 16 from about 2600 agents on), and batches of few envs of
  * more than 1300 agents (of 384 with wide views, K > 8, or grids too large for 16-bit scaled
  * positions), run in the large-env layout, whose work tables (about 20 bytes per agent) the

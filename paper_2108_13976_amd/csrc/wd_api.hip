@@ -608,6 +608,8 @@ int fill_params(const wd_config& c, const wd_buffers& b, wd::Params* p, bool own
   if (!planned || !wd::env_kernel_available(*p)) return WD_E_UNSUPPORTED;
   plan_spread(c, p);
   plan_waves(c, p);
+  const int64_t groups = (int64_t(c.num_envs) + p->teams_per_wg - 1) / p->teams_per_wg;
+  if (!p->wave_envs && groups * p->wg_size > kMaxLaunchThreads) return WD_E_UNSUPPORTED;
   return WD_OK;
 }
 

@@ -71,6 +71,8 @@ def test_bad_configurations_are_rejected(over):
     dict(num_agents=20000, num_taggers=100, grid_size=30000, tag_r2=50),   # the same with 64-bit keys
     dict(num_agents=9000, num_taggers=100, grid_size=300, obs_mode=binding.WD_OBS_FULL),
     dict(num_agents=9000, num_taggers=100, grid_size=300, obs_k=17),
+    dict(num_envs=(1 << 29) + 1, num_agents=3, num_taggers=1, grid_size=3, obs_k=1),   # 2^32 threads in a launch
+    dict(num_envs=(1 << 30) - 1, num_agents=2, num_taggers=1, grid_size=3, obs_mode=binding.WD_OBS_FULL),
 ])
 def test_valid_configurations_without_a_kernel_are_refused(over):
     """Sizes the header allows but no kernel of this build covers: WD_E_UNSUPPORTED from wd_create
