@@ -487,13 +487,13 @@ bool full_rows_apart(const wd_config& c) {
 //   env_kernel -> small_env_kernel, K = 4: 10 x 100 14.7 -> 11.7, 3000 x 100 26.8 -> 20.1, 20000 x 100 86.5 -> 70.7,
 // 3000 x 128 28.9 -> 22.9; 15000 x 100, K = 8 105.8 -> 78.3; 20000 x 5 24.4 -> 28.0.
 //   wave_env_kernel / small_env_kernel, agent counts that are multiples of four: K = 4: 2000 x 64 9.4 / 10.0, 3000 x 64
-// 12.9 / 11.8, 8000 x 64 24.3 / 19.1, 4000 x 32 9.8 / 10.7, 4000 x 40 11.5 / 11.3; 9000 x 20 12.2 / 14.3, 9000 x 28
-// 15.2 / 15.9, 20000 x 28 33.6 / 28.8; K = 8: 9000 x 20 17.0 / 18.9, 9000 x 28 21.4 / 20.9.
-//   Other agent counts, whose groups of four small_env_kernel loads and stores one by one: K = 1: 4000 x 33 9.3 / 10.9,
-// 8000 x 63 16.9 / 19.6, 20000 x 50 30.8 / 35.7 (env_kernel 36.1); K = 4: 4000 x 33 10.5 / 12.8, 6000 x 50 17.0 / 16.5,
+// 12.5 / 11.4, 8000 x 64 25.3 / 19.9, 4000 x 32 9.7 / 10.6, 4000 x 40 11.6 / 11.4; 9000 x 20 13.1 / 15.3, 9000 x 28
+// 15.2 / 16.0, 20000 x 28 33.6 / 28.7; K = 8: 9000 x 20 17.2 / 19.1, 9000 x 28 20.8 / 20.4.
+//   Other agent counts, whose groups of four small_env_kernel loads and stores one by one: K = 1: 4000 x 33 9.3 / 10.8,
+// 8000 x 63 16.9 / 19.6, 20000 x 50 30.8 / 35.7 (env_kernel 36.1); K = 4: 4000 x 33 10.5 / 12.7, 6000 x 50 17.5 / 16.9,
 // 9000 x 25 14.5 / 18.4, 9000 x 41 19.1 / 20.4 (four recorded iterations 86.7 / 72.3), 20000 x 34 39.1 / 38.7 (38.2);
-// K = 8: 4000 x 41 16.3 / 16.3, 8000 x 33 21.2 / 22.6, 9000 x 33 23.2 / 24.2 (four recorded 123.9 / 91.6),
-// 18000 x 25, K = 5 29.2 / 32.4 (35.3); 20000 x 25 48.1 / 45.2 (42.5).
+// K = 8: 4000 x 41 15.7 / 15.7, 8000 x 33 21.2 / 22.6, 9000 x 33 23.2 / 24.2 (four recorded 123.9 / 91.6),
+// 18000 x 25, K = 5 29.2 / 32.3 (35.3); 20000 x 25 48.1 / 45.2 (42.5).
 //   With K > 8 (bucket rings, which strips replaced / strips / wave_env_kernel): K = 12: 9000 x 20 37.2 / 40.6 / 21.2,
 // 20000 x 20 64.3 / 71.6 / 54.4, 20000 x 32 93.3 / 87.6 / 85.2, 20000 x 40 88.1 / 76.3 / 101; K = 9: 20000 x 12 28.3 /
 // 36.8 / 27.0, 20000 x 32 61.1 / 79.9 / 66.2, 20000 x 34 78.6 / 69.0 / 74.8 (bucket rings were faster yet around

@@ -786,7 +786,7 @@ __device__ __forceinline__ void search_queue(const BlockLds& L, const Strips& g,
 // The agents marked open: a few of them by a whole wave each; many (a crowd, whose distances the windows cannot tell
 // apart) by a lane each, which costs as much as comparing all pairs, but once for all of them.  With everybody on one spot
 // every one of them had a wave, one after the other: 2000 x 105 177 us per iteration -> 34.8 (comparing all pairs: 44.0),
-// 250 x 820, K = 8 1143 -> 402 (484); in three clusters 2000 x 105, K = 8 69.4 -> 45.9 (41.6), 250 x 820, K = 8 420 -> 225 (345).
+// 250 x 820, K = 8 1143 -> 402 (484); in three clusters 2000 x 105, K = 8 69.4 -> 45.9 (41.6), 250 x 820, K = 8 420 -> 237 (345).
 template <int KT>
 __device__ __forceinline__ void search_open(const BlockLds& L, int n, int queued, int open, int tid, int waves) {
   // (instructions of a wave: KT passes over the list and reductions for an agent, or the list once for 64)
