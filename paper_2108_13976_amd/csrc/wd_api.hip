@@ -469,8 +469,8 @@ void plan_spread(const wd_config& c, wd::Params* p) {
 // 8000 x 100 373 -> 218 and 427 -> 420, 16000 x 100 366 -> 411 and 568 -> 813; 2000 x 220 252 -> 167 and 356 -> 406;
 // 200 x 500 364 -> 66.9 and 370 -> 189, 500 x 500 373 -> 157 and 384 -> 469, 2000 x 1000 2587 -> 1676 and 6085 -> 6162.
 //   others (env_kernel deals their slots to all lanes of a team, which serves small batches better): 1000 x 65 20.3 -> 25.9 and
-// 22.7 -> 33.6; 200 x 101 24.0 -> 19.6 and 24.6 -> 23.0, 1000 x 101 28.3 -> 34.2 and 46.3 -> 59.5; 200 x 150 36.3 -> 21.9
-// and 36.4 -> 27.0, 1000 x 150 44.0 -> 49.9 and 91.0 -> 110; 500 x 201 56.5 -> 39.4 and 83.5 -> 94.1, 5000 x 201 406 -> 329
+// 22.7 -> 33.6; 200 x 101 24.0 -> 19.6 and 24.6 -> 23.0, 1000 x 101 28.3 -> 34.2 and 46.3 -> 59.5; 500 x 150 37.9 -> 30.0
+// and 49.7 -> 57.9, 1000 x 150 44.0 -> 49.9 and 91.0 -> 110; 750 x 243 (15 taggers) 169 -> 121; 500 x 201 56.5 -> 39.4 and 83.5 -> 94.1, 5000 x 201 406 -> 329
 // and 681 -> 826; 2000 x 251 227 -> 221 and 516 -> 513; 1000 x 499 410 -> 301 and 1049 -> 908.
 bool full_rows_apart(const wd_config& c) {
   const int N = c.num_agents, E = c.num_envs;
@@ -478,7 +478,7 @@ bool full_rows_apart(const wd_config& c) {
     const int64_t row_bytes = int64_t(E) * N * obs_dim(&c) * 4;
     return (N >= 100 || (N >= wd::kWaveSize && row_bytes >= (64 << 20))) && E <= 8192;
   }
-  return N >= 250 || (N >= 200 && E <= 512) || (N >= 100 && E <= 256);
+  return N >= 200 || (N >= 128 && E <= 512) || (N >= 100 && E <= 256);
 }
 
 // Envs that run in a wave each, without workgroup barriers: in wave_env_kernel (a lane per agent, everything in

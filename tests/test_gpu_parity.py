@@ -950,7 +950,7 @@ def test_edge_case(name, fused):
 
 @pytest.mark.parametrize("num_envs,num_agents", [(7, 100), (5, 101), (6, 102), (5, 103), (3, 353), (1100, 64), (1100, 67),
                                                   # env_kernel writes them from here on: odd counts in many envs, any count in very many
-                                                  (257, 101), (513, 203), (8193, 64)])
+                                                  (257, 101), (513, 143), (8193, 64)])
 def test_full_observation_rows_in_a_launch_of_their_own(num_envs, num_agents):
     """Full observations from the sizes on at which the rows have their own kernel: every remainder of the row
     length, against the oracle in separate and fused calls, and recorded slices (which start on 4-byte
