@@ -498,6 +498,13 @@ bool full_rows_apart(const wd_config& c) {
 // 20000 x 20 64.3 / 71.6 / 54.4, 20000 x 32 93.3 / 87.6 / 85.2, 20000 x 40 88.1 / 76.3 / 101; K = 9: 20000 x 12 28.3 /
 // 36.8 / 27.0, 20000 x 32 61.1 / 79.9 / 66.2, 20000 x 34 78.6 / 69.0 / 74.8 (bucket rings were faster yet around
 // 20000 x 24 with K = 9 and 10: 45.0 / 47.3 / 50.8 and 46.3 / 71.1 / 56.0).
+//   wave_env_kernel / quad_env_kernel, one round of waves.  Single calls: K = 4: 100 x 16 5.3 / 4.5, 8000 x 16 10.7 / 8.9,
+// 8000 x 5 9.3 / 8.5, 1200 x 18 6.0 / 5.6, 2500 x 18 6.8 / 7.0, 5000 x 18 8.9 / 9.7, 2500 x 24 7.1 / 7.2, 2500 x 32 7.7 / 7.3,
+// 2500 x 33 8.3 / 8.7, 100 x 50 6.0 / 5.3, 1200 x 64 7.8 / 7.5; K = 8: 100 x 60 7.3 / 5.0, 5000 x 20 12.1 / 11.4, 8000 x 15
+// 14.3 / 10.6; K = 14: 100 x 60 9.0 / 6.0, 5000 x 30 19.8 / 15.9.  Twenty recorded iterations: K = 4: 10 x 5 32.9 / 21.8,
+// 100 x 50 63.3 / 31.7, 1000 x 50 68.2 / 53.3, 1500 x 50 79.8 / 80.3, 8000 x 14 115.8 / 99.1, 4000 x 20 76.2 / 80.8, 8000 x 30
+// 228 / 205; K = 8: 100 x 50 81.5 / 37.9, 2000 x 50 145 / 141; K = 16: 100 x 50 112 / 51.3, 8000 x 50 1187 / 749; twelve:
+// K = 4: 5000 x 18 54.6 / 63, 5000 x 24 64.8 / 67, 2500 x 33 50.5 / 52, 2500 x 40 58.2 / 55; K = 8: 5000 x 20 86.6 / 88.
 void plan_waves(const wd_config& c, wd::Params* p) {
   const int N = c.num_agents, E = c.num_envs, K = p->K;
   p->wave_envs = 0;
@@ -523,6 +530,13 @@ void plan_waves(const wd_config& c, wd::Params* p) {
     wave = K > wd::kMaxRegisterK ? N <= 32
                                  : N >= 12 && (N < 24 || (!fours && (K <= 3 || (K <= 6 && N <= 32) || E <= 2 * kWaveEnvsMaxBatch)));
   if (wave) p->wave_envs = 1;
+  if (wave && one_round) {
+    // (`used`: of the lanes, per cent; the waves of an env repeat its move and tag check)
+    const int waves = (N + wd::kQuadAgents - 1) / wd::kQuadAgents;
+    const int used = 100 * N / (waves * wd::kQuadAgents), total = E * waves;
+    p->quad_single = K > 4 || waves == 1 || E <= 2000 || used >= 75;
+    p->quad_roll = K > 8 || waves == 1 || (K > 4 ? total <= 8000 || used >= 75 : total <= 5000 || used >= 82);
+  }
 }
 
 // (`own_tables`: the handle's, allocated for it.  wd_iterate_static has a fixed array for them and refuses what exceeds

@@ -46,6 +46,7 @@ constexpr int strip_pad(int k) {
   const int a = strip_half_own(k) + 2 * strip_half_adj(k), b = 2 * strip_half_adj2(k), c = strip_half_own2(k);
   return a > b ? (a > c ? a : c) : (b > c ? b : c);
 }
+constexpr int kQuadAgents = kWaveSize / 4;  // quad_env_kernel: agents that a wave serves, four lanes each
 constexpr int kSmallEnvAgents = 128, kSmallEnvs = 2;  // small_env_kernel: two agents per lane (Params.wave_envs)
 // Lists up to this length are scanned whole instead of through windows.  For K > 8 that is the number of entries
 // in the windows, which an env of 65 to 110 agents does not fill (us per iteration with 64 / with this: 5000 x 70, K = 16
@@ -147,6 +148,7 @@ struct Params {
   int32_t acc_credits, acc_tags;  // word offsets inside one env's accumulators
   int32_t wave_envs;     // 1: wave_env_kernel (envs of at most 64 agents); kSmallEnvs: small_env_kernel (of up to
                          // kSmallEnvAgents); a wave per env in both (see plan_waves)
+  int32_t quad_single, quad_roll;  // wave_envs == 1: quad_env_kernel instead, for single calls and in wd_rollout
   // device buffers (borrowed from the caller)
   int32_t *pos_x, *pos_y, *pos_x0, *pos_y0, *live, *action;
   float* reward;

@@ -1805,7 +1805,281 @@ __global__ __launch_bounds__(kWaveSize) void wave_env_kernel(const WaveArgs args
   }
 }
 
-hipError_t launch_wave_kernel(const Params& p, int mode, const Roll& roll, const float* probs, uint64_t g,
+// ----------------------------------------------------------------------------------
+// The same envs where a chain of instructions, not the chip, is what bounds them: a wave per sixteen agents of an
+// env, four lanes per agent in the search and the rows.  Every wave of an env moves and tag-checks all of its agents as
+// above (so they agree without exchanging anything; a barrier behind the first loads keeps a wave from overwriting state
+// that another has yet to read), lists the agents in play in its own piece of LDS, and serves agents 16 w .. 16 w + 15:
+// each of an agent's four lanes meets every fourth entry of the list, two exchanges between neighbouring lanes merge the
+// four sorted lists (the K smallest of two sorted lists are the smaller ones of opposite pairs, put in order by half a
+// bitonic network), and each lane writes every fourth slot of the row.
+//
+// Bound: still a wave's chain (about 400 instructions per iteration at 50 agents), and for 5 agents the launch.  100 envs x
+// 50 agents, twenty recorded iterations, K = 4: 63.3 -> 31.7 us (without a drawing wave 40.9; that and single calls in
+// one kernel 33.7), K = 8 81.5 -> 37.9, K = 16 112 -> 51.3; one iteration per call 6.0 -> 5.3, K = 14, 60 agents 9.0 -> 6.0.
+// ----------------------------------------------------------------------------------
+constexpr int kQuadPad = 16;  // list entries that a round of the search meets
+
+template <int kCtrl>
+__device__ __forceinline__ uint32_t quad_read(uint32_t v) {  // from another lane of the quad, by quad_perm control
+  return uint32_t(__builtin_amdgcn_update_dpp(0, int(v), kCtrl, 0xF, 0xF, true));
+}
+// keys[] and the list of the lane that kCtrl names, both ascending -> the KT smallest of both, ascending, in both lanes
+template <int KT, int kCtrl>
+__device__ __forceinline__ void merge_with_lane(uint32_t (&keys)[KT]) {
+  uint32_t low[KT];
+#pragma unroll
+  for (int k = 0; k < KT; ++k) low[k] = min(keys[k], quad_read<kCtrl>(keys[KT - 1 - k]));
+#pragma unroll
+  for (int d = KT / 2; d >= 1; d /= 2)
+#pragma unroll
+    for (int k = 0; k < KT; ++k)
+      if ((k & d) == 0) {
+        const uint32_t lo = min(low[k], low[k + d]), hi = max(low[k], low[k + d]);
+        low[k] = lo;
+        low[k + d] = hi;
+      }
+#pragma unroll
+  for (int k = 0; k < KT; ++k) keys[k] = low[k];
+}
+
+// The action of agent `a` in step g.
+__device__ __forceinline__ int draw_one(const WaveArgs& args, const float (&f)[4], int a, int e, uint64_t g) {
+  const Block4 r = random_block(args.p, uint32_t(e), uint32_t(a >> 2), uint32_t(g), uint32_t(g >> 32), kStreamAction);
+  const uint32_t w = (a & 2) ? ((a & 1) ? r.w[3] : r.w[2]) : ((a & 1) ? r.w[1] : r.w[0]);
+  return sample_action(f[0], f[1], f[2], f[3], w);
+}
+
+// The drawing wave of a launch of several iterations: actions do not depend on the state, so it draws them ahead of the
+// serving waves (an iteration by the barriers, its probabilities three further) and is the only one that waits for
+// memory: loads and stores share a counter that is waited on in order, so a wave that writes rows and then needs
+// probabilities waits for its rows to be written.
+__device__ __forceinline__ void draw_iterations(const WaveArgs& args, int32_t (*drawn)[kWaveSize], int a, int e, bool active,
+                                                int64_t ai) {
+  constexpr int kAhead = 4;
+  const Params& p = args.p;
+  const Roll& roll = args.roll;
+  const int64_t EN = int64_t(p.E) * p.N;
+  int ring_at = roll.ring_pos, asked = 0;
+  float f[kAhead][4];
+  const auto ask = [&](float (&to)[4]) {
+    if (asked < roll.steps && active) {
+      const float* pr = args.probs + int64_t(ring_at) * EN * kNumActions + ai * kNumActions;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) to[c] = pr[c];
+    }
+    ring_at = ring_at + 1 == roll.ring_len ? 0 : ring_at + 1;
+    ++asked;
+  };
+#pragma unroll
+  for (int j = 0; j < kAhead; ++j) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) f[j][c] = 0.0f;
+    ask(f[j]);
+  }
+  __syncthreads();  // (the serving waves have read the state)
+  for (int s0 = 0; s0 < roll.steps; s0 += kAhead) {
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) {
+      const int s = s0 + j;
+      if (s < roll.steps) {
+        const int act = draw_one(args, f[j], a, e, args.g0 + uint64_t(s));
+        ask(f[j]);
+        drawn[s & 1][a] = act;
+        if (active) {
+          if (s + 1 == roll.steps) p.action[ai] = act;
+          if (roll.action) roll.action[int64_t(s) * EN + ai] = act;
+        }
+        __syncthreads();
+      }
+    }
+  }
+}
+
+// KT: K <= KT, a power of two.  ROLL: several iterations, the last wave draws; else one call of any mode.
+template <int KT, bool ROLL>
+__global__ __launch_bounds__((4 + ROLL) * kWaveSize) void quad_env_kernel(const WaveArgs args) {
+  __shared__ uint2 lists[4][kWaveSize + kQuadPad];  // position and number (slot) of the agents in play, in index order
+  __shared__ int32_t drawn[2][kWaveSize];           // actions of this iteration and the next, by the drawing wave
+  const Params& p = args.p;
+  const Roll& roll = args.roll;
+  const int a = threadIdx.x & (kWaveSize - 1), e = blockIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+  const int N = p.N, N_tag = p.N_tag, G = p.G, K = p.K;
+  const int64_t D = 5 + 4 * K;
+  const bool active = a < N, writer = wave == 0;  // the first wave writes what belongs to all agents
+  const int64_t EN = int64_t(p.E) * N, ai = int64_t(e) * N + (active ? a : 0);
+  const int mode = ROLL ? int(kModeIterate) : args.mode;
+  const bool stepping = mode == kModeStep || mode == kModeIterate;
+  if constexpr (ROLL) {
+    if (wave == (int(blockDim.x) >> 6) - 1) {
+      draw_iterations(args, drawn, a, e, active, ai);
+      return;
+    }
+  }
+  uint2* const list = lists[wave];
+  const int mine = wave * kQuadAgents + (a >> 2), q = a & 3;  // the agent that this lane serves, and its lane of four
+  int x = 0, y = 0, act = 0;
+  bool lv = false;
+  int done = 0, t = 0, nlr = 0, tags_out = -1;  // (tags_out < 0: tags_step keeps its value)
+  float f[4] = {0.0f, 0.0f, 0.0f, 0.0f};  // (the first four probabilities decide a draw, the fifth action is the fall-through)
+  if (!ROLL && mode == kModeIterate && active) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) f[c] = args.probs[ai * kNumActions + c];
+  }
+  float kept = 0.0f;
+  if (mode != kModeResetAll) {
+    if (active) {
+      x = min(max(p.pos_x[ai], 0), G - 1);
+      y = min(max(p.pos_y[ai], 0), G - 1);
+      lv = p.live[ai] != 0;
+      if (mode == kModeStep) act = p.action[ai];
+      if (ROLL && roll.reward) kept = p.reward[ai];
+    }
+    done = p.done[e];
+    t = p.t[e];
+    nlr = p.n_live_runners[e];
+  }
+  __syncthreads();  // every wave has read the state
+  if (ROLL && done && roll.reward && active && writer) roll.reward[ai] = kept;  // (an env that enters done: the first iteration does not step it)
+  const int steps = ROLL ? roll.steps : 1;
+  for (int s = 0; s < steps; ++s) {
+    const bool last = s + 1 == steps;
+    if constexpr (ROLL) {
+      __syncthreads();  // the drawing wave has left this iteration's actions
+      act = drawn[s & 1][a];
+    } else if (mode == kModeIterate) {
+      act = draw_one(args, f, a, e, args.g0);
+      if (active && writer) p.action[ai] = act;
+    }
+    bool out_act = false;
+    if (stepping && !done) {
+      if (active && lv) {
+        x = min(max(x + (act == 4) - (act == 3), 0), G - 1);
+        y = min(max(y + (act == 1) - (act == 2), 0), G - 1);
+      }
+      const uint32_t here = pack_pos(x, y, true);
+      uint32_t best = ~0u;
+      if (p.tag_r2 >= 0)
+        for (int tg = 0; tg < N_tag; ++tg) {
+          const uint32_t at = uint32_t(__builtin_amdgcn_readlane(int(here), tg));
+          const uint32_t d2 = squared_length(__builtin_bit_cast(short2v, at) - __builtin_bit_cast(short2v, here));
+          best = min(best, (d2 << 6) | uint32_t(tg));
+        }
+      const bool tagged = active && a >= N_tag && lv && p.tag_r2 >= 0 && int(best >> 6) <= p.tag_r2;
+      const int tags = __popcll(__ballot(tagged));
+      int credit = 0;
+      if (tags)
+        for (int tg = 0; tg < N_tag; ++tg) {
+          const int c = __popcll(__ballot(tagged && int(best & 63u) == tg));
+          if (a == tg) credit = c;
+        }
+      if (tagged) lv = false;
+      if (active && writer) {
+        const float rew = a < N_tag ? static_cast<float>(credit) * p.tag_reward : (tagged ? p.tag_penalty : 0.0f);
+        if (last) p.reward[ai] = rew;
+        if (ROLL && roll.reward) roll.reward[int64_t(s) * EN + ai] = rew;
+      }
+      nlr -= tags;
+      t += 1;
+      done = (nlr == 0 || t >= p.T) ? 1 : 0;
+      tags_out = tags;
+      out_act = true;
+    }
+    if (mode != kModeStep) {
+      if (roll.done && threadIdx.x == 0) roll.done[int64_t(s) * p.E + e] = done;  // the flag before the reset clears it
+      if (mode == kModeResetAll || done) {
+        if (active) {
+          x = min(max(p.pos_x0[ai], 0), G - 1);
+          y = min(max(p.pos_y0[ai], 0), G - 1);
+        }
+        lv = active;
+        t = 0;
+        nlr = N - N_tag;
+        done = 0;
+        tags_out = 0;
+        out_act = true;
+      }
+    }
+    if (!out_act) continue;  // this env keeps its rows
+    // ---- observations: the K nearest agents in play, by (squared distance, index) ----
+    const uint64_t in_play = __ballot(active && lv);
+    const uint32_t here = pack_pos(x, y, true);
+    const int n = __popcll(in_play), n_taggers = __popcll(__ballot(active && lv && a < N_tag));
+    const int slot = int(__builtin_amdgcn_mbcnt_hi(uint32_t(in_play >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(in_play), 0u)));
+    if (active && lv) list[slot] = make_uint2(here, uint32_t(slot));
+    if (a < kQuadPad) list[n + a] = make_uint2(0u, ~0u);  // its keys are "nobody"
+    const uint32_t me = uint32_t(__shfl(int(here), mine & (kWaveSize - 1)));
+    // (number of the served agent in the list; bit 6: not in play)
+    const uint32_t own = uint32_t(__shfl(slot | (lv ? 0 : 64), mine & (kWaveSize - 1)));
+    wave_sync_lds();
+    uint32_t keys[KT];
+#pragma unroll
+    for (int k = 0; k < KT; ++k) keys[k] = ~0u;
+    for (int s0 = 0; s0 < n; s0 += kQuadPad) {
+      uint2 c[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) c[j] = list[s0 + 4 * j + q];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const uint32_t d2 = squared_length(__builtin_bit_cast(short2v, c[j].x) - __builtin_bit_cast(short2v, me));
+        const uint32_t key = (d2 << 6) | c[j].y;
+        insert_key<KT>(keys, c[j].y == own ? ~0u : key);
+      }
+    }
+    merge_with_lane<KT, 0xB1>(keys);  // quad_perm [1, 0, 3, 2]
+    merge_with_lane<KT, 0x4E>(keys);  // quad_perm [2, 3, 0, 1]
+    const int mx = pos_x_of(me), my = pos_y_of(me);
+    const bool served = mine < N, in_game = served && own < 64u;
+    const int64_t row_at = (int64_t(e) * N + mine) * D;
+    float* const rows[2] = {last ? p.obs + row_at : nullptr, ROLL && roll.obs ? roll.obs + int64_t(s) * EN * D + row_at : nullptr};
+    if (served) {
+      const Slot4 head = {static_cast<float>(mx) * p.inv_G, static_cast<float>(my) * p.inv_G, mine < N_tag ? 1.0f : 0.0f,
+                          in_game ? 1.0f : 0.0f};
+      const float t_frac = static_cast<float>(t) * p.inv_T;
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
+        if (rows[r]) {
+          if (q == 0) *reinterpret_cast<Slot4*>(rows[r]) = head;
+          if (q == 1) rows[r][4] = t_frac;
+        }
+    }
+#pragma unroll
+    for (int k0 = 0; k0 < KT; k0 += 4) {
+      const uint32_t key = (q & 2) ? ((q & 1) ? keys[k0 + 3] : keys[k0 + 2]) : ((q & 1) ? keys[k0 + 1] : keys[k0]);
+      if (served && k0 + q < K) {
+        // no branch: an empty slot looks up the first entry and is masked
+        const bool none = !in_game || key == ~0u;
+        const uint32_t j = none ? 0u : key & 63u;
+        const uint32_t other = list[j].x;
+        const Slot4 v = {none ? 0.0f : static_cast<float>(pos_x_of(other) - mx) * p.inv_G,
+                         none ? 0.0f : static_cast<float>(pos_y_of(other) - my) * p.inv_G,
+                         (!none && int(j) < n_taggers) ? 1.0f : 0.0f, none ? 0.0f : 1.0f};
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+          if (rows[r]) *reinterpret_cast<Slot4*>(rows[r] + 5 + 4 * (k0 + q)) = v;
+      }
+    }
+    wave_sync_lds();  // the list has been read
+  }
+  // the state, once per launch (an env that was neither stepped nor reset gets its own values back)
+  if (writer) {
+    if (active) {
+      p.pos_x[ai] = x;
+      p.pos_y[ai] = y;
+      p.live[ai] = lv ? 1 : 0;
+    }
+    if (a == 0) {
+      p.t[e] = t;
+      p.n_live_runners[e] = nlr;
+      p.done[e] = done;
+      if (tags_out >= 0) p.tags_step[e] = tags_out;
+    }
+  }
+}
+
+// (`recording`: a launch of wd_rollout, of one iteration or more)
+hipError_t launch_wave_kernel(const Params& p, int mode, const Roll& roll, bool recording, const float* probs, uint64_t g,
                               hipStream_t stream) {
   WaveArgs args;
   args.p = p;
@@ -1813,7 +2087,23 @@ hipError_t launch_wave_kernel(const Params& p, int mode, const Roll& roll, const
   args.probs = probs;
   args.g0 = g;
   args.mode = mode;
-  if (p.K == 4)
+  if (recording ? p.quad_roll : p.quad_single) {
+    const int serving = (p.N + kQuadAgents - 1) / kQuadAgents;
+    const dim3 threads((serving + (recording ? 1 : 0)) * kWaveSize);
+    const auto launch = [&](auto kt) {
+      constexpr int KT = decltype(kt)::value;
+      if (recording)
+        hipLaunchKernelGGL((quad_env_kernel<KT, true>), dim3(p.E), threads, 0, stream, args);
+      else
+        hipLaunchKernelGGL((quad_env_kernel<KT, false>), dim3(p.E), threads, 0, stream, args);
+    };
+    if (p.K <= 4)
+      launch(std::integral_constant<int, 4>{});
+    else if (p.K <= 8)
+      launch(std::integral_constant<int, 8>{});
+    else
+      launch(std::integral_constant<int, 16>{});
+  } else if (p.K == 4)
     hipLaunchKernelGGL(wave_env_kernel<4>, dim3(p.E), dim3(kWaveSize), 0, stream, args);
   else if (p.K <= kMaxRegisterK)
     hipLaunchKernelGGL(wave_env_kernel<0>, dim3(p.E), dim3(kWaveSize), 0, stream, args);
@@ -2328,7 +2618,7 @@ hipError_t launch_env_kernel(const Params& p, int mode, const float* probs, uint
     one.ring_len = 1;
     one.done = p.done_log;
     return p.wave_envs == kSmallEnvs ? launch_small_kernel(p, mode, one, probs, g, stream)
-                                     : launch_wave_kernel(p, mode, one, probs, g, stream);
+                                     : launch_wave_kernel(p, mode, one, false, probs, g, stream);
   }
   WD_DISPATCH(launch_env_variant, mode, probs, g, stream, pipe);
 }
@@ -2339,7 +2629,7 @@ bool rollout_available(const Params& p) {
 
 hipError_t launch_rollout(const Params& p, const Roll& roll, const float* ring, uint64_t g, hipStream_t stream) {
   if (p.wave_envs == kSmallEnvs) return launch_small_kernel(p, kModeIterate, roll, ring, g, stream);
-  if (p.wave_envs) return launch_wave_kernel(p, kModeIterate, roll, ring, g, stream);
+  if (p.wave_envs) return launch_wave_kernel(p, kModeIterate, roll, true, ring, g, stream);
   const int kx = variant_of(p);
   if (!p.wide) {
     if (kx == 4 && p.compact_nbr) return launch_rollout_variant<false, 4, true>(p, roll, ring, g, stream);

@@ -1130,29 +1130,23 @@ SMALL = [  # up to 128 agents, most of them in a wave per env, two agents per la
 ]
 
 
-@pytest.mark.parametrize("n", range(len(SMALL)))
-def test_env_per_wave(n):
-    """Against the oracle in separate and fused calls over episode ends; recorded multi-step launches (slices on
-    4-byte boundaries for odd sizes), entered with envs that are done, against single iterations byte for byte."""
+def recorded_against_single_iterations(kw, seed, launches):
+    """Recorded multi-step launches of launches[i] iterations, entered with envs that are done, against single iterations."""
     import torch
 
     import paper_2108_13976_amd as wd
 
-    kw = dict(SMALL[n], seed=500 + n, episode_length=5)
     E, N = kw["num_envs"], kw["num_agents"]
-    for fused in (False, True):
-        lockstep(kw, 8, 500 + n, fused=fused)
-    k = 4
-    ring = upload(np.stack([probs_for_step(500 + n, r, E, N) for r in range(3)]), "cuda:0")
+    ring = upload(np.stack([probs_for_step(seed, r, E, N) for r in range(3)]), "cuda:0")
     a, b = make_gpu(kw), make_gpu(kw)
     for env in (a, b):
         env.reset(wd.WD_RESET_ALL)
-    for launch in range(3):
+    for launch, k in enumerate(launches):
         for env in (a, b):
             env.done[launch::2] = 1  # (marked by the caller: such an env is reset by the next iteration without a step)
             env.reward.fill_(7.0 + launch)
-        rec = a.rollout(ring, k if launch else 1)
-        for s in range(k if launch else 1):
+        rec = a.rollout(ring, k)
+        for s in range(k):
             b.iterate(ring[b.global_step % 3])
             where = (launch, s)
             assert torch.equal(rec["reward"][s], b.reward), where
@@ -1162,6 +1156,42 @@ def test_env_per_wave(n):
         for name in got:
             assert got[name].tobytes() == want[name].tobytes(), (launch, name)
     a.close(), b.close()
+
+
+@pytest.mark.parametrize("n", range(len(SMALL)))
+def test_env_per_wave(n):
+    """Against the oracle in separate and fused calls over episode ends; recorded multi-step launches (slices on
+    4-byte boundaries for odd sizes), entered with envs that are done, against single iterations byte for byte."""
+    kw = dict(SMALL[n], seed=500 + n, episode_length=5)
+    for fused in (False, True):
+        lockstep(kw, 8, 500 + n, fused=fused)
+    recorded_against_single_iterations(kw, 500 + n, (1, 4, 4))
+
+
+QUAD = [  # four lanes per agent (quad_env_kernel): edges of its waves of sixteen agents, of its key lists and of the rule for it
+    dict(num_envs=5, num_agents=2, num_taggers=1, grid_size=4, obs_k=1),
+    dict(num_envs=11, num_agents=16, num_taggers=3, grid_size=9, obs_k=4),
+    dict(num_envs=11, num_agents=17, num_taggers=16, grid_size=1, obs_k=3),                  # one cell
+    dict(num_envs=3, num_agents=32, num_taggers=5, grid_size=4096, obs_k=8, tag_r2=9000000), # largest grid, all tagged at once
+    dict(num_envs=7, num_agents=33, num_taggers=1, grid_size=20, obs_k=5),
+    dict(num_envs=4, num_agents=48, num_taggers=40, grid_size=6, obs_k=9, tag_r2=0),
+    dict(num_envs=2, num_agents=49, num_taggers=7, grid_size=60, obs_k=16, tag_r2=-1),
+    dict(num_envs=1, num_agents=64, num_taggers=63, grid_size=25, obs_k=12),
+    dict(num_envs=2, num_agents=64, num_taggers=6, grid_size=30, obs_k=0),
+    dict(num_envs=2001, num_agents=18, num_taggers=2, grid_size=14, obs_k=2),                # wave_env_kernel for one iteration
+    dict(num_envs=2501, num_agents=27, num_taggers=3, grid_size=16, obs_k=4),                # and for several
+    dict(num_envs=8192, num_agents=14, num_taggers=2, grid_size=12, obs_k=4),
+]
+
+
+@pytest.mark.parametrize("n", range(len(QUAD)))
+def test_four_lanes_per_agent(n):
+    """The same checks as for the kernels above; the multi-step launches run past the four iterations whose
+    probabilities are asked for in advance."""
+    kw = dict(QUAD[n], seed=800 + n, episode_length=5)
+    for fused in (False, True):
+        lockstep(kw, 8, 800 + n, fused=fused)
+    recorded_against_single_iterations(kw, 800 + n, (1, 9, 5))
 
 
 @pytest.mark.parametrize("num_agents", [12, 13])
