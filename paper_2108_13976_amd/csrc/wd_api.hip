@@ -539,6 +539,60 @@ void plan_waves(const wd_config& c, wd::Params* p) {
   }
 }
 
+// Envs of 65 to 1024 agents that run in crew_env_kernel: a workgroup per env, a lane per agent.  A shorter chain of phases than
+// env_kernel's (or small_env_kernel's, up to 128 agents), for more lanes and instructions per agent: it wins while the chain is what
+// bounds a batch.  Measured, us per iteration in mid-training, K = 4, the other kernel -> crew_env_kernel:
+//   20 x 100 11.8 -> 9.1, 1000 x 100 14.2 -> 11.7, 3000 x 100 19.3 -> 17.7 (every agent in play 20.8 -> 21.3), 5000 x 100 24.5 -> 24.0
+// (28.1 -> 29.7); 800 x 65 12.6 -> 10.5, 4000 x 65 18.8 -> 18.1 (18.1 -> 20.3), four recorded iterations of 2000 x 65 39.3 -> 40.9;
+// 4000 x 128 25.7 -> 22.1; 100 x 160 16.2 -> 9.8, 5000 x 160 39.8 -> 32.6; 20 x 333 18.0 -> 10.6, 777 x 333 25.6 -> 18.2,
+// 3000 x 333 51.1 -> 45.5; 1600 x 450 37.8 -> 34.4; 1000 x 512 27.3 -> 25.1, 1200 x 512 29.7 -> 30.5; 500 x 700 24.3 -> 22.1,
+// 600 x 700 26.3 -> 28.8 (two workgroups fit a CU); 500 x 850 28.7 -> 27.2; 256 x 1000 23.4 -> 20.1, 300 x 1000 25.2 -> 28.5.
+//   K = 8: 500 x 333 28.4 -> 18.5, 2000 x 333 62.0 -> 43.2, 3000 x 100 25.0 -> 22.6, 5000 x 100 32.4 -> 35.0, 256 x 850 31.6 -> 23.0,
+// 400 x 850 36.2 -> 38.5; K = 1: 100 x 200 14.9 -> 9.6, 500 x 700 20.8 -> 19.7.  Four recorded iterations, K = 4: 100 x 200 57.6 -> 33.1,
+// 1200 x 333 109 -> 75, 500 x 700 88 -> 75, 2700 x 200 146 -> 95.
+bool crew_serves(const wd_config& c, const wd::Params& p) {
+  const int N = c.num_agents, E = c.num_envs, K = p.K;
+  if (p.big || !p.strips || N <= wd::kWaveSize || N > wd::kMaxEnvWorkgroupSize || K < 1 || K > wd::kMaxRegisterK) return false;
+  if (N < 96) return E <= 1500;
+  if (N < 112) return E <= 3000;
+  if (N <= wd::kSmallEnvAgents) return E <= 4096;
+  if (N <= 480) return int64_t(E) * N <= 1200000;
+  if (N > (K > 4 ? 768 : 896)) return E <= 256;
+  const int waves = (N + wd::kWaveSize - 1) / wd::kWaveSize;
+  return E <= 256 * (32 / waves);  // one round of workgroups
+}
+
+void plan_crew(const wd_config& c, wd::Params* p) {
+  p->crew_threads = 0;
+  if (!crew_serves(c, *p)) return;
+  const int N = c.num_agents, threads = (N + wd::kWaveSize - 1) / wd::kWaveSize * wd::kWaveSize;
+  p->crew_threads = threads;
+  p->wave_envs = 0;
+  const int KT = p->K <= 4 ? 4 : 8;  // places in the neighbour lists
+  int shift = 0;  // columns as narrow as four bins per lane allow
+  while (p->strip_rmax * (((c.grid_size - 1) >> shift) + 1) > 4 * threads) ++shift;
+  p->cshift = shift;
+  p->strip_C = ((c.grid_size - 1) >> shift) + 1;
+  int64_t off = 0;
+  auto take = [&off](int64_t bytes) {
+    const int64_t at = off;
+    off = align16(off + bytes);
+    return int32_t(at);
+  };
+  take(4 * threads);  // packed positions
+  p->crew_misc = take(4 * 40);
+  p->crew_taggers = take(4 * (c.num_taggers + 3));
+  p->crew_credits = take(4 * c.num_taggers);
+  p->crew_nbr = take(2 * KT * threads);
+  p->crew_list = take(4 * (threads + p->pad_l + p->pad_r));  // (the rows are staged over the list and its table)
+  p->crew_ids = take(2 * (threads + p->pad_l + p->pad_r));
+  p->crew_starts = take(2 * (p->strip_rmax * p->strip_C + 4));
+  p->crew_edges = take(2 * (p->strip_rmax + 2));
+  p->crew_queue = take(4 * threads);
+  off = std::max<int64_t>(off, p->crew_list + int64_t(threads / wd::kWaveSize) * 32 * p->D * 4);
+  p->crew_lds = int32_t(off);
+}
+
 // (`own_tables`: the handle's, allocated for it.  wd_iterate_static has a fixed array for them and refuses what exceeds
 // it, so the set of configurations that need tables there is a rule of its own: see wd.h)
 int fill_params(const wd_config& c, const wd_buffers& b, wd::Params* p, bool own_tables) {
@@ -622,6 +676,7 @@ int fill_params(const wd_config& c, const wd_buffers& b, wd::Params* p, bool own
   if (!planned || !wd::env_kernel_available(*p)) return WD_E_UNSUPPORTED;
   plan_spread(c, p);
   plan_waves(c, p);
+  plan_crew(c, p);
   const int64_t groups = (int64_t(c.num_envs) + p->teams_per_wg - 1) / p->teams_per_wg;
   if (!p->wave_envs && groups * p->wg_size > kMaxLaunchThreads) return WD_E_UNSUPPORTED;
   return WD_OK;

@@ -1194,6 +1194,31 @@ def test_four_lanes_per_agent(n):
     recorded_against_single_iterations(kw, 800 + n, (1, 9, 5))
 
 
+CREW = [  # a lane per agent (crew_env_kernel): edges of its workgroups, of lists compared whole (a quarter of the lanes), of the keys
+    dict(num_envs=3, num_agents=65, num_taggers=64, grid_size=14, obs_k=1, tag_r2=5),
+    dict(num_envs=1500, num_agents=66, num_taggers=6, grid_size=30, obs_k=4),
+    dict(num_envs=3, num_agents=129, num_taggers=1, grid_size=40, obs_k=2),
+    dict(num_envs=3, num_agents=129, num_taggers=31, grid_size=9, obs_k=3, tag_r2=300),       # 48 lanes' lists at most: whole after one step
+    dict(num_envs=4, num_agents=192, num_taggers=48, grid_size=1, obs_k=8, tag_r2=-1),        # one cell, nobody tagged
+    dict(num_envs=4, num_agents=192, num_taggers=47, grid_size=2, obs_k=7, tag_r2=0),
+    dict(num_envs=2, num_agents=255, num_taggers=25, grid_size=844, obs_k=5, tag_r2=40000),   # largest grid of its keys
+    dict(num_envs=2, num_agents=257, num_taggers=256, grid_size=30, obs_k=6, tag_r2=3000),    # everybody tagged at once
+    dict(num_envs=9, num_agents=333, num_taggers=33, grid_size=58, obs_k=4),
+    dict(num_envs=257, num_agents=640, num_taggers=60, grid_size=80, obs_k=4),
+    dict(num_envs=2, num_agents=1023, num_taggers=100, grid_size=60, obs_k=8),
+    dict(num_envs=2, num_agents=1024, num_taggers=300, grid_size=300, obs_k=4, tag_r2=100),
+]
+
+
+@pytest.mark.parametrize("n", range(len(CREW)))
+def test_lane_per_agent(n):
+    """The same checks as for the kernels above."""
+    kw = dict(CREW[n], seed=900 + n, episode_length=5)
+    for fused in (False, True):
+        lockstep(kw, 8, 900 + n, fused=fused)
+    recorded_against_single_iterations(kw, 900 + n, (1, 4, 3))
+
+
 @pytest.mark.parametrize("num_agents", [12, 13])
 def test_more_envs_than_a_launch_has_waves(num_agents):
     """Batches of 2^26 envs and more: a wave per env would be 2^32 threads, more than one launch can have.  Envs from both
