@@ -541,23 +541,34 @@ void plan_waves(const wd_config& c, wd::Params* p) {
 
 // Envs of 65 to 1024 agents that run in crew_env_kernel: a workgroup per env, a lane per agent.  A shorter chain of phases than
 // env_kernel's (or small_env_kernel's, up to 128 agents), for more lanes and instructions per agent: it wins while the chain is what
-// bounds a batch.  Measured, us per iteration in mid-training, K = 4, the other kernel -> crew_env_kernel:
-//   20 x 100 11.8 -> 9.1, 1000 x 100 14.2 -> 11.7, 3000 x 100 19.3 -> 17.7 (every agent in play 20.8 -> 21.3), 5000 x 100 24.5 -> 24.0
-// (28.1 -> 29.7); 800 x 65 12.6 -> 10.5, 4000 x 65 18.8 -> 18.1 (18.1 -> 20.3), four recorded iterations of 2000 x 65 39.3 -> 40.9;
-// 4000 x 128 25.7 -> 22.1; 100 x 160 16.2 -> 9.8, 5000 x 160 39.8 -> 32.6; 20 x 333 18.0 -> 10.6, 777 x 333 25.6 -> 18.2,
-// 3000 x 333 51.1 -> 45.5; 1600 x 450 37.8 -> 34.4; 1000 x 512 27.3 -> 25.1, 1200 x 512 29.7 -> 30.5; 500 x 700 24.3 -> 22.1,
-// 600 x 700 26.3 -> 28.8 (two workgroups fit a CU); 500 x 850 28.7 -> 27.2; 256 x 1000 23.4 -> 20.1, 300 x 1000 25.2 -> 28.5.
-//   K = 8: 500 x 333 28.4 -> 18.5, 2000 x 333 62.0 -> 43.2, 3000 x 100 25.0 -> 22.6, 5000 x 100 32.4 -> 35.0, 256 x 850 31.6 -> 23.0,
-// 400 x 850 36.2 -> 38.5; K = 1: 100 x 200 14.9 -> 9.6, 500 x 700 20.8 -> 19.7.  Four recorded iterations, K = 4: 100 x 200 57.6 -> 33.1,
-// 1200 x 333 109 -> 75, 500 x 700 88 -> 75, 2700 x 200 146 -> 95.
+// bounds a batch.  Measured, us per iteration in mid-training, the other kernel -> crew_env_kernel:
+//   K = 4: 20 x 100 11.8 -> 9.1, 1000 x 100 14.2 -> 11.7, 3000 x 100 19.3 -> 17.7 (every agent in play 20.8 -> 21.3), 5000 x 100
+// 24.4 -> 24.3 (28.1 -> 29.7), 20000 x 100 68.4 -> 70.3; 800 x 65 12.6 -> 10.5, 4000 x 65 18.8 -> 18.1 (18.1 -> 20.3), four recorded
+// iterations of 2000 x 65 39.3 -> 40.9; 4000 x 128 25.7 -> 22.1; 100 x 160 16.2 -> 9.8, 5000 x 160 39.8 -> 32.6, 8000 x 200 62.7 -> 58.6;
+// 20 x 333 17.8 -> 11.0, 777 x 333 25.4 -> 17.3, 3500 x 333 56.3 -> 49.2; 2000 x 480 37.7 -> 37.5; 1000 x 512 27.3 -> 25.1, 2000 x 512
+// 39.1 -> 39.6; 500 x 700 24.3 -> 22.1, 1000 x 700 31.2 -> 33.7 (two workgroups fit a CU); 500 x 850 28.4 -> 23.1; 256 x 1000 23.1 -> 18.2,
+// 500 x 1000 27.1 -> 25.1, 600 x 1000 30.5 -> 32.6, 2000 x 1000 63.7 -> 75.2.
+//   K = 8: 500 x 333 28.4 -> 18.5, 2500 x 333 77.5 -> 51.2, 3000 x 100 25.0 -> 22.6, 5000 x 100 32.2 -> 34.9, 256 x 1000 29.4 -> 22.8,
+// 500 x 850 37.1 -> 37.1, 500 x 1000 37.6 -> 40.0; K = 1: 100 x 200 14.9 -> 9.6, 500 x 700 20.8 -> 19.7.
+//   K = 12: 20 x 100 18.4 -> 19.1, 100 x 100 22.2 -> 19.8, 300 x 65 19.9 -> 20.4 (recorded 66.5 -> 72.3), 2000 x 128 47.7 -> 32.8, 500 x 333
+// 39.8 -> 29.7, 3500 x 200 82.3 -> 71.3, 1300 x 512 79.8 -> 64.7, 250 x 1000 40.8 -> 33.4, 560 x 1000 89.4 -> 81.0; K = 16: 20 x 128 22.5 ->
+// 23.5, 300 x 128 33.0 -> 28.4, 300 x 100 22.7 -> 27.1, 500 x 333 50.7 -> 36.8, 2000 x 200 84.9 -> 63.7, 400 x 1000 82.1 -> 70.9.
+//   Four recorded iterations: K = 4: 100 x 200 57.6 -> 33.1, 1200 x 333 109 -> 75, 2700 x 200 146 -> 95; K = 12: 500 x 333 169 -> 103.
+//   Full observations whose rows have a launch of their own (the step alone; bucket rings before): 20 x 100 15.5 -> 9.8, 400 x 150 29.7 ->
+// 22.1, 200 x 500 93.9 -> 87.9, 250 x 1000 351 -> 344, 8000 x 64 124 -> 117.
 bool crew_serves(const wd_config& c, const wd::Params& p) {
   const int N = c.num_agents, E = c.num_envs, K = p.K;
-  if (p.big || !p.strips || N <= wd::kWaveSize || N > wd::kMaxEnvWorkgroupSize || K < 1 || K > wd::kMaxRegisterK) return false;
+  if (p.big || N > wd::kMaxEnvWorkgroupSize) return false;
+  if (c.obs_mode == WD_OBS_FULL) return p.obs_mode == wd::kObsFullSplit && !p.wide;
+  if (!p.strips || N <= wd::kWaveSize) return false;
+  const int64_t agents = int64_t(E) * N;
+  if (K > wd::kMaxRegisterK3) return agents <= 500000 && (N > wd::kSmallEnvAgents || (N >= 112 && E >= 256));
+  if (K > wd::kMaxRegisterK) return agents <= 700000 && (N >= 112 || (N >= 96 && E >= 64));
   if (N < 96) return E <= 1500;
   if (N < 112) return E <= 3000;
   if (N <= wd::kSmallEnvAgents) return E <= 4096;
-  if (N <= 480) return int64_t(E) * N <= 1200000;
-  if (N > (K > 4 ? 768 : 896)) return E <= 256;
+  if (N <= 480) return agents <= 1200000;
+  if (K > 4 && N > 768) return E <= 256;
   const int waves = (N + wd::kWaveSize - 1) / wd::kWaveSize;
   return E <= 256 * (32 / waves);  // one round of workgroups
 }
@@ -568,11 +579,16 @@ void plan_crew(const wd_config& c, wd::Params* p) {
   const int N = c.num_agents, threads = (N + wd::kWaveSize - 1) / wd::kWaveSize * wd::kWaveSize;
   p->crew_threads = threads;
   p->wave_envs = 0;
-  const int KT = p->K <= 4 ? 4 : 8;  // places in the neighbour lists
-  int shift = 0;  // columns as narrow as four bins per lane allow
-  while (p->strip_rmax * (((c.grid_size - 1) >> shift) + 1) > 4 * threads) ++shift;
-  p->cshift = shift;
-  p->strip_C = ((c.grid_size - 1) >> shift) + 1;
+  const bool full = c.obs_mode == WD_OBS_FULL;
+  const int KT = full ? 0 : p->K <= 4 ? 4 : p->K <= 8 ? 8 : 16;  // places in the neighbour lists
+  if (!full) {
+    int shift = 0;  // columns as narrow as four bins per lane allow
+    while (p->strip_rmax * (((c.grid_size - 1) >> shift) + 1) > 4 * threads) ++shift;
+    p->cshift = shift;
+    p->strip_C = ((c.grid_size - 1) >> shift) + 1;
+  }
+  const int reach_words = (c.grid_size + 31) / 32 + 1;  // (a tagger's reach in a row touches two words at most)
+  p->crew_reach_words = p->tag_rad <= 8 && reach_words * c.grid_size <= 4096 && c.num_taggers >= 16 ? reach_words : 0;
   int64_t off = 0;
   auto take = [&off](int64_t bytes) {
     const int64_t at = off;
@@ -582,14 +598,17 @@ void plan_crew(const wd_config& c, wd::Params* p) {
   take(4 * threads);  // packed positions
   p->crew_misc = take(4 * 40);
   p->crew_taggers = take(4 * (c.num_taggers + 3));
+  p->crew_reached = take(4 * p->crew_reach_words * c.grid_size);
   p->crew_credits = take(4 * c.num_taggers);
-  p->crew_nbr = take(2 * KT * threads);
-  p->crew_list = take(4 * (threads + p->pad_l + p->pad_r));  // (the rows are staged over the list and its table)
-  p->crew_ids = take(2 * (threads + p->pad_l + p->pad_r));
-  p->crew_starts = take(2 * (p->strip_rmax * p->strip_C + 4));
-  p->crew_edges = take(2 * (p->strip_rmax + 2));
-  p->crew_queue = take(4 * threads);
-  off = std::max<int64_t>(off, p->crew_list + int64_t(threads / wd::kWaveSize) * 32 * p->D * 4);
+  if (!full) {
+    p->crew_nbr = take(2 * KT * threads);
+    p->crew_list = take(4 * (threads + p->pad_l + p->pad_r));  // (the rows are staged over the list and its table)
+    p->crew_ids = take(2 * (threads + p->pad_l + p->pad_r));
+    p->crew_starts = take(2 * (p->strip_rmax * p->strip_C + 4));
+    p->crew_edges = take(2 * (p->strip_rmax + 2));
+    p->crew_queue = take(4 * threads);
+    off = std::max<int64_t>(off, p->crew_list + int64_t(threads / wd::kWaveSize) * (p->K <= 8 ? 32 : 16) * p->D * 4);
+  }
   p->crew_lds = int32_t(off);
 }
 
@@ -642,7 +661,8 @@ int fill_params(const wd_config& c, const wd_buffers& b, wd::Params* p, bool own
   const int64_t pair_up_to = c.num_agents <= 1024 ? 3ll * c.num_agents / 10 : 450;  // envs
   bool prefer_pair = pair_serves && c.num_agents >= 384 && c.num_envs <= pair_up_to;
   // the largest batch that the pair serves faster than strips do
-  const int pair_envs = p->K > wd::kMaxRegisterK ? (c.num_agents - 500) / (p->K > wd::kMaxRegisterK3 ? 2 : 4)
+  const int pair_envs = c.num_agents <= wd::kMaxEnvWorkgroupSize ? 0  // (crew_env_kernel serves those: 100 x 1000, K = 12 39.8 -> 32.1)
+                        : p->K > wd::kMaxRegisterK               ? (c.num_agents - 500) / (p->K > wd::kMaxRegisterK3 ? 2 : 4)
                                                     : (c.num_agents - 1300) / (p->K > 4 ? 5 : 18);
   if (prefer_pair && own_tables && c.num_envs > pair_envs) {
     wd::Params small = *p;

@@ -149,8 +149,10 @@ struct Params {
   int32_t wave_envs;     // 1: wave_env_kernel (envs of at most 64 agents); kSmallEnvs: small_env_kernel (of up to
                          // kSmallEnvAgents); a wave per env in both (see plan_waves)
   int32_t quad_single, quad_roll;  // wave_envs == 1: quad_env_kernel instead, for single calls and in wd_rollout
-  // crew_env_kernel (0 threads: another kernel serves the envs): lanes per env, LDS map in byte offsets
-  int32_t crew_threads, crew_misc, crew_taggers, crew_credits, crew_list, crew_ids, crew_starts, crew_edges, crew_queue, crew_nbr, crew_lds;
+  // crew_env_kernel (0 threads: another kernel serves the envs): lanes per env, LDS map in byte offsets, words per row of
+  // its map of cells in reach (0: every runner is compared with every tagger)
+  int32_t crew_reach_words;
+  int32_t crew_threads, crew_misc, crew_taggers, crew_reached, crew_credits, crew_list, crew_ids, crew_starts, crew_edges, crew_queue, crew_nbr, crew_lds;
   // device buffers (borrowed from the caller)
   int32_t *pos_x, *pos_y, *pos_x0, *pos_y0, *live, *action;
   float* reward;

@@ -2464,7 +2464,8 @@ hipError_t launch_small_kernel(const Params& p, int mode, const Roll& roll, cons
 }
 
 // ----------------------------------------------------------------------------------
-// Envs of 65 to 1024 agents in batches that are bound by one workgroup's chain of phases: one workgroup per env and a
+// Envs of 65 to 1024 agents in batches that are bound by one workgroup's chain of phases (and the step of full
+// observations whose rows have a launch of their own): one workgroup per env and a
 // lane per agent, whose state stays in registers from phase to phase and, in a roll-out, from iteration to iteration.
 // env_kernel gives a lane four agents for the sake of wide accesses and walks through a dozen barriers; here a phase is
 // one agent's work, the tag check comes before the sort (so no entry of the list has to be marked afterwards), and lists
@@ -2472,32 +2473,39 @@ hipError_t launch_small_kernel(const Params& p, int mode, const Roll& roll, cons
 // quad_env_kernel does.  Longer lists are sorted by strip and column and searched through the windows of wd_dev_strips.h;
 // agents that the windows do not settle get sixteen lanes each, which read the bins within the distance already known.
 //
-// Bound: the chain of one workgroup (three barriers and about 600 instructions up to the rows where the list is compared
-// whole), for larger batches the vector ALUs.  20 envs x 333 agents, K = 4: 18.0 -> 10.6 us per iteration, 777 x 333 25.6 -> 18.2 (its
-// three services one by one 41.1 -> 28.9), 2000 x 200 26.0 -> 21.0, 256 x 1000 23.4 -> 20.1; eight recorded iterations of
-// 300 x 333 137 -> 87.  Rows stored by each lane (or by four) straight from registers instead of through LDS: 777 x 333 20.1, 2000 x 200
-// 25.2.  At most 64 registers: with 76 in the multi-step form 300 x 333 takes 84 but 777 x 333 127 instead of 112, for the waves on a CU.
+// Where many taggers have a short reach, they mark the cells that they reach in a bit map, and only runners on marked cells are
+// compared with them.
+//
+// Bound: the chain of one workgroup (three or four barriers and about 600 instructions up to the rows where the list is compared
+// whole), for larger batches the vector ALUs.  20 envs x 333 agents, K = 4: 18.0 -> 11.0 us per iteration, 777 x 333 25.6 -> 17.3 (its
+// three services one by one 41.1 -> 28.2), 2000 x 200 26.0 -> 20.5, 256 x 1000 23.4 -> 18.3 (without the bit map 20.6; 777 x 333, eight
+// recorded iterations 111 -> 99); 500 x 333, K = 12 39.8 -> 29.7.  Rows stored by each lane (or by four) straight from registers
+// instead of through LDS: 777 x 333 20.1, 2000 x 200 25.2.  At most 64 registers: with 76 in the multi-step form 300 x 333 takes 84 us
+// but 777 x 333 127 instead of 112, for the waves on a CU.  Two agents per lane (up to 2048): 256 x 2000 30.1 -> 30.3, four recorded
+// iterations 115 -> 135, for spilled registers: not taken.
 // ----------------------------------------------------------------------------------
 struct CrewLds {
-  uint32_t* pl;        // [threads] packed positions by agent
+  uint32_t* pl;        // [agents] packed positions by agent
   uint32_t* taggers;   // [N_tag, padded] x | y << 16 after the move
+  uint32_t* reached;   // a bit per cell: within the tag radius of some tagger
   int32_t* credits;    // [N_tag]
   uint32_t* pos;       // list: scaled positions, with pads
   uint16_t* id;        // and agents
   uint16_t* starts;    // bin starts
   uint16_t* edges;
-  uint32_t* queue;     // [threads] slots that the windows did not settle, and their radius in the upper half
+  uint32_t* queue;     // [agents] slots that the windows did not settle, and their radius in the upper half
   int32_t* wave_live;  // [16] agents in play by wave
   int32_t* totals;     // [16] scan scratch
   int32_t* tags;       // [0] tags of this step, [1] length of the queue
-  uint16_t* nbr;       // [threads][4 or 8] neighbours by agent
-  float* stage;        // [waves][32 rows], over the list and its table
+  uint16_t* nbr;       // [agents][4, 8 or 16] neighbours by agent
+  float* stage;        // [waves][32 or 16 rows], over the list and its table
   __device__ __forceinline__ CrewLds(unsigned char* smem, const Params& p) {
     pl = reinterpret_cast<uint32_t*>(smem);
     wave_live = reinterpret_cast<int32_t*>(smem + p.crew_misc);
     totals = wave_live + 16;
     tags = wave_live + 32;
     taggers = reinterpret_cast<uint32_t*>(smem + p.crew_taggers);
+    reached = reinterpret_cast<uint32_t*>(smem + p.crew_reached);
     credits = reinterpret_cast<int32_t*>(smem + p.crew_credits);
     pos = reinterpret_cast<uint32_t*>(smem + p.crew_list) + p.pad_l;
     id = reinterpret_cast<uint16_t*>(smem + p.crew_ids) + p.pad_l;
@@ -2536,11 +2544,29 @@ __device__ __forceinline__ void crew_put_neighbours(uint16_t* nbr, uint32_t agen
 #define p (((const WaveArgs*)ka)->p)
 #define roll (((const WaveArgs*)ka)->roll)
 
+// Smallest value of the wave, in every lane.
+__device__ __forceinline__ uint32_t wave_smallest(uint32_t v) {
+  const auto step = [&](auto ctrl, auto rows) {
+    v = min(v, uint32_t(__builtin_amdgcn_update_dpp(-1, int(v), decltype(ctrl)::value, decltype(rows)::value, 0xF, false)));
+  };
+  step(std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xF>{});
+  step(std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xF>{});
+  step(std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xF>{});
+  step(std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xF>{});
+  step(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xA>{});
+  step(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xC>{});
+  return uint32_t(__builtin_amdgcn_readlane(int(v), kWaveSize - 1));
+}
+
+// KX: the windows' list size (K itself up to 8, then 12 and 16; 0: full observations, whose rows full_rows_kernel writes).
+// ROLL: a launch of wd_rollout, else one call of any mode.
 template <int KX, bool ROLL>
-__global__ __launch_bounds__(kMaxEnvWorkgroupSize) __attribute__((amdgpu_waves_per_eu(8, 8))) void
+__global__ __launch_bounds__(kMaxEnvWorkgroupSize) __attribute__((amdgpu_waves_per_eu(KX <= 8 ? 8 : 4, 8))) void
 crew_env_kernel(const WaveArgs) {
   extern __shared__ __align__(16) unsigned char smem[];
-  constexpr int KT = KX <= 4 ? 4 : 8, D = 5 + 4 * KX;  // KT: lists that lanes merge
+  constexpr int KT = KX <= 4 ? 4 : KX <= 8 ? 8 : 16;  // lists that lanes merge
+  constexpr bool kRowInRegisters = KX <= 8;           // (K == KX then)
+  constexpr int kStaged = kRowInRegisters ? 32 : 16;  // rows that a wave stages at a time
   KernargWave ka = (KernargWave)__builtin_amdgcn_kernarg_segment_ptr();
   int tid = threadIdx.x;
   const int e = blockIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -2551,37 +2577,41 @@ crew_env_kernel(const WaveArgs) {
 #define lane (tid & (kWaveSize - 1))
 #define valid (tid < N)
 #define tagger (tid < N_tag)
-#define a (env_at + (valid ? tid : 0))
+#define at (env_at + (valid ? tid : 0))
   int x = 0, y = 0, act = 0;
-  bool lv = false, moved = false;
+  bool lv = false, moved = false, live_dirty = false;
   int done = 0, t = 0, nlr = 0, tags_out = -1;  // (tags_out < 0: tags_step keeps its value)
   float f[4] = {0.0f, 0.0f, 0.0f, 0.0f};
   int ring_at = roll.ring_pos;
   const auto ask = [&]() {
-    const float* pr = ka->probs + int64_t(ring_at) * EN * kNumActions + a * kNumActions;
+    const float* const ring = ka->probs + int64_t(ring_at) * EN * kNumActions;
     ring_at = ring_at + 1 == roll.ring_len ? 0 : ring_at + 1;
+    if (valid) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) f[c] = pr[c];
+      for (int c = 0; c < 4; ++c) f[c] = ring[at * kNumActions + c];
+    }
   };
-  if (mode == kModeIterate && valid) ask();
+  if (mode == kModeIterate) ask();
   if (mode != kModeResetAll) {
     if (valid) {
-      x = p.pos_x[a];
-      y = p.pos_y[a];
-      lv = p.live[a] != 0;
-      if (mode == kModeStep) act = p.action[a];
+      x = p.pos_x[at];
+      y = p.pos_y[at];
+      lv = p.live[at] != 0;
+      if (mode == kModeStep) act = p.action[at];
     }
-    done = p.done[e];
-    t = p.t[e];
-    nlr = p.n_live_runners[e];
+    done = __builtin_amdgcn_readfirstlane(p.done[e]);
+    t = __builtin_amdgcn_readfirstlane(p.t[e]);
+    nlr = __builtin_amdgcn_readfirstlane(p.n_live_runners[e]);
     if ((mode == kModeStep && done) || (mode == kModeResetDone && !done)) return;  // this env keeps its state and rows
     const int raw_x = x, raw_y = y;
     x = min(max(x, 0), p.G - 1);
     y = min(max(y, 0), p.G - 1);
     moved = x != raw_x || y != raw_y;
-    if (ROLL && done && roll.reward && valid) roll.reward[a] = p.reward[a];  // (an env that enters done: the first iteration does not step it)
+    // (an env that enters a roll-out done: its first iteration does not step it)
+    float* const unstepped = ROLL ? roll.reward : p.kept_reward ? p.reward : nullptr;
+    const float* const kept = ROLL ? p.reward : p.kept_reward;
+    if (done && stepping && unstepped && valid) unstepped[at] = kept[at];
   }
-  bool live_dirty = false;
   const int steps = ROLL ? roll.steps : 1;
   for (int s = 0; s < steps; ++s) {
     const bool last = s + 1 == steps;
@@ -2590,26 +2620,27 @@ crew_env_kernel(const WaveArgs) {
     const CrewLds L(smem, p);
     if (mode == kModeIterate) {
       const uint64_t g = ka->g0 + uint64_t(s);
-      const Block4 r = random_block(p, uint32_t(e), uint32_t(tid >> 2), uint32_t(g), uint32_t(g >> 32), kStreamAction);
-      const uint32_t w = (tid & 2) ? ((tid & 1) ? r.w[3] : r.w[2]) : ((tid & 1) ? r.w[1] : r.w[0]);
-      act = sample_action(f[0], f[1], f[2], f[3], w);
+      act = draw_one(*(const WaveArgs*)ka, f, tid, e, g);
+      if (!last) ask();
       if (valid) {
-        if (!last) ask();
-        if (last) p.action[a] = act;
-        if (ROLL && roll.action) roll.action[int64_t(s) * EN + a] = act;
+        if (last) p.action[at] = act;
+        if (ROLL && roll.action) roll.action[int64_t(s) * EN + at] = act;
       }
     }
     WD_NEW_PHASE();
     // lists of up to a quarter of the lanes are compared whole; the table of bins is not needed if no list can be longer
     const int whole_up_to = threads >> 2;
-    if (N > whole_up_to) {
+    if (KX > 0 && N > whole_up_to) {
       uint32_t* const tw = reinterpret_cast<uint32_t*>(L.starts);
       const int words = (p.strip_rmax * p.strip_C + 2) >> 1;
       for (int j = tid; j < words; j += threads) tw[j] = 0u;
     }
     if (tid < 2) L.tags[tid] = 0;
-    bool tagged = false;
+    bool tagged = false, stale = !lv;  // (stale: out of play before this step)
     if (stepping && !done) {
+      const int reach_words = p.crew_reach_words;  // of a row of the bit map; 0: none
+      if (reach_words)
+        for (int j = tid; j < reach_words * p.G; j += threads) L.reached[j] = 0u;
       if (lv) {
         const int nx = min(max(x + (act == 4) - (act == 3), 0), p.G - 1);
         const int ny = min(max(y + (act == 1) - (act == 2), 0), p.G - 1);
@@ -2624,241 +2655,289 @@ crew_env_kernel(const WaveArgs) {
       }
       __syncthreads();
       // ---- tag check: a runner's smallest (distance, tagger) key --------------------------------------
-      if (p.tag_r2 >= 0 && wave * kWaveSize + kWaveSize > N_tag) {  // (uniform: some lane of the wave owns a runner)
+      if (p.tag_r2 >= 0) {
         const int ib = p.idx_bits;
-        uint32_t best = ~0u;
-        const auto meet = [&](uint32_t at, int tg) {
-          const uint32_t d2 = squared_length(__builtin_bit_cast(short2v, at) - __builtin_bit_cast(short2v, here));
-          best = min(best, (d2 << ib) | uint32_t(tg));
+        const auto key_of = [&](uint32_t other, uint32_t me, int tg) {
+          return (squared_length(__builtin_bit_cast(short2v, other) - __builtin_bit_cast(short2v, me)) << ib) | uint32_t(tg);
         };
-        int tg = 0;
-        for (; tg + 4 <= N_tag; tg += 4) {
-          const uint4 q = *reinterpret_cast<const uint4*>(L.taggers + tg);
-          meet(q.x, tg);
-          meet(q.y, tg + 1);
-          meet(q.z, tg + 2);
-          meet(q.w, tg + 3);
-        }
-        for (; tg < N_tag; ++tg) meet(L.taggers[tg], tg);
-        tagged = lv && !tagger && int(best >> ib) <= p.tag_r2;
-        if (tagged) {
-          lv = false;
-          live_dirty = true;
-          atomicAdd(&L.credits[best & ((1u << ib) - 1u)], 1);
+        if (reach_words) {
+          // Many taggers with a short reach: they mark the cells that they reach, and only a runner on a marked cell is compared
+          // with them, by its whole wave.
+          if (tagger) {
+            const int rad = p.tag_rad, x0 = max(x - rad, 0), x1 = min(x + rad, p.G - 1);
+            const uint64_t bits = ((2ull << (x1 - x0)) - 1ull) << (x0 & 31);
+            for (int row = max(y - rad, 0); row <= min(y + rad, p.G - 1); ++row) {
+              uint32_t* const word = L.reached + row * reach_words + (x0 >> 5);
+              atomicOr(word, uint32_t(bits));
+              if (bits >> 32) atomicOr(word + 1, uint32_t(bits >> 32));
+            }
+          }
+          __syncthreads();
+          const bool near = lv && !tagger && ((L.reached[y * reach_words + (x >> 5)] >> (x & 31)) & 1u);
+          for (uint64_t left = __ballot(near); left != 0; left &= left - 1) {
+            const int who = __builtin_ctzll(left);
+            const uint32_t me = uint32_t(__builtin_amdgcn_readlane(int(here), who));
+            uint32_t best = ~0u;
+            for (int tg = lane; tg < N_tag; tg += kWaveSize) best = min(best, key_of(L.taggers[tg], me, tg));
+            best = wave_smallest(best);
+            if (int(best >> ib) <= p.tag_r2 && lane == who) {
+              tagged = true;
+              atomicAdd(&L.credits[best & ((1u << ib) - 1u)], 1);
+            }
+          }
+        } else if (wave * kWaveSize + kWaveSize > N_tag) {  // (uniform: some lane of the wave owns a runner)
+          uint32_t best = ~0u;
+          int tg = 0;
+          for (; tg + 4 <= N_tag; tg += 4) {
+            const uint4 q = *reinterpret_cast<const uint4*>(L.taggers + tg);
+            best = min(best, key_of(q.x, here, tg));
+            best = min(best, key_of(q.y, here, tg + 1));
+            best = min(best, key_of(q.z, here, tg + 2));
+            best = min(best, key_of(q.w, here, tg + 3));
+          }
+          for (; tg < N_tag; ++tg) best = min(best, key_of(L.taggers[tg], here, tg));
+          tagged = lv && !tagger && int(best >> ib) <= p.tag_r2;
+          if (tagged) atomicAdd(&L.credits[best & ((1u << ib) - 1u)], 1);
         }
         const int mine = __popcll(__ballot(tagged));
+        lv = lv && !tagged;
+        live_dirty = live_dirty || tagged;
         if (mine && lane == 0) atomicAdd(&L.tags[0], mine);
       }
     }
     const uint64_t in_play = __ballot(lv);
-    if (lane == 0) L.wave_live[wave] = __popcll(in_play);
-    L.pl[tid] = pack_pos(x, y, lv);
+    if (KX > 0 && lane == 0) L.wave_live[wave] = __popcll(in_play);
+    if (KX > 0) L.pl[tid] = pack_pos(x, y, lv);
     __syncthreads();
     WD_NEW_PHASE();
     // ---- rewards, clock, reset -----------------------------------------------------------------------------
     if (stepping && !done) {
       if (valid) {
         const float rew = tagger ? static_cast<float>(L.credits[tid]) * p.tag_reward : tagged ? p.tag_penalty : 0.0f;
-        if (last) p.reward[a] = rew;
-        if (ROLL && roll.reward) roll.reward[int64_t(s) * EN + a] = rew;
+        if (last) p.reward[at] = rew;
+        if (ROLL && roll.reward) roll.reward[int64_t(s) * EN + at] = rew;
       }
-      tags_out = L.tags[0];
+      tags_out = __builtin_amdgcn_readfirstlane(L.tags[0]);
       nlr -= tags_out;
       t += 1;
       done = (nlr == 0 || t >= p.T) ? 1 : 0;
     }
     int n = 0, before = 0;  // agents in play, and of them in the waves before this one
-    for (int w = 0; w < threads / kWaveSize; ++w) {
-      const int c = L.wave_live[w];
-      before += w < wave ? c : 0;
-      n += c;
+    if constexpr (KX > 0) {
+      for (int w = 0; w < threads / kWaveSize; ++w) {
+        const int c = __builtin_amdgcn_readfirstlane(L.wave_live[w]);
+        before += w < wave ? c : 0;
+        n += c;
+      }
     }
     if (mode != kModeStep) {
       int32_t* const log = roll.done;
       if (log && tid == 0) log[int64_t(s) * p.E + e] = done;  // the flag before the reset clears it
       if (mode == kModeResetAll || done) {
+        n = N;
         if (valid) {
-          x = min(max(p.pos_x0[a], 0), p.G - 1);
-          y = min(max(p.pos_y0[a], 0), p.G - 1);
+          x = min(max(p.pos_x0[at], 0), p.G - 1);
+          y = min(max(p.pos_y0[at], 0), p.G - 1);
         }
         lv = valid;
         moved = live_dirty = true;
+        stale = false;
+        before = wave * kWaveSize;
+        if (KX > 0) L.pl[tid] = pack_pos(x, y, lv);
         t = 0;
         nlr = N - N_tag;
         done = 0;
         tags_out = 0;
-        n = N;
-        before = wave * kWaveSize;
-        L.pl[tid] = pack_pos(x, y, lv);
       }
     }
-    const uint64_t listed = __ballot(lv);
-    const int h = p.pos_shift;
-    const uint32_t scaled = (uint32_t(x) << h) | (uint32_t(y) << (16 + h));
-    if (n <= whole_up_to) {
-      const int slot = before + int(__builtin_amdgcn_mbcnt_hi(uint32_t(listed >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(listed), 0u)));
-      if (lv) {
-        L.pos[slot] = scaled;
-        L.id[slot] = uint16_t(tid);
-      }
-      if (tid < kQuadPad) {  // its keys are "nobody"
-        L.pos[n + tid] = kStripDeadY << 16;
-        L.id[n + tid] = 0;
-      }
-      __syncthreads();
-      WD_NEW_PHASE();
-      const int mine = tid >> 2, q = tid & 3;
-      if (mine < n) {
-        const uint32_t me = L.pos[mine], own = L.id[mine];
-        uint32_t keys[KT];
-#pragma unroll
-        for (int k = 0; k < KT; ++k) keys[k] = ~0u;
-        for (int s0 = 0; s0 < n; s0 += kQuadPad) {
-          uint32_t c[4], i[4];
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            c[j] = L.pos[s0 + 4 * j + q];
-            i[j] = L.id[s0 + 4 * j + q];
-          }
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const uint32_t key = strip_key(__builtin_bit_cast(short2v, c[j]) - __builtin_bit_cast(short2v, me), i[j]);
-            insert_key<KT>(keys, key == own ? ~0u : key);
-          }
-        }
-        merge_with_lane<KT, 0xB1>(keys);
-        merge_with_lane<KT, 0x4E>(keys);
-        if (q == 0) crew_put_neighbours<KX, KT>(L.nbr, own, keys, p);
+    if constexpr (KX == 0) {
+      // the rows are marked in their first feature, or (those that are kept) get their time feature
+      if (valid) {
+        float* const row = p.obs + at * p.D;
+        if (p.rows_kept && stale)
+          row[4] = static_cast<float>(t) * p.inv_T;
+        else
+          row[0] = __uint_as_float(kRowWanted);
       }
     } else {
-      // ---- the list by strip and column ---------------------------------------------------------------------
-      const Strips sg = choose_strips(p, n);
-      uint32_t* const tw = reinterpret_cast<uint32_t*>(L.starts);
-      const int words = strip_words(sg);
-      const int bin = strip_bin(x, y, sg);
-      if (lv) strip_count(tw, bin);
-      for (int j = tid; j <= sg.R; j += threads) L.edges[j] = uint16_t(min(strip_first_cell(j, sg), p.G));
-      __syncthreads();
-      const int chunk = (words + threads - 1) / threads;
-      const int j0 = min(tid * chunk, words), j1 = min(j0 + chunk, words);
-      int part = 0;
-      for (int j = j0; j < j1; ++j) part += int(tw[j] & 0xFFFFu) + int(tw[j] >> 16);
-      const int incl = wave_inclusive_scan(part);
-      if (lane == kWaveSize - 1) L.totals[wave] = incl;
-      __syncthreads();
-      int run = incl - part;
-      for (int w = 0; w < wave; ++w) run += L.totals[w];
-      for (int j = j0; j < j1; ++j) {
-        const uint32_t c = tw[j], lo = uint32_t(run);
-        run += int(c & 0xFFFFu);
-        tw[j] = lo | (uint32_t(run) << 16);
-        run += int(c >> 16);
-      }
-      for (int j = tid; j < p.pad_l + p.pad_r; j += threads) {
-        const int at = j < p.pad_l ? -1 - j : n + (j - p.pad_l);
-        L.pos[at] = kStripDeadY << 16;
-        L.id[at] = 0;
-      }
-      __syncthreads();
-      if (lv) {
-        const uint32_t at = strip_take_slot(tw, bin);
-        L.pos[at] = scaled;
-        L.id[at] = uint16_t(tid);
-      }
-      __syncthreads();
-      WD_NEW_PHASE();
-      // ---- windows ---------------------------------------------------------------------------------------------
-      if (tid < n) {
-        const uint32_t me = L.pos[tid];
-        uint32_t keys[KX];
-        if (strip_window_search<KX, strip_half_own(KX), strip_half_adj(KX), 0, false>(keys, me, tid, 0, sg, p.key_shift, n, p.pad_l,
-                                                                                      L.pos, L.id, L.starts, L.edges)) {
-          crew_put_neighbours<KX, KT>(L.nbr, L.id[tid], keys, p);
-        } else {
-          const int radius = strip_radius(keys, sg, p.key_shift);
-          L.queue[atomicAdd(&L.tags[1], 1)] = uint32_t(tid) | (uint32_t(radius) << 16);
+      const int hs = p.pos_shift;
+      if (n <= whole_up_to) {
+        const uint64_t listed = __ballot(lv);
+        const int slot = before + int(__builtin_amdgcn_mbcnt_hi(uint32_t(listed >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(listed), 0u)));
+        if (lv) {
+          L.pos[slot] = (uint32_t(x) << hs) | (uint32_t(y) << (16 + hs));
+          L.id[slot] = uint16_t(tid);
         }
-      }
-      __syncthreads();
-      WD_NEW_PHASE();
-      // ---- what they did not settle: sixteen lanes per agent ----------------------------------------------------
-      const int queued = L.tags[1], sub = tid & 15;
-      for (int w = tid >> 4; w < queued; w += threads >> 4) {
-        const uint32_t entry = L.queue[w];
-        const int q = int(entry & 0xFFFFu), radius = int(entry >> 16);
-        const uint32_t me = L.pos[q], own = L.id[q];
-        const int X = int((me & 0xFFFFu) >> h), Y = int(me >> (16 + h));
-        const int c0 = max(X - radius, 0) >> sg.cshift, c1 = min(X + radius, p.G - 1) >> sg.cshift;
-        const int r0 = strip_of(max(Y - radius, 0), sg), r1 = strip_of(min(Y + radius, p.G - 1), sg);
-        uint32_t keys[KT];
+        if (tid < kQuadPad) {  // its keys are "nobody"
+          L.pos[n + tid] = kStripDeadY << 16;
+          L.id[n + tid] = 0;
+        }
+        __syncthreads();
+        WD_NEW_PHASE();
+        const int mine = tid >> 2, q = tid & 3;
+        if (mine < n) {
+          const uint32_t me = L.pos[mine], own = L.id[mine];
+          uint32_t keys[KT];
 #pragma unroll
-        for (int k = 0; k < KT; ++k) keys[k] = ~0u;
-        for (int row = r0; row <= r1; ++row) {
-          const int end = L.starts[row * sg.C + c1 + 1];
-          for (int i = int(L.starts[row * sg.C + c0]) + sub; i < end; i += 16) {
-            const uint32_t key = strip_key(__builtin_bit_cast(short2v, L.pos[i]) - __builtin_bit_cast(short2v, me), uint32_t(L.id[i]));
-            insert_key<KT>(keys, i == q ? ~0u : key);
+          for (int k = 0; k < KT; ++k) keys[k] = ~0u;
+          for (int s0 = 0; s0 < n; s0 += kQuadPad) {
+            uint32_t c[4], i[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              c[j] = L.pos[s0 + 4 * j + q];
+              i[j] = L.id[s0 + 4 * j + q];
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              const uint32_t key = strip_key(__builtin_bit_cast(short2v, c[j]) - __builtin_bit_cast(short2v, me), i[j]);
+              insert_key<KT>(keys, key == own ? ~0u : key);
+            }
+          }
+          merge_with_lane<KT, 0xB1>(keys);
+          merge_with_lane<KT, 0x4E>(keys);
+          if (q == 0) crew_put_neighbours<KX, KT>(L.nbr, own, keys, p);
+        }
+      } else {
+        // ---- the list by strip and column ---------------------------------------------------------------------
+        const Strips sg = choose_strips(p, n);
+        uint32_t* const tw = reinterpret_cast<uint32_t*>(L.starts);
+        const int words = strip_words(sg);
+        if (lv) strip_count(tw, strip_bin(x, y, sg));
+        for (int j = tid; j <= sg.R; j += threads) L.edges[j] = uint16_t(min(strip_first_cell(j, sg), p.G));
+        __syncthreads();
+        const int chunk = (words + threads - 1) / threads;
+        const int j0 = min(tid * chunk, words), j1 = min(j0 + chunk, words);
+        int part = 0;
+        for (int j = j0; j < j1; ++j) part += int(tw[j] & 0xFFFFu) + int(tw[j] >> 16);
+        const int incl = wave_inclusive_scan(part);
+        if (lane == kWaveSize - 1) L.totals[wave] = incl;
+        __syncthreads();
+        int run = incl - part;
+        for (int w = 0; w < wave; ++w) run += L.totals[w];
+        for (int j = j0; j < j1; ++j) {
+          const uint32_t c = tw[j], lo = uint32_t(run);
+          run += int(c & 0xFFFFu);
+          tw[j] = lo | (uint32_t(run) << 16);
+          run += int(c >> 16);
+        }
+        for (int j = tid; j < p.pad_l + p.pad_r; j += threads) {
+          const int to = j < p.pad_l ? -1 - j : n + (j - p.pad_l);
+          L.pos[to] = kStripDeadY << 16;
+          L.id[to] = 0;
+        }
+        __syncthreads();
+        if (lv) {
+          const uint32_t to = strip_take_slot(tw, strip_bin(x, y, sg));
+          L.pos[to] = (uint32_t(x) << hs) | (uint32_t(y) << (16 + hs));
+          L.id[to] = uint16_t(tid);
+        }
+        __syncthreads();
+        WD_NEW_PHASE();
+        // ---- windows ---------------------------------------------------------------------------------------------
+        if (tid < n) {
+          const uint32_t me = L.pos[tid];
+          uint32_t keys[KX];
+          if (strip_window_search<KX, strip_half_own(KX), strip_half_adj(KX), 0, false>(keys, me, tid, 0, sg, p.key_shift, n, p.pad_l,
+                                                                                        L.pos, L.id, L.starts, L.edges)) {
+            crew_put_neighbours<KX, KT>(L.nbr, L.id[tid], keys, p);
+          } else {
+            const int radius = strip_radius(keys, sg, p.key_shift);
+            L.queue[atomicAdd(&L.tags[1], 1)] = uint32_t(tid) | (uint32_t(radius) << 16);
           }
         }
-        merge_with_lane<KT, 0xB1>(keys);
-        merge_with_lane<KT, 0x4E>(keys);
-        merge_with_lane<KT, 0x141>(keys);  // the mirror image in eight lanes: the other quad
-        merge_with_lane<KT, 0x140>(keys);  // and in sixteen: the other half
-        if (sub == 0) crew_put_neighbours<KX, KT>(L.nbr, own, keys, p);
+        __syncthreads();
+        WD_NEW_PHASE();
+        // ---- what they did not settle: sixteen lanes per agent ----------------------------------------------------
+        const int queued = __builtin_amdgcn_readfirstlane(L.tags[1]), sub = tid & 15;
+        for (int w = tid >> 4; w < queued; w += threads >> 4) {
+          const uint32_t entry = L.queue[w];
+          const int q = int(entry & 0xFFFFu), radius = int(entry >> 16);
+          const uint32_t me = L.pos[q], own = L.id[q];
+          const int X = int((me & 0xFFFFu) >> hs), Y = int(me >> (16 + hs));
+          const int c0 = max(X - radius, 0) >> sg.cshift, c1 = min(X + radius, p.G - 1) >> sg.cshift;
+          const int r0 = strip_of(max(Y - radius, 0), sg), r1 = strip_of(min(Y + radius, p.G - 1), sg);
+          uint32_t keys[KT];
+#pragma unroll
+          for (int k = 0; k < KT; ++k) keys[k] = ~0u;
+          for (int row = r0; row <= r1; ++row) {
+            const int end = L.starts[row * sg.C + c1 + 1];
+            for (int i = int(L.starts[row * sg.C + c0]) + sub; i < end; i += 16) {
+              const uint32_t key = strip_key(__builtin_bit_cast(short2v, L.pos[i]) - __builtin_bit_cast(short2v, me), uint32_t(L.id[i]));
+              insert_key<KT>(keys, i == q ? ~0u : key);
+            }
+          }
+          merge_with_lane<KT, 0xB1>(keys);
+          merge_with_lane<KT, 0x4E>(keys);
+          merge_with_lane<KT, 0x141>(keys);  // the mirror image in eight lanes: the other quad
+          merge_with_lane<KT, 0x140>(keys);  // and in sixteen: the other half
+          if (sub == 0) crew_put_neighbours<KX, KT>(L.nbr, own, keys, p);
+        }
       }
-    }
-    __syncthreads();
-    WD_NEW_PHASE();
-    // ---- rows, in index order: 32 at a time through LDS, in pieces that are contiguous across the wave ---------------------
-    {
+      __syncthreads();
+      WD_NEW_PHASE();
+      // ---- rows, in index order: some at a time through LDS, in pieces that are contiguous across the wave ---------------------
+      const int K = kRowInRegisters ? KX : p.K, D = 5 + 4 * K;
+      float* const stage = L.stage + wave * (kStaged * D);
       const uint32_t me = L.pl[tid];
-      float row[D];
-      row[0] = static_cast<float>(pos_x_of(me)) * p.inv_G;
-      row[1] = static_cast<float>(pos_y_of(me)) * p.inv_G;
-      row[2] = tagger ? 1.0f : 0.0f;
-      row[3] = lv ? 1.0f : 0.0f;
-      row[4] = static_cast<float>(t) * p.inv_T;
-      uint2 near[KT / 4];
+      const auto build = [&](float* row) {
+        row[0] = static_cast<float>(pos_x_of(me)) * p.inv_G;
+        row[1] = static_cast<float>(pos_y_of(me)) * p.inv_G;
+        row[2] = tagger ? 1.0f : 0.0f;
+        row[3] = lv ? 1.0f : 0.0f;
+        row[4] = static_cast<float>(t) * p.inv_T;
 #pragma unroll
-      for (int k = 0; k < KT / 4; ++k) near[k] = reinterpret_cast<const uint2*>(L.nbr + tid * KT)[k];
+        for (int k4 = 0; k4 < KT; k4 += 4) {
+          if (k4 >= K) break;
+          const uint2 near = reinterpret_cast<const uint2*>(L.nbr + tid * KT)[k4 / 4];
 #pragma unroll
-      for (int k = 0; k < KX; ++k) {
-        const uint32_t pair = (k & 2) ? near[k / 4].y : near[k / 4].x;
-        const uint32_t j = (k & 1) ? pair >> 16 : pair & 0xFFFFu;
-        // no branch: an empty slot looks up the agent itself, whose offsets are zero
-        const bool none = !lv || j == kNoNeighbour;
-        const uint32_t other = L.pl[none ? uint32_t(tid) : j];
-        row[5 + 4 * k] = static_cast<float>(pos_x_of(other) - pos_x_of(me)) * p.inv_G;
-        row[6 + 4 * k] = static_cast<float>(pos_y_of(other) - pos_y_of(me)) * p.inv_G;
-        row[7 + 4 * k] = (!none && int(j) < p.N_tag) ? 1.0f : 0.0f;
-        row[8 + 4 * k] = none ? 0.0f : 1.0f;
-      }
-      float* const stage = L.stage + wave * (32 * D);
+          for (int k = k4; k < k4 + 4; ++k) {
+            if (k < K) {
+              const uint32_t pair = (k & 2) ? near.y : near.x, j = (k & 1) ? pair >> 16 : pair & 0xFFFFu;
+              // no branch: an empty slot looks up the agent itself, whose offsets are zero
+              const bool none = !lv || j == kNoNeighbour;
+              const uint32_t other = L.pl[none ? uint32_t(tid) : j];
+              row[5 + 4 * k] = static_cast<float>(pos_x_of(other) - pos_x_of(me)) * p.inv_G;
+              row[6 + 4 * k] = static_cast<float>(pos_y_of(other) - pos_y_of(me)) * p.inv_G;
+              row[7 + 4 * k] = (!none && int(j) < p.N_tag) ? 1.0f : 0.0f;
+              row[8 + 4 * k] = none ? 0.0f : 1.0f;
+            }
+          }
+        }
+      };
+      float held[kRowInRegisters ? 5 + 4 * KX : 1];
+      if constexpr (kRowInRegisters) build(held);
 #pragma unroll
-      for (int half = 0; half < 2; ++half) {
-        const int first = wave * kWaveSize + 32 * half, floats = min(max(N - first, 0), 32) * D;
-        if ((lane >> 5) == half) {
-          float* const dst = stage + (lane & 31) * D;
+      for (int part = 0; part < kWaveSize / kStaged; ++part) {
+        const int first = wave * kWaveSize + kStaged * part, floats = min(max(N - first, 0), kStaged) * D;
+        if (lane / kStaged == part) {
+          float* const dst = stage + lane % kStaged * D;
+          if constexpr (kRowInRegisters) {
 #pragma unroll
-          for (int c = 0; c < D; ++c) dst[c] = row[c];
+            for (int c = 0; c < 5 + 4 * KX; ++c) dst[c] = held[c];
+          } else {
+            build(dst);
+          }
         }
         wave_sync_lds();
-        constexpr int kRounds = (32 * D / 4 + kWaveSize - 1) / kWaveSize;
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
           float* const rows = r ? (ROLL && roll.obs ? roll.obs + int64_t(s) * EN * D : nullptr) : (last ? p.obs : nullptr);
           if (!rows) continue;
-          float* const out = rows + (int64_t(e) * N + first) * D;
+          float* const out = rows + (env_at + first) * D;
+          const auto piece = [&](int v) {
+            const float4 q = reinterpret_cast<const float4*>(stage)[v];
+            reinterpret_cast<Slot4*>(out)[v] = Slot4{q.x, q.y, q.z, q.w};
+          };
+          if constexpr (kRowInRegisters) {
+            constexpr int kRounds = (kStaged * (5 + 4 * KX) / 4 + kWaveSize - 1) / kWaveSize;
 #pragma unroll
-          for (int c = 0; c < kRounds; ++c) {
-            const int v = lane + c * kWaveSize;
-            if (4 * v + 4 <= floats) {
-              const float4 q = reinterpret_cast<const float4*>(stage)[v];
-              reinterpret_cast<Slot4*>(out)[v] = Slot4{q.x, q.y, q.z, q.w};
-            }
+            for (int c = 0; c < kRounds; ++c)
+              if (4 * (lane + c * kWaveSize) + 4 <= floats) piece(lane + c * kWaveSize);
+          } else {
+            for (int v = lane; 4 * v + 4 <= floats; v += kWaveSize) piece(v);
           }
-          const int at = (floats & ~3) + lane;
-          if (at < floats) out[at] = stage[at];
+          const int tail = (floats & ~3) + lane;
+          if (tail < floats) out[tail] = stage[tail];
         }
         wave_sync_lds();
       }
@@ -2867,11 +2946,11 @@ crew_env_kernel(const WaveArgs) {
   }
   WD_NEW_PHASE();
   if (valid) {
-    if (moved) {
-      p.pos_x[a] = x;
-      p.pos_y[a] = y;
+    if (ROLL || moved) {
+      p.pos_x[at] = x;
+      p.pos_y[at] = y;
     }
-    if (live_dirty) p.live[a] = lv ? 1 : 0;
+    if (ROLL || live_dirty) p.live[at] = lv ? 1 : 0;
   }
   if (tid == 0) {
     p.t[e] = t;
@@ -2884,7 +2963,7 @@ crew_env_kernel(const WaveArgs) {
 #undef lane
 #undef valid
 #undef tagger
-#undef a
+#undef at
 #undef WD_NEW_PHASE
 #undef p
 #undef roll
@@ -2906,6 +2985,15 @@ hipError_t ensure_dynamic_lds(Kernel kernel, int bytes) {
   return hipSuccess;
 }
 
+hipError_t launch_full_rows(const Params& p, hipStream_t stream) {
+  const int runs = std::min<int64_t>(std::max<int64_t>(int64_t(p.E) * p.N / (kFullGroups * kFullRun), 8 / kFullRun),
+                                     kFullRowsPerGroup / kFullRun);  // of a workgroup
+  const int slices = ((p.N + kFullRun - 1) / kFullRun + runs - 1) / runs;
+  hipLaunchKernelGGL(full_rows_kernel, dim3(p.E * slices), dim3(kWorkgroupSize), size_t(4 * p.N), stream, p, slices,
+                     runs * kFullRun);
+  return hipGetLastError();
+}
+
 hipError_t launch_crew_kernel(const Params& p, int mode, const Roll& roll, bool recording, const float* probs, uint64_t g,
                               hipStream_t stream) {
   WaveArgs args;
@@ -2914,16 +3002,22 @@ hipError_t launch_crew_kernel(const Params& p, int mode, const Roll& roll, bool 
   args.probs = probs;
   args.g0 = g;
   args.mode = mode;
-  const auto launch = [&](auto kt) {
-    constexpr int KT = decltype(kt)::value;
-    hipError_t err = recording ? ensure_dynamic_lds(&crew_env_kernel<KT, true>, p.crew_lds) : ensure_dynamic_lds(&crew_env_kernel<KT, false>, p.crew_lds);
-    if (err != hipSuccess) return err;
-    if (recording)
-      hipLaunchKernelGGL((crew_env_kernel<KT, true>), dim3(p.E), dim3(p.crew_threads), size_t(p.crew_lds), stream, args);
-    else
-      hipLaunchKernelGGL((crew_env_kernel<KT, false>), dim3(p.E), dim3(p.crew_threads), size_t(p.crew_lds), stream, args);
-    return hipGetLastError();
+  const auto launch = [&](auto kx) {
+    constexpr int KX = decltype(kx)::value;
+    const auto go = [&](auto kernel) {
+      const hipError_t err = ensure_dynamic_lds(kernel, p.crew_lds);
+      if (err != hipSuccess) return err;
+      hipLaunchKernelGGL(kernel, dim3(p.E), dim3(p.crew_threads), size_t(p.crew_lds), stream, args);
+      return hipGetLastError();
+    };
+    if constexpr (KX > 0)
+      if (recording) return go(&crew_env_kernel<KX, true>);
+    return go(&crew_env_kernel<KX, false>);
   };
+  if (p.obs_mode != 0) {
+    const hipError_t err = launch(std::integral_constant<int, 0>{});
+    return err == hipSuccess ? launch_full_rows(p, stream) : err;
+  }
   switch (p.K) {
     case 1: return launch(std::integral_constant<int, 1>{});
     case 2: return launch(std::integral_constant<int, 2>{});
@@ -2932,8 +3026,9 @@ hipError_t launch_crew_kernel(const Params& p, int mode, const Roll& roll, bool 
     case 5: return launch(std::integral_constant<int, 5>{});
     case 6: return launch(std::integral_constant<int, 6>{});
     case 7: return launch(std::integral_constant<int, 7>{});
-    default: return launch(std::integral_constant<int, 8>{});
+    case 8: return launch(std::integral_constant<int, 8>{});
   }
+  return p.K <= kMaxRegisterK3 ? launch(std::integral_constant<int, kMaxRegisterK3>{}) : launch(std::integral_constant<int, kMaxRegisterK2>{});
 }
 
 // (one team per workgroup gets the variant whose team-dependent values are uniform, where one is compiled)
@@ -2985,12 +3080,7 @@ hipError_t launch_env_variant(const Params& p, int mode, const float* probs, uin
   }
   if constexpr (KX == -1) {
     if (err != hipSuccess || p.obs_mode != kObsFullSplit) return err;
-    const int runs = std::min<int64_t>(std::max<int64_t>(int64_t(p.E) * p.N / (kFullGroups * kFullRun), 8 / kFullRun),
-                                       kFullRowsPerGroup / kFullRun);  // of a workgroup
-    const int slices = ((p.N + kFullRun - 1) / kFullRun + runs - 1) / runs;
-    hipLaunchKernelGGL(full_rows_kernel, dim3(p.E * slices), dim3(kWorkgroupSize), size_t(4 * p.N), stream, p, slices,
-                       runs * kFullRun);
-    err = hipGetLastError();
+    return launch_full_rows(p, stream);
   }
   return err;
 }
@@ -3081,7 +3171,7 @@ hipError_t launch_env_kernel(const Params& p, int mode, const float* probs, uint
 }
 
 bool rollout_available(const Params& p) {
-  return p.wave_envs || p.crew_threads || (!p.big && p.obs_mode == 0 && (p.K <= kMaxRegisterK || p.strips));
+  return p.wave_envs || (p.crew_threads && p.obs_mode == 0) || (!p.big && p.obs_mode == 0 && (p.K <= kMaxRegisterK || p.strips));
 }
 
 hipError_t launch_rollout(const Params& p, const Roll& roll, const float* ring, uint64_t g, hipStream_t stream) {

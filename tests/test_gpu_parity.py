@@ -1207,6 +1207,21 @@ CREW = [  # a lane per agent (crew_env_kernel): edges of its workgroups, of list
     dict(num_envs=257, num_agents=640, num_taggers=60, grid_size=80, obs_k=4),
     dict(num_envs=2, num_agents=1023, num_taggers=100, grid_size=60, obs_k=8),
     dict(num_envs=2, num_agents=1024, num_taggers=300, grid_size=300, obs_k=4, tag_r2=100),
+    # the map of cells in reach: its word edges, its widest reach, the grid just beyond it
+    dict(num_envs=3, num_agents=200, num_taggers=16, grid_size=64, obs_k=4, tag_r2=64),
+    dict(num_envs=3, num_agents=300, num_taggers=90, grid_size=33, obs_k=2, tag_r2=80),
+    dict(num_envs=3, num_agents=300, num_taggers=90, grid_size=345, obs_k=4, tag_r2=81),
+    dict(num_envs=3, num_agents=700, num_taggers=150, grid_size=346, obs_k=4, tag_r2=2),
+    # K > 8
+    dict(num_envs=5, num_agents=112, num_taggers=12, grid_size=30, obs_k=9),
+    dict(num_envs=3, num_agents=129, num_taggers=13, grid_size=12, obs_k=16, tag_r2=0),
+    dict(num_envs=3, num_agents=300, num_taggers=30, grid_size=5, obs_k=12, tag_r2=-1),
+    dict(num_envs=2, num_agents=1023, num_taggers=90, grid_size=110, obs_k=13),
+    dict(num_envs=300, num_agents=640, num_taggers=60, grid_size=90, obs_k=10),
+    # full observations
+    dict(num_envs=3, num_agents=64, num_taggers=6, grid_size=20, obs_mode=1, obs_k=0),
+    dict(num_envs=9, num_agents=333, num_taggers=33, grid_size=58, obs_mode=1, obs_k=0),
+    dict(num_envs=2, num_agents=1024, num_taggers=100, grid_size=100, obs_mode=1, obs_k=0),
 ]
 
 
