@@ -472,13 +472,18 @@ void plan_spread(const wd_config& c, wd::Params* p) {
 // 22.7 -> 33.6; 200 x 101 24.0 -> 19.6 and 24.6 -> 23.0, 1000 x 101 28.3 -> 34.2 and 46.3 -> 59.5; 500 x 150 37.9 -> 30.0
 // and 49.7 -> 57.9, 1000 x 150 44.0 -> 49.9 and 91.0 -> 110; 750 x 243 (15 taggers) 169 -> 121; 500 x 201 56.5 -> 39.4 and 83.5 -> 94.1, 5000 x 201 406 -> 329
 // and 681 -> 826; 2000 x 251 227 -> 221 and 516 -> 513; 1000 x 499 410 -> 301 and 1049 -> 908.
+//   With the step in crew_env_kernel instead of env_kernel: 6000 x 20 60.1 -> 26.9; 100 x 48 28.9 -> 9.7, 5000 x 48 112 -> 49; 50 x 80 49.0 -> 9.9,
+// 500 x 80 46.8 -> 16.2 and 46.1 -> 19.5, 3000 x 80 62.8 -> 62.8; others: 65 x 43 13.8 -> 9.5, 500 x 43 15.6 -> 13.0 and 15.4 -> 14.2, 2000 x 43
+// 27.0 -> 23.2 and 26.7 -> 27.1; 300 x 65 18.0 -> 12.5 and 17.4 -> 14.3, 1000 x 65 20.7 -> 19.7 and 20.9 -> 23.9; 400 x 101 25.1 -> 16.8 and 24.3
+// -> 20.8, 1000 x 101 29.1 -> 31.3; 700 x 131 34.7 -> 30.4 and 54.8 -> 54.7, 1000 x 150 63.1 -> 53.1 and 91.0 -> 98.7.
 bool full_rows_apart(const wd_config& c) {
   const int N = c.num_agents, E = c.num_envs;
-  if (N % 4 == 0) {
-    const int64_t row_bytes = int64_t(E) * N * obs_dim(&c) * 4;
-    return (N >= 100 || (N >= wd::kWaveSize && row_bytes >= (64 << 20))) && E <= 8192;
-  }
-  return N >= 200 || (N >= 128 && E <= 512) || (N >= 100 && E <= 256);
+  // (small envs: where crew_env_kernel does the step, whose keys hold such a grid)
+  const bool short_step = c.grid_size <= 512;
+  if (N % 4 == 0) return (N >= 100 || (N >= 16 && short_step)) && E <= 8192;
+  if (N >= 200) return true;
+  if (!short_step) return (N >= 128 && E <= 512) || (N >= 100 && E <= 256);
+  return N >= 128 ? E <= 700 : N >= 64 ? E <= 500 : N >= 40 && E <= 1500;
 }
 
 // Envs that run in a wave each, without workgroup barriers: in wave_env_kernel (a lane per agent, everything in

@@ -2971,14 +2971,14 @@ crew_env_kernel(const WaveArgs) {
 // The limit on a kernel's dynamic LDS is a property of the kernel function on a device, not of a
 // handle: it is raised whenever a launch needs more than any launch before it on that device.
 constexpr int kMaxDevicesTracked = 64;
-template <typename Kernel>
-hipError_t ensure_dynamic_lds(Kernel kernel, int bytes) {
+template <auto kKernel>
+hipError_t ensure_dynamic_lds(int bytes) {
   static int granted[kMaxDevicesTracked];  // per kernel function (one instance of this template each)
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return hipGetLastError();
   if (dev < 0 || dev >= kMaxDevicesTracked || bytes > granted[dev]) {
     const hipError_t err =
-        hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+        hipFuncSetAttribute(reinterpret_cast<const void*>(kKernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (err != hipSuccess) return err;
     if (dev >= 0 && dev < kMaxDevicesTracked) granted[dev] = bytes;
   }
@@ -3004,15 +3004,16 @@ hipError_t launch_crew_kernel(const Params& p, int mode, const Roll& roll, bool 
   args.mode = mode;
   const auto launch = [&](auto kx) {
     constexpr int KX = decltype(kx)::value;
-    const auto go = [&](auto kernel) {
-      const hipError_t err = ensure_dynamic_lds(kernel, p.crew_lds);
+    const auto go = [&](auto rolls) {
+      constexpr bool kRoll = decltype(rolls)::value;
+      const hipError_t err = ensure_dynamic_lds<&crew_env_kernel<KX, kRoll>>(p.crew_lds);
       if (err != hipSuccess) return err;
-      hipLaunchKernelGGL(kernel, dim3(p.E), dim3(p.crew_threads), size_t(p.crew_lds), stream, args);
+      hipLaunchKernelGGL((crew_env_kernel<KX, kRoll>), dim3(p.E), dim3(p.crew_threads), size_t(p.crew_lds), stream, args);
       return hipGetLastError();
     };
     if constexpr (KX > 0)
-      if (recording) return go(&crew_env_kernel<KX, true>);
-    return go(&crew_env_kernel<KX, false>);
+      if (recording) return go(std::true_type{});
+    return go(std::false_type{});
   };
   if (p.obs_mode != 0) {
     const hipError_t err = launch(std::integral_constant<int, 0>{});
@@ -3043,7 +3044,7 @@ hipError_t launch_env_variant(const Params& p, int mode, const float* probs, uin
   }
   if constexpr (BIG) {
     if (p.big_spread) {  // both kernels on the caller's stream: the next call's first kernel needs what the second leaves
-      hipError_t err = ensure_dynamic_lds(&spread_obs_kernel<WIDE, KX>, p.lds_bytes);
+      hipError_t err = ensure_dynamic_lds<&spread_obs_kernel<WIDE, KX>>(p.lds_bytes);
       if (err != hipSuccess) return err;
       hipLaunchKernelGGL(spread_move_kernel, dim3(p.E * p.spread_slices), dim3(2 * kSpreadMoveThreads), 0, stream, p, mode,
                          probs, uint32_t(g), uint32_t(g >> 32));
@@ -3055,7 +3056,7 @@ hipError_t launch_env_variant(const Params& p, int mode, const float* probs, uin
     }
   }
   const int groups = (p.E + p.teams_per_wg - 1) / p.teams_per_wg;
-  hipError_t lds_err = ensure_dynamic_lds(&env_kernel<WIDE, KX, CN, BIG, ONE>, p.lds_bytes);
+  hipError_t lds_err = ensure_dynamic_lds<&env_kernel<WIDE, KX, CN, BIG, ONE>>(p.lds_bytes);
   if (lds_err != hipSuccess) return lds_err;
   hipLaunchKernelGGL((env_kernel<WIDE, KX, CN, BIG, ONE>), dim3(groups), dim3(p.wg_size), size_t(p.lds_bytes), stream, p,
                      mode, probs, uint32_t(g), uint32_t(g >> 32));
@@ -3064,7 +3065,7 @@ hipError_t launch_env_variant(const Params& p, int mode, const float* probs, uin
     if (err != hipSuccess) return err;
     // stream order puts the observation kernel behind the tables it reads; with a pipe it runs on
     // the pipe's stream behind an event, so that the caller's stream can go on with the next step
-    err = ensure_dynamic_lds(&big_obs_kernel<WIDE, KX>, p.y_base);
+    err = ensure_dynamic_lds<&big_obs_kernel<WIDE, KX>>(p.y_base);
     if (err != hipSuccess) return err;
     hipStream_t obs_stream = stream;
     if (pipe) {
@@ -3090,7 +3091,7 @@ hipError_t launch_rollout_variant(const Params& p, const Roll& roll, const float
   if constexpr (!ONE && kHasOneTeamVariant<WIDE, KX, false>) {
     if (p.teams_per_wg == 1) return launch_rollout_variant<WIDE, KX, CN, true>(p, roll, ring, g, stream);
   }
-  const hipError_t err = ensure_dynamic_lds(&rollout_kernel<WIDE, KX, CN, ONE>, p.lds_bytes);
+  const hipError_t err = ensure_dynamic_lds<&rollout_kernel<WIDE, KX, CN, ONE>>(p.lds_bytes);
   if (err != hipSuccess) return err;
   const int groups = (p.E + p.teams_per_wg - 1) / p.teams_per_wg;
   RollArgs args;

@@ -1222,6 +1222,9 @@ CREW = [  # a lane per agent (crew_env_kernel): edges of its workgroups, of list
     dict(num_envs=3, num_agents=64, num_taggers=6, grid_size=20, obs_mode=1, obs_k=0),
     dict(num_envs=9, num_agents=333, num_taggers=33, grid_size=58, obs_mode=1, obs_k=0),
     dict(num_envs=2, num_agents=1024, num_taggers=100, grid_size=100, obs_mode=1, obs_k=0),
+    dict(num_envs=7, num_agents=16, num_taggers=2, grid_size=512, obs_mode=1, obs_k=0, tag_r2=9000),
+    dict(num_envs=7, num_agents=41, num_taggers=20, grid_size=12, obs_mode=1, obs_k=0, tag_r2=0),
+    dict(num_envs=3, num_agents=199, num_taggers=30, grid_size=512, obs_mode=1, obs_k=0),
 ]
 
 
