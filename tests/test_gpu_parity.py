@@ -1237,6 +1237,24 @@ def test_lane_per_agent(n):
     recorded_against_single_iterations(kw, 900 + n, (1, 4, 3))
 
 
+BEYOND_CREW = [  # just beyond what crew_env_kernel serves: small_env_kernel, env_kernel and rollout_kernel for each K
+    dict(num_envs=1501, num_agents=66, num_taggers=6, grid_size=30, obs_k=2),
+    dict(num_envs=3001, num_agents=99, num_taggers=9, grid_size=35, obs_k=8),
+    dict(num_envs=4097, num_agents=128, num_taggers=12, grid_size=40, obs_k=5),
+] + [dict(num_envs=2, num_agents=1025 + k, num_taggers=100, grid_size=113, obs_k=k) for k in range(1, 9)] + [
+    dict(num_envs=160, num_agents=1026, num_taggers=100, grid_size=113, obs_k=12),
+    dict(num_envs=290, num_agents=1027, num_taggers=100, grid_size=113, obs_k=16),
+]
+
+
+@pytest.mark.parametrize("n", range(len(BEYOND_CREW)))
+def test_beyond_lane_per_agent(n):
+    """Two iterations against the oracle, then recorded multi-step launches against single iterations."""
+    kw = dict(BEYOND_CREW[n], seed=950 + n, episode_length=3)
+    lockstep(kw, 2, 950 + n, fused=True, sharded=8)
+    recorded_against_single_iterations(kw, 950 + n, (1, 4))
+
+
 @pytest.mark.parametrize("num_agents", [12, 13])
 def test_more_envs_than_a_launch_has_waves(num_agents):
     """Batches of 2^26 envs and more: a wave per env would be 2^32 threads, more than one launch can have.  Envs from both
