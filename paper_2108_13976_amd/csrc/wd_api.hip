@@ -20,7 +20,6 @@ struct wd_handle {
   bool started;        // wd_reset(WD_RESET_ALL) has run
   bool rows_valid;     // bufs.obs holds the rows this library wrote for the current state
   void* scratch;       // device memory of the large-env tables (NULL for the small layout)
-  int spread_parity;   // spread form of the large-env pair: the set of accumulators the next stepping call uses
   // roll-outs of the large-env layout: a second stream for the observation kernels, a second
   // table image and two events per image (created by the first such roll-out, freed by wd_destroy)
   hipStream_t obs_stream;
@@ -718,9 +717,9 @@ int64_t place_big_tables(wd::Params* p, int64_t E, unsigned char* base) {
   const int64_t key_bytes = p->wide == 1 ? 8 : 4;
   const int64_t slot_b = align16(2 * p->g_stride_agents * E), best_b = align16(key_bytes * p->g_stride_agents * E);
   const int64_t cred_b = align16(4 * p->g_stride_credits * E), image_b = p->big_spread ? 0 : p->g_stride_image * E;
-  // spread form: packed positions, the envs' scalars and the two sets of accumulators
+  // spread form: packed positions, the envs' scalars, the number of each env's current set of accumulators, both sets
   const int64_t pl_b = p->big_spread ? align16(4 * p->g_stride_agents * E) : 0;
-  const int64_t env_b = p->big_spread ? 16 * E : 0;
+  const int64_t env_b = p->big_spread ? 16 * E : 0, set_b = p->big_spread ? align16(4 * E) : 0;
   const int64_t acc_b = p->big_spread ? 2 * 4 * p->g_stride_acc * E : 0;
   if (base) {
     p->g_best = base;
@@ -730,9 +729,10 @@ int64_t place_big_tables(wd::Params* p, int64_t E, unsigned char* base) {
     unsigned char* at = p->g_image + image_b;
     p->g_pl = reinterpret_cast<uint32_t*>(at);
     p->g_env = reinterpret_cast<int32_t*>(at + pl_b);
-    p->g_acc = reinterpret_cast<uint32_t*>(at + pl_b + env_b);
+    p->g_set = reinterpret_cast<int32_t*>(at + pl_b + env_b);
+    p->g_acc = reinterpret_cast<uint32_t*>(at + pl_b + env_b + set_b);
   }
-  return slot_b + best_b + cred_b + image_b + pl_b + env_b + acc_b;
+  return slot_b + best_b + cred_b + image_b + pl_b + env_b + set_b + acc_b;
 }
 
 // What a roll-out of the large-env layout needs to run the observation kernel of one iteration
@@ -800,15 +800,14 @@ int wd_create(const wd_config* cfg, const wd_buffers* bufs, wd_handle** out) {
       return WD_E_HIP;
     }
     place_big_tables(&params, cfg->num_envs, static_cast<unsigned char*>(h->scratch));
-    if (params.big_spread &&  // both sets of accumulators start clear
-        hipMemset(params.g_acc, 0, size_t(2 * 4 * params.g_stride_acc) * size_t(cfg->num_envs)) != hipSuccess) {
+    const size_t clear = size_t(align16(4 * int64_t(cfg->num_envs)) + 2 * 4 * params.g_stride_acc * int64_t(cfg->num_envs));
+    if (params.big_spread && hipMemset(params.g_set, 0, clear) != hipSuccess) {  // set 0 is the first, both start clear
       (void)hipGetLastError();
       (void)hipFree(h->scratch);
       delete h;
       return WD_E_HIP;
     }
   }
-  h->spread_parity = 0;
   h->cfg = *cfg;
   h->bufs = *bufs;
   h->params = params;
@@ -857,10 +856,8 @@ int wd_step(wd_handle* h) {
   if (!h->started) return WD_E_STATE;
   wd::Params q = h->params;
   q.rows_kept = h->rows_valid ? 1 : 0;
-  q.spread_parity = h->spread_parity;
   const hipError_t err = wd::launch_env_kernel(q, wd::kModeStep, nullptr, h->g, h->stream);
   if (err != hipSuccess) return hip_failed(h, err, "step kernel");
-  h->spread_parity ^= 1;
   h->rows_valid = true;
   h->g += 1;
   return WD_OK;
@@ -872,10 +869,8 @@ int wd_iterate(wd_handle* h, const float* probs) {
   if (!h->started) return WD_E_STATE;
   wd::Params q = h->params;
   q.rows_kept = h->rows_valid ? 1 : 0;
-  q.spread_parity = h->spread_parity;
   const hipError_t err = wd::launch_env_kernel(q, wd::kModeIterate, probs, h->g, h->stream);
   if (err != hipSuccess) return hip_failed(h, err, "iterate kernel");
-  h->spread_parity ^= 1;
   h->rows_valid = true;
   h->g += 1;
   return WD_OK;
@@ -951,7 +946,6 @@ int wd_rollout(wd_handle* h, const float* probs_ring, int ring_len, int k, const
     for (int s = 0; s < k; ++s) {
       wd::Params q = h->params;
       q.rows_kept = rows_kept;
-      q.spread_parity = h->spread_parity;
       wd::ObsPipe pipe = {};
       if (piped) {
         const int b = s & 1;
@@ -975,7 +969,6 @@ int wd_rollout(wd_handle* h, const float* probs_ring, int ring_len, int k, const
       const hipError_t err = wd::launch_env_kernel(q, wd::kModeIterate, probs, h->g + uint64_t(s), h->stream,
                                                    piped ? &pipe : nullptr);
       if (err != hipSuccess) return hip_failed(h, err, "iteration kernel of a roll-out");
-      h->spread_parity ^= 1;
     }
     if (piped) {  // what follows on the caller's stream sees every row
       const hipError_t werr = hipStreamWaitEvent(h->stream, h->rows_done[(k - 1) & 1], 0);

@@ -135,14 +135,15 @@ struct Params {
   // by slices of 512 agents) leaves packed positions, ranks inside the buckets and, in the
   // accumulators, bucket counts, credits and the number of tags; spread_obs_kernel finishes the step
   // and builds the tables per slice.  Two sets of accumulators take turns: the kernels of one call
-  // use set `spread_parity`, and the second kernel clears the other set for the next call.
+  // use the env's current set, and the second kernel clears the other one and makes it current for the next call.
+  // Which one is current stands in device memory, so that a HIP graph of such calls can be replayed.
   int32_t big_spread;
   int32_t spread_slices;   // workgroups per env in spread_move_kernel
-  int32_t spread_parity;
   uint32_t tag_mul;        // coarse cell of a tagger: (x * tag_mul) >> 16 per axis, tag_nbx cells per side
   int32_t tag_nbx;
   uint32_t* g_pl;          // [E][NPAD] packed positions after the move and the tag check
-  int32_t* g_env;          // [E][4] done, t, n_live_runners as the call found them
+  int32_t* g_env;          // [E][4] done, t, n_live_runners and set of accumulators as the call found them
+  int32_t* g_set;          // [E] current set; the first kernel reads it, the second one writes it
   uint32_t* g_acc;         // [2][E][g_stride_acc]: credits per tagger, number of tags
   int64_t g_stride_acc;
   int32_t acc_credits, acc_tags;  // word offsets inside one env's accumulators

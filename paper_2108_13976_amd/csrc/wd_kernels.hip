@@ -1226,11 +1226,12 @@ __global__ __launch_bounds__(2 * kSpreadMoveThreads) void spread_move_kernel(con
   const int tid = threadIdx.x, lt = tid & (kSpreadMoveThreads - 1);
   const bool tagger_half = tid >= kSpreadMoveThreads;
   const int e = blockIdx.x / p.spread_slices, s = blockIdx.x - e * p.spread_slices;
-  const int done_in = p.done[e], t_in = p.t[e], nlr_in = p.n_live_runners[e];
+  const int done_in = p.done[e], t_in = p.t[e], nlr_in = p.n_live_runners[e], set = p.g_set[e];
   if (s == 0 && tid == 0) {  // the second kernel overwrites these while its other workgroups still need them
     p.g_env[4 * e + 0] = done_in;
     p.g_env[4 * e + 1] = t_in;
     p.g_env[4 * e + 2] = nlr_in;
+    p.g_env[4 * e + 3] = set;
   }
   if (mode != kModeStep && mode != kModeIterate) return;
   const int N = p.N, N_tag = p.N_tag;
@@ -1276,7 +1277,7 @@ __global__ __launch_bounds__(2 * kSpreadMoveThreads) void spread_move_kernel(con
   const bool vec = p.vec4 != 0;
   if (mode == kModeIterate) store4(p.action, a0, mine.n, vec, mine.act);
   if (!step_act) return;
-  uint32_t* const acc = p.g_acc + (int64_t(p.spread_parity) * p.E + e) * p.g_stride_acc;
+  uint32_t* const acc = p.g_acc + (int64_t(set) * p.E + e) * p.g_stride_acc;
   int my_tags = 0;
   bool live_after[4];
   // A coarse cell is at least a tag radius wide, so a runner's reach touches at most 3 x 3 of them.
@@ -1357,10 +1358,13 @@ __global__ __launch_bounds__(kSpreadObsThreads) void spread_obs_kernel(const Par
   const int64_t abase = int64_t(e) * N;
   const TeamLds<WIDE, true> L(smem, 0, p, e);
   const int done_in = p.g_env[4 * e + 0], t_in = p.g_env[4 * e + 1], nlr_in = p.g_env[4 * e + 2];
+  const int set = p.g_env[4 * e + 3];
   const bool stepping = mode == kModeStep || mode == kModeIterate;
-  const uint32_t* const acc = p.g_acc + (int64_t(p.spread_parity) * p.E + e) * p.g_stride_acc;
+  uint32_t* const acc0 = p.g_acc + int64_t(e) * p.g_stride_acc;
+  uint32_t* const acc1 = acc0 + int64_t(p.E) * p.g_stride_acc;
+  const uint32_t* const acc = set ? acc1 : acc0;
   const uint32_t* const env_pl = p.g_pl + int64_t(e) * p.NPAD;
-  const int acc_tags = int(acc[p.acc_tags]);
+  const int tags0 = int(acc0[p.acc_tags]), tags1 = int(acc1[p.acc_tags]);  // (both, so that neither waits for `set`)
   // The packed positions of a stepped env go straight into LDS, and the bucket counters are cleared,
   // before anything waits for the env's scalars (a reset does not use the positions).
   {
@@ -1370,15 +1374,16 @@ __global__ __launch_bounds__(kSpreadObsThreads) void spread_obs_kernel(const Par
     for (int j = tid; j < p.NPAD / 4; j += ts) dst[j] = src[j];
     for (int j = tid; j < p.nb_cap; j += ts) L.counts[j] = 0u;
   }
-  if (stepping) {  // the other set of accumulators is clear when the next call's first kernel starts
-    uint32_t* const other = p.g_acc + (int64_t(p.spread_parity ^ 1) * p.E + e) * p.g_stride_acc;
+  if (stepping) {  // the other set of accumulators is clear, and current, when the next call's first kernel starts
+    uint32_t* const other = set ? acc0 : acc1;
+    if (s == 0 && tid == 0) p.g_set[e] = set ^ 1;
     for (int64_t j = int64_t(s) * ts + tid; j < p.g_stride_acc; j += int64_t(p.big_slices) * ts) other[j] = 0u;
   }
   const bool stepped = stepping && !done_in;
   int t_out = t_in, tags = 0;
   bool done_now = done_in != 0;
   if (stepped) {
-    tags = acc_tags;
+    tags = set ? tags1 : tags0;
     t_out = t_in + 1;
     done_now = (nlr_in - tags == 0) || (t_out >= p.T);
   }

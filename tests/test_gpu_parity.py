@@ -1255,6 +1255,54 @@ def test_beyond_lane_per_agent(n):
     recorded_against_single_iterations(kw, 950 + n, (1, 4))
 
 
+REPLAYED = {  # a kernel of each kind; the large envs' step spread over workgroups keeps what it counts in device memory
+    "large_env_spread": dict(num_envs=3, num_agents=2500, num_taggers=250, grid_size=160, obs_k=4),
+    "large_env_spread_wide_reach": dict(num_envs=2, num_agents=4200, num_taggers=20, grid_size=300, obs_k=4, tag_r2=900),
+    "large_env_pair": dict(num_envs=3, num_agents=800, num_taggers=80, grid_size=1000, obs_k=4),
+    "one_workgroup": dict(num_envs=3, num_agents=300, num_taggers=30, grid_size=55, obs_k=4),
+    "few_agents": dict(num_envs=5, num_agents=20, num_taggers=3, grid_size=14, obs_k=4),
+    "full_views": dict(num_envs=5, num_agents=48, num_taggers=5, grid_size=20, obs_mode=1, obs_k=0),
+}
+
+
+@pytest.mark.parametrize("calls", [1, 2])
+@pytest.mark.parametrize("name", list(REPLAYED))
+def test_graph_replays(name, calls):
+    """A HIP graph of one or two iterations, replayed with eager calls on the same handle between the replays: every
+    replay leaves what eager calls with the same step numbers leave."""
+    import torch
+
+    import paper_2108_13976_amd as wd
+
+    kw = dict(REPLAYED[name], seed=71, episode_length=6)
+    E, N = kw["num_envs"], kw["num_agents"]
+    stream = torch.cuda.Stream()
+    ring = upload(np.stack([probs_for_step(71, r, E, N) for r in range(3)]), "cuda:0")
+    with torch.cuda.stream(stream):
+        a, b = make_gpu(kw), make_gpu(kw)
+        for env in (a, b):
+            env.reset(wd.WD_RESET_ALL)
+            env.iterate(ring[2])
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            for c in range(calls):
+                a.iterate(ring[c])
+        for replay in range(5):
+            graph.replay()
+            b.global_step = 1
+            for c in range(calls):
+                b.iterate(ring[c])
+            stream.synchronize()
+            got, want = a.to_host(), b.to_host()
+            for n in want:
+                assert got[n].tobytes() == want[n].tobytes(), (replay, n)
+            for env in (a, b)[:2 if replay % 2 else 0]:
+                env.global_step = 40 + replay
+                env.iterate(ring[replay % 3])
+        a.close(), b.close()
+
+
 @pytest.mark.parametrize("num_agents", [12, 13])
 def test_more_envs_than_a_launch_has_waves(num_agents):
     """Batches of 2^26 envs and more: a wave per env would be 2^32 threads, more than one launch can have.  Envs from both
