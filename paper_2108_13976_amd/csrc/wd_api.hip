@@ -475,11 +475,19 @@ void plan_spread(const wd_config& c, wd::Params* p) {
 // 500 x 80 46.8 -> 16.2 and 46.1 -> 19.5, 3000 x 80 62.8 -> 62.8; others: 65 x 43 13.8 -> 9.5, 500 x 43 15.6 -> 13.0 and 15.4 -> 14.2, 2000 x 43
 // 27.0 -> 23.2 and 26.7 -> 27.1; 300 x 65 18.0 -> 12.5 and 17.4 -> 14.3, 1000 x 65 20.7 -> 19.7 and 20.9 -> 23.9; 400 x 101 25.1 -> 16.8 and 24.3
 // -> 20.8, 1000 x 101 29.1 -> 31.3; 700 x 131 34.7 -> 30.4 and 54.8 -> 54.7, 1000 x 150 63.1 -> 53.1 and 91.0 -> 98.7.
-bool full_rows_apart(const wd_config& c) {
+//   Larger grids (the figures above are of grids of up to 110 cells a side), rows of env_kernel -> apart behind env_kernel -> apart behind
+// crew_env_kernel, which has keys of 32 bits (up to 1639 cells for 20 agents, 1159 for 64, 820 for 100, 579 for 200): 8000 x 64 on 600 cells 239 -> 102
+// -> 89.3 and 246 -> 191 -> 178, 1100 x 64 49.7 -> 29.4 -> 23.4, 1000 x 96 62.2 -> 33.6 -> 27.9; 500 x 48 on 700 cells 30.1 -> 13.9, 6000 x 20 on 600
+// 60.7 -> 27.2 and 55.6 -> 37.2, 100 x 43 on 800 13.3 -> 9.4.  Keys of 64 bits: 8000 x 64 on 5000 cells 265 -> 101 and 271 -> 191, 3000 x 80 on 1000 153 ->
+// 57.1 and 158 -> 86.2, 1000 x 96 on 4500 61.8 -> 33.4 and 63.6 -> 43.4.
+bool full_rows_apart(const wd_config& c, const wd::Params& p) {
   const int N = c.num_agents, E = c.num_envs;
-  // (small envs: where crew_env_kernel does the step, whose keys hold such a grid)
-  const bool short_step = c.grid_size <= 512;
-  if (N % 4 == 0) return (N >= 100 || (N >= 16 && short_step)) && E <= 8192;
+  // (small envs: where crew_env_kernel does the step, which has keys of 32 bits)
+  const bool short_step = !p.big && N <= wd::kMaxEnvWorkgroupSize && !p.wide;
+  if (N % 4 == 0) {
+    const int64_t row_bytes = int64_t(E) * N * obs_dim(&c) * 4;
+    return (N >= 100 || (N >= 16 && short_step) || (N >= wd::kWaveSize && row_bytes >= (64 << 20))) && E <= 8192;
+  }
   if (N >= 200) return true;
   if (!short_step) return (N >= 128 && E <= 512) || (N >= 100 && E <= 256);
   return N >= 128 ? E <= 700 : N >= 64 ? E <= 500 : N >= 40 && E <= 1500;
@@ -631,7 +639,6 @@ int fill_params(const wd_config& c, const wd_buffers& b, wd::Params* p, bool own
   p->K = c.obs_mode == WD_OBS_PARTIAL ? c.obs_k : 0;
   p->D = obs_dim(&c);
   p->obs_mode = c.obs_mode;
-  if (c.obs_mode == WD_OBS_FULL && full_rows_apart(c)) p->obs_mode = wd::kObsFullSplit;
   p->env_offset = uint32_t(c.env_offset);
   p->seed_lo = uint32_t(c.seed);
   p->seed_hi = uint32_t(c.seed >> 32);
@@ -698,6 +705,7 @@ int fill_params(const wd_config& c, const wd_buffers& b, wd::Params* p, bool own
     }
   }
   if (!planned || !wd::env_kernel_available(*p)) return WD_E_UNSUPPORTED;
+  if (c.obs_mode == WD_OBS_FULL && full_rows_apart(c, *p)) p->obs_mode = wd::kObsFullSplit;
   plan_spread(c, p);
   plan_waves(c, p);
   plan_crew(c, p);

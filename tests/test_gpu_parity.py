@@ -1237,6 +1237,23 @@ def test_lane_per_agent(n):
     recorded_against_single_iterations(kw, 900 + n, (1, 4, 3))
 
 
+FULL_ON_LARGE_GRIDS = [  # rows apart behind crew_env_kernel up to the largest grid of its keys, then behind env_kernel
+    dict(num_envs=7, num_agents=20, num_taggers=2, grid_size=1639, tag_r2=2 * 1639 * 1639),  # everybody tagged at once
+    dict(num_envs=3, num_agents=43, num_taggers=20, grid_size=1159, tag_r2=90000),
+    dict(num_envs=3, num_agents=64, num_taggers=6, grid_size=1159, tag_r2=9000),
+    dict(num_envs=3, num_agents=100, num_taggers=50, grid_size=820, tag_r2=10000),
+    dict(num_envs=1100, num_agents=64, num_taggers=6, grid_size=1160, tag_r2=9000),
+]
+
+
+@pytest.mark.parametrize("n", range(len(FULL_ON_LARGE_GRIDS)))
+def test_full_observations_on_large_grids(n):
+    kw = dict(FULL_ON_LARGE_GRIDS[n], obs_mode=1, obs_k=0, seed=940 + n, episode_length=4)
+    for fused in (False, True):
+        lockstep(kw, 6, 940 + n, fused=fused, sharded=8 if kw["num_envs"] > 100 else 0)
+    recorded_against_single_iterations(kw, 940 + n, (1, 3))
+
+
 BEYOND_CREW = [  # just beyond what crew_env_kernel serves: small_env_kernel, env_kernel and rollout_kernel for each K
     dict(num_envs=1501, num_agents=66, num_taggers=6, grid_size=30, obs_k=2),
     dict(num_envs=3001, num_agents=99, num_taggers=9, grid_size=35, obs_k=8),

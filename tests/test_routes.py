@@ -1,0 +1,25 @@
+"""Which kernel serves which configuration (host side only, no GPU)."""
+import pytest
+
+from routes import route
+
+
+def full_views(E, N, G):
+    return dict(num_envs=E, num_agents=N, num_taggers=max(1, N // 10), grid_size=G, obs_mode=1, obs_k=0)
+
+
+@pytest.mark.parametrize("E,N,G", [
+    (8000, 64, 512), (8000, 64, 513), (8000, 64, 1159), (1100, 64, 600), (1000, 96, 600), (3000, 80, 800), (500, 48, 700),
+    (6000, 20, 1600), (100, 43, 800), (300, 65, 800)])
+def test_full_views_rows_apart_wherever_the_keys_have_32_bits(E, N, G):
+    r = route(full_views(E, N, G))
+    assert r.wide == 0 and r.apart == 1 and r.kernel == "crew_env_kernel", r
+
+
+@pytest.mark.parametrize("E,N,G,apart", [
+    (8000, 64, 1160, 1), (8000, 64, 5000, 1), (1100, 64, 5000, 1), (900, 64, 5000, 0), (1000, 96, 4500, 1), (300, 96, 4500, 0), (8193, 64, 5000, 0),
+    (300, 65, 5000, 0), (256, 101, 5000, 1), (257, 101, 5000, 0), (512, 131, 5000, 1), (513, 131, 5000, 0)])
+def test_full_views_with_keys_of_64_bits(E, N, G, apart):
+    """env_kernel does the step; agent counts that are multiples of four have their rows apart from 64 MB on."""
+    r = route(full_views(E, N, G))
+    assert r.wide != 0 and r.apart == apart and r.kernel == "env_kernel", r
