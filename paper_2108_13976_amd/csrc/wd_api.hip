@@ -471,10 +471,13 @@ void plan_spread(const wd_config& c, wd::Params* p) {
 // 22.7 -> 33.6; 200 x 101 24.0 -> 19.6 and 24.6 -> 23.0, 1000 x 101 28.3 -> 34.2 and 46.3 -> 59.5; 500 x 150 37.9 -> 30.0
 // and 49.7 -> 57.9, 1000 x 150 44.0 -> 49.9 and 91.0 -> 110; 750 x 243 (15 taggers) 169 -> 121; 500 x 201 56.5 -> 39.4 and 83.5 -> 94.1, 5000 x 201 406 -> 329
 // and 681 -> 826; 2000 x 251 227 -> 221 and 516 -> 513; 1000 x 499 410 -> 301 and 1049 -> 908.
-//   With the step in crew_env_kernel instead of env_kernel: 6000 x 20 60.1 -> 26.9; 100 x 48 28.9 -> 9.7, 5000 x 48 112 -> 49; 50 x 80 49.0 -> 9.9,
-// 500 x 80 46.8 -> 16.2 and 46.1 -> 19.5, 3000 x 80 62.8 -> 62.8; others: 65 x 43 13.8 -> 9.5, 500 x 43 15.6 -> 13.0 and 15.4 -> 14.2, 2000 x 43
-// 27.0 -> 23.2 and 26.7 -> 27.1; 300 x 65 18.0 -> 12.5 and 17.4 -> 14.3, 1000 x 65 20.7 -> 19.7 and 20.9 -> 23.9; 400 x 101 25.1 -> 16.8 and 24.3
-// -> 20.8, 1000 x 101 29.1 -> 31.3; 700 x 131 34.7 -> 30.4 and 54.8 -> 54.7, 1000 x 150 63.1 -> 53.1 and 91.0 -> 98.7.
+//   With the step in crew_env_kernel instead of env_kernel (20 to 60 agents: bucket rings and rows in one launch): 10 x 16 17.4 -> 8.9 and 16.8 -> 9.1,
+// 8192 x 16 73.1 -> 28.5 and 65.8 -> 38.8; 6000 x 20 61.8 -> 26.7 and 57.6 -> 35.7; 8192 x 32 125 -> 41.9 and 112 -> 59.6; 100 x 48 30.2 -> 9.6 and 28.4 ->
+// 10.0, 6000 x 48 127 -> 46.5 and 115 -> 66.5; 8192 x 60 216 -> 84.8 and 197 -> 160; 50 x 80 49.0 -> 9.9, 500 x 80 46.8 -> 16.2 and 46.1 -> 19.5, 8192 x
+// 96 208 -> 198 and 343 -> 336.  Others: 5 x 41 12.4 -> 8.6 and 14.4 -> 9.1, 700 x 46 18.1 -> 15.5 and 19.4 -> 18.6, 700 x 50 18.6 -> 17.5 and 19.9 -> 20.3,
+// 900 x 50 19.3 -> 19.2 and 21.0 -> 23.1, 1500 x 43 20.0 -> 21.4 and 21.9 -> 26.4; 500 x 65 19.9 -> 15.7 and 21.5 -> 19.2, 500 x 127 32.8 -> 23.2 and 34.1
+// -> 31.6; 1000 x 65 20.7 -> 19.7 and 20.9 -> 23.9, 1000 x 101 29.1 -> 31.3; 700 x 150 41.2 -> 32.7 and 51.5 -> 49.7, 700 x 199 60.8 -> 44.4 and 110 -> 94.8,
+// 1000 x 150 63.1 -> 53.1 and 91.0 -> 98.7.
 //   Larger grids (the figures above are of grids of up to 110 cells a side), rows of env_kernel -> apart behind env_kernel -> apart behind
 // crew_env_kernel, which has keys of 32 bits (up to 1639 cells for 20 agents, 1159 for 64, 820 for 100, 579 for 200): 8000 x 64 on 600 cells 239 -> 102
 // -> 89.3 and 246 -> 191 -> 178, 1100 x 64 49.7 -> 29.4 -> 23.4, 1000 x 96 62.2 -> 33.6 -> 27.9; 500 x 48 on 700 cells 30.1 -> 13.9, 6000 x 20 on 600
@@ -490,7 +493,7 @@ bool full_rows_apart(const wd_config& c, const wd::Params& p) {
   }
   if (N >= 200) return true;
   if (!short_step) return (N >= 128 && E <= 512) || (N >= 100 && E <= 256);
-  return N >= 128 ? E <= 700 : N >= 64 ? E <= 500 : N >= 40 && E <= 1500;
+  return N >= 128 ? E <= 700 : N >= 64 ? E <= 500 : N >= 40 && E <= 700;
 }
 
 // Envs that run in a wave each, without workgroup barriers: in wave_env_kernel (a lane per agent, everything in

@@ -23,3 +23,10 @@ def test_full_views_with_keys_of_64_bits(E, N, G, apart):
     """env_kernel does the step; agent counts that are multiples of four have their rows apart from 64 MB on."""
     r = route(full_views(E, N, G))
     assert r.wide != 0 and r.apart == apart and r.kernel == "env_kernel", r
+
+
+@pytest.mark.parametrize("E,N,apart", [(700, 41, 1), (701, 41, 0), (700, 63, 1), (1500, 43, 0), (500, 65, 1), (501, 65, 0), (700, 129, 1), (701, 129, 0),
+                                       (9000, 203, 1), (8192, 16, 1), (8193, 16, 0), (8192, 12, 0), (100, 39, 0)])
+def test_full_views_rows_apart_by_the_size_of_the_batch(E, N, apart):
+    """Agent counts that are no multiple of four gain only in batches that do not fill the chip."""
+    assert route(full_views(E, N, 110)).apart == apart
