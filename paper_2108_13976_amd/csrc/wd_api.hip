@@ -554,6 +554,17 @@ void plan_waves(const wd_config& c, wd::Params* p) {
   }
 }
 
+// Words per row of crew_env_kernel's map of the cells that taggers reach; 0: no map, every runner is compared with every tagger.
+// The map costs two barriers' worth and a row of marks per cell of the tag's height, a comparison about four instructions per
+// tagger, so the map pays from 16 taggers per row of the reach on.  us per iteration in mid-training, without / with it: radius 0, 16 taggers
+// 256 x 1000 18.5 / 18.4; radius 1, 777 x 333: 16 taggers 17.8 / 17.8, 32 19.3 / 18.3, 64 20.2 / 18.5; radius 3: 32 taggers 777 x 200 15.3 / 15.6, 64 777 x
+// 333 20.3 / 19.2, 100 22.4 / 20.3; radius 5: 64 19.1 / 18.8, 100 22.6 / 20.1; radius 8: 16 17.4 / 18.4, 100 777 x 200 19.1 / 20.6, 256 x 1000 21.4 / 20.8, 500 34.7
+// / 32.4.  (Larger grids and longer reaches: the map's 16 KB and two words per mark are where it was made to end.)
+int crew_map_words(const wd_config& c, const wd::Params& p) {
+  const int words = (c.grid_size + 31) / 32 + 1;  // (a tagger's reach in a row touches two words at most)
+  return p.tag_rad <= 8 && words * c.grid_size <= 4096 && c.num_taggers >= 16 * (1 + p.tag_rad) ? words : 0;
+}
+
 // Envs of 65 to 1024 agents that run in crew_env_kernel: a workgroup per env, a lane per agent.  A shorter chain of phases than
 // env_kernel's (or small_env_kernel's, up to 128 agents), for more lanes and instructions per agent: it wins while the chain is what
 // bounds a batch.  Measured, us per iteration in mid-training, the other kernel -> crew_env_kernel:
@@ -576,6 +587,10 @@ bool crew_serves(const wd_config& c, const wd::Params& p) {
   if (p.big || N > wd::kMaxEnvWorkgroupSize) return false;
   if (c.obs_mode == WD_OBS_FULL) return p.obs_mode == wd::kObsFullSplit && !p.wide;
   if (!p.strips || N <= wd::kWaveSize) return false;
+  // many taggers of a short reach on a grid too large for the map: env_kernel's taggers look into the bins that they reach (K = 4 on 342 cells,
+  // env_kernel / this: 200 taggers, 256 x 700 no difference, 256 x 1000 up to 11 %; 256 taggers 256 x 850 24.9 / 25.6; 500 256 x 1000 24.3 / 34.1;
+  // radius 10, 100 taggers on 100 cells 62.9 / 21.5)
+  if (c.num_taggers > 192 && p.tag_rad <= 8 && !crew_map_words(c, p)) return false;
   const int64_t agents = int64_t(E) * N;
   if (K > wd::kMaxRegisterK3) return agents <= 500000 && (N > wd::kSmallEnvAgents || (N >= 112 && E >= 256));
   if (K > wd::kMaxRegisterK) return agents <= 700000 && (N >= 112 || (N >= 96 && E >= 64));
@@ -602,8 +617,7 @@ void plan_crew(const wd_config& c, wd::Params* p) {
     p->cshift = shift;
     p->strip_C = ((c.grid_size - 1) >> shift) + 1;
   }
-  const int reach_words = (c.grid_size + 31) / 32 + 1;  // (a tagger's reach in a row touches two words at most)
-  p->crew_reach_words = p->tag_rad <= 8 && reach_words * c.grid_size <= 4096 && c.num_taggers >= 16 ? reach_words : 0;
+  p->crew_reach_words = crew_map_words(c, *p);
   int64_t off = 0;
   auto take = [&off](int64_t bytes) {
     const int64_t at = off;

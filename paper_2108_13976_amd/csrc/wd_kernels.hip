@@ -2479,7 +2479,7 @@ hipError_t launch_small_kernel(const Params& p, int mode, const Roll& roll, cons
 // agents that the windows do not settle get sixteen lanes each, which read the bins within the distance already known.
 //
 // Where many taggers have a short reach, they mark the cells that they reach in a bit map, and only runners on marked cells are
-// compared with them.
+// compared with them, one by one by their wave, or all of the wave's by a lane each where they are many.
 //
 // Bound: the chain of one workgroup (three or four barriers and about 600 instructions up to the rows where the list is compared
 // whole), for larger batches the vector ALUs.  20 envs x 333 agents, K = 4: 18.0 -> 11.0 us per iteration, 777 x 333 25.6 -> 17.3 (its
@@ -2665,6 +2665,7 @@ crew_env_kernel(const WaveArgs) {
         const auto key_of = [&](uint32_t other, uint32_t me, int tg) {
           return (squared_length(__builtin_bit_cast(short2v, other) - __builtin_bit_cast(short2v, me)) << ib) | uint32_t(tg);
         };
+        bool compare = wave * kWaveSize + kWaveSize > N_tag;  // (uniform: some lane of the wave owns a runner)
         if (reach_words) {
           // Many taggers with a short reach: they mark the cells that they reach, and only a runner on a marked cell is compared
           // with them, by its whole wave.
@@ -2679,18 +2680,24 @@ crew_env_kernel(const WaveArgs) {
           }
           __syncthreads();
           const bool near = lv && !tagger && ((L.reached[y * reach_words + (x >> 5)] >> (x & 31)) & 1u);
-          for (uint64_t left = __ballot(near); left != 0; left &= left - 1) {
-            const int who = __builtin_ctzll(left);
-            const uint32_t me = uint32_t(__builtin_amdgcn_readlane(int(here), who));
-            uint32_t best = ~0u;
-            for (int tg = lane; tg < N_tag; tg += kWaveSize) best = min(best, key_of(L.taggers[tg], me, tg));
-            best = wave_smallest(best);
-            if (int(best >> ib) <= p.tag_r2 && lane == who) {
-              tagged = true;
-              atomicAdd(&L.credits[best & ((1u << ib) - 1u)], 1);
+          uint64_t left = __ballot(near);
+          // (a runner by its wave costs about as much as ten taggers by a lane, more where there are more taggers than lanes; one by one
+          // whatever their number: 256 x 1000 with 500 taggers of radius 3 54.1 us instead of 29.4, 777 x 333 with 33 of radius 8 26.5 / 18)
+          compare = __popcll(left) * (10 + (N_tag >> 5)) > N_tag;
+          if (!compare)
+            for (; left != 0; left &= left - 1) {
+              const int who = __builtin_ctzll(left);
+              const uint32_t me = uint32_t(__builtin_amdgcn_readlane(int(here), who));
+              uint32_t best = ~0u;
+              for (int tg = lane; tg < N_tag; tg += kWaveSize) best = min(best, key_of(L.taggers[tg], me, tg));
+              best = wave_smallest(best);
+              if (int(best >> ib) <= p.tag_r2 && lane == who) {
+                tagged = true;
+                atomicAdd(&L.credits[best & ((1u << ib) - 1u)], 1);
+              }
             }
-          }
-        } else if (wave * kWaveSize + kWaveSize > N_tag) {  // (uniform: some lane of the wave owns a runner)
+        }
+        if (compare) {
           uint32_t best = ~0u;
           int tg = 0;
           for (; tg + 4 <= N_tag; tg += 4) {

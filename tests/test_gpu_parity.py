@@ -1237,6 +1237,29 @@ def test_lane_per_agent(n):
     recorded_against_single_iterations(kw, 900 + n, (1, 4, 3))
 
 
+REACH = [  # crew_env_kernel's map of the cells in reach: largest grid, widest reach, word edges, few and many runners on marked cells
+    dict(num_envs=3, num_agents=700, num_taggers=150, grid_size=341, obs_k=4, tag_r2=80),
+    dict(num_envs=3, num_agents=300, num_taggers=144, grid_size=341, obs_k=2, tag_r2=64),
+    dict(num_envs=3, num_agents=700, num_taggers=150, grid_size=342, obs_k=4, tag_r2=80),     # no map
+    dict(num_envs=3, num_agents=400, num_taggers=160, grid_size=64, obs_k=4, tag_r2=80),
+    dict(num_envs=3, num_agents=300, num_taggers=144, grid_size=33, obs_k=4, tag_r2=64),
+    dict(num_envs=4, num_agents=333, num_taggers=33, grid_size=97, obs_k=4, tag_r2=2),        # few near
+    dict(num_envs=4, num_agents=333, num_taggers=40, grid_size=9, obs_k=4, tag_r2=2),         # all near
+    dict(num_envs=4, num_agents=333, num_taggers=16, grid_size=20, obs_k=4, tag_r2=0),
+    dict(num_envs=2, num_agents=1024, num_taggers=500, grid_size=100, obs_k=4, tag_r2=9),     # some waves few, some many
+    dict(num_envs=2, num_agents=1024, num_taggers=400, grid_size=32, obs_k=12, tag_r2=1),
+    dict(num_envs=2, num_agents=500, num_taggers=200, grid_size=70, obs_mode=1, obs_k=0, tag_r2=9),
+]
+
+
+@pytest.mark.parametrize("n", range(len(REACH)))
+def test_cells_in_reach_of_taggers(n):
+    kw = dict(REACH[n], seed=1000 + n, episode_length=5)
+    for fused in (False, True):
+        lockstep(kw, 8, 1000 + n, fused=fused)
+    recorded_against_single_iterations(kw, 1000 + n, (1, 4))
+
+
 FULL_ON_LARGE_GRIDS = [  # rows apart behind crew_env_kernel up to the largest grid of its keys, then behind env_kernel
     dict(num_envs=7, num_agents=20, num_taggers=2, grid_size=1639, tag_r2=2 * 1639 * 1639),  # everybody tagged at once
     dict(num_envs=3, num_agents=43, num_taggers=20, grid_size=1159, tag_r2=90000),

@@ -30,3 +30,21 @@ def test_full_views_with_keys_of_64_bits(E, N, G, apart):
 def test_full_views_rows_apart_by_the_size_of_the_batch(E, N, apart):
     """Agent counts that are no multiple of four gain only in batches that do not fill the chip."""
     assert route(full_views(E, N, 110)).apart == apart
+
+
+def partial(E, N, taggers, G, K=4, tag_r2=2):
+    return dict(num_envs=E, num_agents=N, num_taggers=taggers, grid_size=G, obs_k=K, tag_r2=tag_r2)
+
+
+@pytest.mark.parametrize("taggers,G,tag_r2,reach", [
+    (15, 100, 0, 0), (16, 100, 0, 5), (31, 100, 2, 0), (32, 100, 2, 5), (63, 100, 9, 0), (64, 100, 9, 5), (143, 100, 64, 0), (144, 100, 64, 5),
+    (144, 341, 80, 12), (144, 342, 80, 0), (144, 341, 81, 0), (160, 32, 64, 2), (160, 33, 64, 3)])
+def test_map_of_the_cells_that_taggers_reach(taggers, G, tag_r2, reach):
+    r = route(partial(3, 700, taggers, G, tag_r2=tag_r2))
+    assert r.kernel == "crew_env_kernel" and r.reach == reach, r
+
+
+@pytest.mark.parametrize("taggers,G,tag_r2,kernel", [
+    (192, 342, 64, "crew_env_kernel"), (193, 342, 64, "env_kernel"), (193, 341, 64, "crew_env_kernel"), (193, 342, 81, "crew_env_kernel")])
+def test_many_taggers_without_a_map(taggers, G, tag_r2, kernel):
+    assert route(partial(3, 700, taggers, G, tag_r2=tag_r2)).kernel == kernel
