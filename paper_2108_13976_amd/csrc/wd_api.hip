@@ -754,7 +754,6 @@ int64_t place_big_tables(wd::Params* p, int64_t E, unsigned char* base) {
     unsigned char* at = p->g_image + image_b;
     p->g_pl = reinterpret_cast<uint32_t*>(at);
     p->g_env = reinterpret_cast<int32_t*>(at + pl_b);
-    p->g_set = reinterpret_cast<int32_t*>(at + pl_b + env_b);
     p->g_acc = reinterpret_cast<uint32_t*>(at + pl_b + env_b + set_b);
   }
   return slot_b + best_b + cred_b + image_b + pl_b + env_b + set_b + acc_b;
@@ -826,7 +825,7 @@ int wd_create(const wd_config* cfg, const wd_buffers* bufs, wd_handle** out) {
     }
     place_big_tables(&params, cfg->num_envs, static_cast<unsigned char*>(h->scratch));
     const size_t clear = size_t(align16(4 * int64_t(cfg->num_envs)) + 2 * 4 * params.g_stride_acc * int64_t(cfg->num_envs));
-    if (params.big_spread && hipMemset(params.g_set, 0, clear) != hipSuccess) {  // set 0 is the first, both start clear
+    if (params.big_spread && hipMemset(wd::spread_sets(params), 0, clear) != hipSuccess) {  // set 0 is the first, both start clear
       (void)hipGetLastError();
       (void)hipFree(h->scratch);
       delete h;

@@ -1226,7 +1226,7 @@ __global__ __launch_bounds__(2 * kSpreadMoveThreads) void spread_move_kernel(con
   const int tid = threadIdx.x, lt = tid & (kSpreadMoveThreads - 1);
   const bool tagger_half = tid >= kSpreadMoveThreads;
   const int e = blockIdx.x / p.spread_slices, s = blockIdx.x - e * p.spread_slices;
-  const int done_in = p.done[e], t_in = p.t[e], nlr_in = p.n_live_runners[e], set = p.g_set[e];
+  const int done_in = p.done[e], t_in = p.t[e], nlr_in = p.n_live_runners[e], set = spread_sets(p)[e];
   if (s == 0 && tid == 0) {  // the second kernel overwrites these while its other workgroups still need them
     p.g_env[4 * e + 0] = done_in;
     p.g_env[4 * e + 1] = t_in;
@@ -1376,7 +1376,7 @@ __global__ __launch_bounds__(kSpreadObsThreads) void spread_obs_kernel(const Par
   }
   if (stepping) {  // the other set of accumulators is clear, and current, when the next call's first kernel starts
     uint32_t* const other = set ? acc0 : acc1;
-    if (s == 0 && tid == 0) p.g_set[e] = set ^ 1;
+    if (s == 0 && tid == 0) spread_sets(p)[e] = set ^ 1;
     for (int64_t j = int64_t(s) * ts + tid; j < p.g_stride_acc; j += int64_t(p.big_slices) * ts) other[j] = 0u;
   }
   const bool stepped = stepping && !done_in;
