@@ -2859,31 +2859,55 @@ crew_env_kernel(const WaveArgs) {
         }
         __syncthreads();
         WD_NEW_PHASE();
-        // ---- what they did not settle: sixteen lanes per agent ----------------------------------------------------
-        const int queued = __builtin_amdgcn_readfirstlane(L.tags[1]), sub = tid & 15;
-        for (int w = tid >> 4; w < queued; w += threads >> 4) {
-          const uint32_t entry = L.queue[w];
-          const int q = int(entry & 0xFFFFu), radius = int(entry >> 16);
-          const uint32_t me = L.pos[q], own = L.id[q];
-          const int X = int((me & 0xFFFFu) >> hs), Y = int(me >> (16 + hs));
-          const int c0 = max(X - radius, 0) >> sg.cshift, c1 = min(X + radius, p.G - 1) >> sg.cshift;
-          const int r0 = strip_of(max(Y - radius, 0), sg), r1 = strip_of(min(Y + radius, p.G - 1), sg);
-          uint32_t keys[KT];
+        // ---- what they did not settle: sixteen lanes per agent, four where that would be more than one round ------
+        // (Merging costs a round about 200 instructions with K = 8, and a crowd leaves most of its agents here.  us per iteration, sixteen lanes
+        // always / this: three clusters in mid-training 2000 x 128, K = 8 31.2 / 23.9, 256 x 1000 34.7 / 25.6, 500 x 1000, K = 12 112 / 82;
+        // 256 x 1000 on one cell 89 / 73; agents spread evenly no difference.  As few lanes as make one round: clusters 1 to 40 % slower than four.)
+        const int queued = __builtin_amdgcn_readfirstlane(L.tags[1]);
+        const auto settle = [&](auto lanes) {
+          constexpr int kLanes = decltype(lanes)::value;
+          constexpr int kAtOnce = ROLL ? 1 : 16 / kLanes;  // entries that a lane has in flight (registers are short in roll-outs)
+          const int sub = tid & (kLanes - 1);
+          for (int w = tid / kLanes; w < queued; w += threads / kLanes) {
+            const uint32_t entry = L.queue[w];
+            const int q = int(entry & 0xFFFFu), radius = int(entry >> 16);
+            const uint32_t me = L.pos[q], own = L.id[q];
+            const int X = int((me & 0xFFFFu) >> hs), Y = int(me >> (16 + hs));
+            const int c0 = max(X - radius, 0) >> sg.cshift, c1 = min(X + radius, p.G - 1) >> sg.cshift;
+            const int r0 = strip_of(max(Y - radius, 0), sg), r1 = strip_of(min(Y + radius, p.G - 1), sg);
+            uint32_t keys[KT];
 #pragma unroll
-          for (int k = 0; k < KT; ++k) keys[k] = ~0u;
-          for (int row = r0; row <= r1; ++row) {
-            const int end = L.starts[row * sg.C + c1 + 1];
-            for (int i = int(L.starts[row * sg.C + c0]) + sub; i < end; i += 16) {
-              const uint32_t key = strip_key(__builtin_bit_cast(short2v, L.pos[i]) - __builtin_bit_cast(short2v, me), uint32_t(L.id[i]));
-              insert_key<KT>(keys, i == q ? ~0u : key);
+            for (int k = 0; k < KT; ++k) keys[k] = ~0u;
+            for (int row = r0; row <= r1; ++row) {
+              const int end = L.starts[row * sg.C + c1 + 1];
+              for (int i = int(L.starts[row * sg.C + c0]) + sub; i < end; i += kLanes * kAtOnce) {
+                uint32_t at_i[kAtOnce], id_i[kAtOnce];
+#pragma unroll
+                for (int j = 0; j < kAtOnce; ++j) {
+                  const int from = min(i + j * kLanes, end - 1);
+                  at_i[j] = L.pos[from];
+                  id_i[j] = L.id[from];
+                }
+#pragma unroll
+                for (int j = 0; j < kAtOnce; ++j) {
+                  const uint32_t key = strip_key(__builtin_bit_cast(short2v, at_i[j]) - __builtin_bit_cast(short2v, me), id_i[j]);
+                  insert_key<KT>(keys, i + j * kLanes == q || i + j * kLanes >= end ? ~0u : key);
+                }
+              }
             }
+            merge_with_lane<KT, 0xB1>(keys);
+            merge_with_lane<KT, 0x4E>(keys);
+            if constexpr (kLanes == 16) {
+              merge_with_lane<KT, 0x141>(keys);  // the mirror image in eight lanes: the other quad
+              merge_with_lane<KT, 0x140>(keys);  // and in sixteen: the other half
+            }
+            if (sub == 0) crew_put_neighbours<KX, KT>(L.nbr, own, keys, p);
           }
-          merge_with_lane<KT, 0xB1>(keys);
-          merge_with_lane<KT, 0x4E>(keys);
-          merge_with_lane<KT, 0x141>(keys);  // the mirror image in eight lanes: the other quad
-          merge_with_lane<KT, 0x140>(keys);  // and in sixteen: the other half
-          if (sub == 0) crew_put_neighbours<KX, KT>(L.nbr, own, keys, p);
-        }
+        };
+        if (16 * queued <= threads)
+          settle(std::integral_constant<int, 16>{});
+        else
+          settle(std::integral_constant<int, 4>{});
       }
       __syncthreads();
       WD_NEW_PHASE();

@@ -1040,6 +1040,9 @@ CROWDS = {  # strips in every form: one env and several envs per workgroup, 256 
     "k_eight": dict(num_envs=3, num_agents=300, grid_size=55, obs_k=8),
     "k_twelve": dict(num_envs=3, num_agents=300, grid_size=55, obs_k=12),
     "k_sixteen": dict(num_envs=4, num_agents=520, grid_size=5, obs_k=16),
+    "hundred_agents": dict(num_envs=5, num_agents=100, grid_size=31, obs_k=4),
+    "one_agent_more_than_a_wave": dict(num_envs=3, num_agents=65, grid_size=25, obs_k=1),
+    "k_eight_largest_of_two_waves": dict(num_envs=3, num_agents=128, grid_size=35, obs_k=8),
 }
 
 
