@@ -565,6 +565,20 @@ int crew_map_words(const wd_config& c, const wd::Params& p) {
   return p.tag_rad <= 8 && words * c.grid_size <= 4096 && c.num_taggers >= 16 * (1 + p.tag_rad) ? words : 0;
 }
 
+// Many taggers whose reach holds few agents, without the map: comparing every runner with every tagger costs crew_env_kernel more than its shorter
+// chain gains, for env_kernel's taggers look into the bins that they reach, four agents to a lane, and so does the large-env pair.  us per
+// iteration, the other kernel / crew_env_kernel, K = 4 and 3 to 11 agents in reach: 192 taggers 250 x 1000 23.4 / 24.7; 250 100 x 1000 21.6 / 24.0, 21.5 / 23.3;
+// 500 60 x 1000 20.9 / 29.7, 21.4 / 29.3, 250 x 1000 22.5 / 31.6; 600 10 x 700 20.9 / 24.4; but 200 20 x 512 17.9 / 14.8, 256 x 700 no
+// difference, 150 120 x 850 23.0 / 20.4, 500 x 333 23.1 / 17.8.  More in reach: 600 10 x 700 with 7 (three and a half taggers to a lane) 31.5 / 24.6,
+// 250 100 x 1000 with 44 53.6 / 24.9, 500 60 x 1000 with 44 42.6 / 30.8.  K = 12 and 16: 192 60 x 1000 39.5 / 38.9 and 45.1 / 46.9; 250 100 x 1000
+// 40.0 / 41.9 and 45.1 / 49.9; 500 60 x 1000 37.8 / 45.0 and 43.4 / 51.4.
+bool tag_check_elsewhere(const wd_config& c, const wd::Params& p) {
+  if (p.tag_r2 < 0 || crew_map_words(c, p)) return false;
+  const int64_t N = c.num_agents, N_tag = c.num_taggers, G = c.grid_size, side = 2 * int64_t(p.tag_rad) + 1;
+  if (N_tag * N <= (p.K > wd::kMaxRegisterK ? 200000 : 170000)) return false;
+  return (4 * N_tag + N - 1) / N * N * side * side <= 24 * G * G;
+}
+
 // Envs of 65 to 1024 agents that run in crew_env_kernel: a workgroup per env, a lane per agent.  A shorter chain of phases than
 // env_kernel's (or small_env_kernel's, up to 128 agents), for more lanes and instructions per agent: it wins while the chain is what
 // bounds a batch.  Measured, us per iteration in mid-training, the other kernel -> crew_env_kernel:
@@ -587,10 +601,7 @@ bool crew_serves(const wd_config& c, const wd::Params& p) {
   if (p.big || N > wd::kMaxEnvWorkgroupSize) return false;
   if (c.obs_mode == WD_OBS_FULL) return p.obs_mode == wd::kObsFullSplit && !p.wide;
   if (!p.strips || N <= wd::kWaveSize) return false;
-  // many taggers of a short reach on a grid too large for the map: env_kernel's taggers look into the bins that they reach (K = 4 on 342 cells,
-  // env_kernel / this: 200 taggers, 256 x 700 no difference, 256 x 1000 up to 11 %; 256 taggers 256 x 850 24.9 / 25.6; 500 256 x 1000 24.3 / 34.1;
-  // radius 10, 100 taggers on 100 cells 62.9 / 21.5)
-  if (c.num_taggers > 192 && p.tag_rad <= 8 && !crew_map_words(c, p)) return false;
+  if (tag_check_elsewhere(c, p)) return false;
   const int64_t agents = int64_t(E) * N;
   if (K > wd::kMaxRegisterK3) return agents <= 500000 && (N > wd::kSmallEnvAgents || (N >= 112 && E >= 256));
   if (K > wd::kMaxRegisterK) return agents <= 700000 && (N >= 112 || (N >= 96 && E >= 64));
@@ -689,9 +700,12 @@ int fill_params(const wd_config& c, const wd_buffers& b, wd::Params* p, bool own
   const int64_t pair_up_to = c.num_agents <= 1024 ? 3ll * c.num_agents / 10 : 450;  // envs
   bool prefer_pair = pair_serves && c.num_agents >= 384 && c.num_envs <= pair_up_to;
   // the largest batch that the pair serves faster than strips do
-  const int pair_envs = c.num_agents <= wd::kMaxEnvWorkgroupSize ? 0  // (crew_env_kernel serves those: 100 x 1000, K = 12 39.8 -> 32.1)
-                        : p->K > wd::kMaxRegisterK               ? (c.num_agents - 500) / (p->K > wd::kMaxRegisterK3 ? 2 : 4)
-                                                    : (c.num_agents - 1300) / (p->K > 4 ? 5 : 18);
+  // (up to 1024 agents crew_env_kernel is faster yet: 100 x 1000, K = 12 39.8 -> 32.1; of what it leaves, pair / env_kernel: K = 12 60 x 1000
+  // 39.8 / 40.8, 100 x 1000 40.1 / 41.4; K = 16 60 x 1000 44.9 / 54.4, 100 x 1000 46.0 / 54.6, 150 x 1000 57.4 / 54.8, 100 x 850 47.1 / 55.0,
+  // 140 x 850 57.0 / 56.1, 100 x 700 43.7 / 47.1)
+  int pair_envs = p->K > wd::kMaxRegisterK ? (c.num_agents - 500) / (p->K > wd::kMaxRegisterK3 ? 2 : 4)
+                                           : (c.num_agents - 1300) / (p->K > 4 ? 5 : 18);
+  if (c.num_agents <= wd::kMaxEnvWorkgroupSize) pair_envs = tag_check_elsewhere(c, *p) ? std::min(pair_envs, 110000 / c.num_agents) : 0;
   if (prefer_pair && own_tables && c.num_envs > pair_envs) {
     wd::Params small = *p;
     if (plan_env_kernels(c, &small, false) && small.strips) prefer_pair = false;

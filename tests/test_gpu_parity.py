@@ -1252,6 +1252,12 @@ REACH = [  # crew_env_kernel's map of the cells in reach: largest grid, widest r
     dict(num_envs=2, num_agents=1024, num_taggers=500, grid_size=100, obs_k=4, tag_r2=9),     # some waves few, some many
     dict(num_envs=2, num_agents=1024, num_taggers=400, grid_size=32, obs_k=12, tag_r2=1),
     dict(num_envs=2, num_agents=500, num_taggers=200, grid_size=70, obs_mode=1, obs_k=0, tag_r2=9),
+    # too large a grid for it: comparisons in crew_env_kernel, taggers that look into bins in env_kernel and the large-env pair
+    dict(num_envs=3, num_agents=512, num_taggers=256, grid_size=342, obs_k=4, tag_r2=9),
+    dict(num_envs=3, num_agents=700, num_taggers=600, grid_size=342, obs_k=4, tag_r2=100),
+    dict(num_envs=3, num_agents=700, num_taggers=600, grid_size=400, obs_k=4, tag_r2=400),
+    dict(num_envs=3, num_agents=1000, num_taggers=500, grid_size=342, obs_k=16, tag_r2=90),
+    dict(num_envs=3, num_agents=1000, num_taggers=201, grid_size=350, obs_k=12, tag_r2=64),
 ]
 
 

@@ -44,7 +44,20 @@ def test_map_of_the_cells_that_taggers_reach(taggers, G, tag_r2, reach):
     assert r.kernel == "crew_env_kernel" and r.reach == reach, r
 
 
-@pytest.mark.parametrize("taggers,G,tag_r2,kernel", [
-    (192, 342, 64, "crew_env_kernel"), (193, 342, 64, "env_kernel"), (193, 341, 64, "crew_env_kernel"), (193, 342, 81, "crew_env_kernel")])
-def test_many_taggers_without_a_map(taggers, G, tag_r2, kernel):
-    assert route(partial(3, 700, taggers, G, tag_r2=tag_r2)).kernel == kernel
+@pytest.mark.parametrize("E,N,taggers,G,K,tag_r2,kernel", [
+    # few agents in reach: by the number of comparisons
+    (3, 1000, 170, 342, 4, 64, "crew_env_kernel"), (3, 1000, 171, 342, 4, 64, "env_kernel"), (3, 1000, 171, 342, 8, 64, "env_kernel"),
+    (20, 512, 256, 342, 4, 9, "crew_env_kernel"), (10, 700, 600, 342, 4, 100, "env_kernel"), (60, 1000, 500, 400, 4, 400, "env_kernel"),
+    (60, 1000, 200, 342, 12, 9, "crew_env_kernel"), (60, 1000, 201, 342, 12, 9, "big_obs_kernel"), (60, 1000, 200, 342, 16, 9, "crew_env_kernel"),
+    # the map
+    (3, 1000, 500, 341, 4, 64, "crew_env_kernel"),
+    # many in reach
+    (60, 1000, 500, 100, 4, 100, "crew_env_kernel"), (10, 700, 600, 400, 4, 400, "crew_env_kernel"), (60, 1000, 500, 100, 16, 100, "crew_env_kernel"),
+    # no tag check
+    (60, 1000, 500, 342, 4, -1, "crew_env_kernel"),
+    # the large-env pair for few envs with K > 8, as before crew_env_kernel
+    (60, 1000, 500, 342, 16, 9, "big_obs_kernel"), (110, 1000, 500, 342, 16, 9, "big_obs_kernel"), (111, 1000, 500, 342, 16, 9, "env_kernel"),
+    (125, 1000, 500, 342, 12, 9, "env_kernel"), (60, 1000, 500, 342, 16, 100, "big_obs_kernel"), (100, 700, 600, 342, 16, 9, "big_obs_kernel"),
+    (101, 700, 600, 342, 16, 9, "env_kernel")])
+def test_many_taggers_without_a_map(E, N, taggers, G, K, tag_r2, kernel):
+    assert route(partial(E, N, taggers, G, K=K, tag_r2=tag_r2)).kernel == kernel
