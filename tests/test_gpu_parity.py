@@ -128,25 +128,41 @@ def test_rollout_100x50_fused_across_episode_ends():
 
 
 def test_rollout_2000x1000_env_slice():
-    """320 envs of the headline workload (global ids 1000..1319: enough of them for the
-    one-workgroup-per-env layout the whole workload runs in), separate calls, 40 steps."""
+    """320 envs of the headline workload (global ids 1000..1319), separate calls, 40 steps.  So few of them run in
+    crew_env_kernel; the next test has the kernel of the whole workload."""
     cfg = CONFIGS["tag_2000x1000"]
     lockstep(cfg.kwargs(), 40, cfg.seed, fused=False, env_lo=1000, env_hi=1320, full_envs=cfg.num_envs, sharded=16)
 
 
+def test_rollout_2000x1000_in_the_kernel_of_the_whole_workload():
+    """1025 envs of the headline workload (global ids 900..1924), the fewest that run in env_kernel with 256 threads per env,
+    as all 2000 do: separate calls over two episode ends, then fused ones."""
+    cfg = CONFIGS["tag_2000x1000"]
+    kw = dict(cfg.kwargs(), episode_length=3)
+    assert lockstep(kw, 7, cfg.seed, fused=False, env_lo=900, env_hi=1925, full_envs=cfg.num_envs, sharded=16) >= 2050
+    lockstep(kw, 4, cfg.seed, fused=True, env_lo=900, env_hi=1925, full_envs=cfg.num_envs, sharded=16)
+
+
 def test_rollout_2000x1000_small_env_slice():
-    """24 envs of the headline workload (global ids 1000..1023): a batch this small runs in the
-    large-env pair of kernels.  Fused, 40 steps."""
+    """24 envs of the headline workload (global ids 1000..1023), fused, 40 steps."""
     cfg = CONFIGS["tag_2000x1000"]
     lockstep(cfg.kwargs(), 40, cfg.seed, fused=True, env_lo=1000, env_hi=1024, full_envs=cfg.num_envs, sharded=8)
 
 
 def test_rollout_20000x100_env_slice():
-    """300 envs (an odd count: the last workgroup is ragged) of the many-small-envs workload,
-    fused, across episode ends."""
+    """301 envs of the many-small-envs workload (in crew_env_kernel), fused, across episode ends."""
     cfg = CONFIGS["tag_20000x100"]
     lockstep(cfg.kwargs(), 2 * cfg.episode_length + 10, cfg.seed, fused=True, env_lo=7001, env_hi=7302,
              full_envs=cfg.num_envs, check_every=5, sharded=8)
+
+
+def test_rollout_20000x100_in_the_kernel_of_the_whole_workload():
+    """3001 envs of the many-small-envs workload, the fewest that run in small_env_kernel as all 20000 do: separate calls
+    over two episode ends, then fused ones."""
+    cfg = CONFIGS["tag_20000x100"]
+    kw = dict(cfg.kwargs(), episode_length=5)
+    assert lockstep(kw, 12, cfg.seed, fused=False, env_lo=7001, env_hi=10002, full_envs=cfg.num_envs, sharded=16) >= 6002
+    lockstep(kw, 12, cfg.seed, fused=True, env_lo=7001, env_hi=10002, full_envs=cfg.num_envs, sharded=16)
 
 
 def test_rollout_10x8192_all_envs():
@@ -477,7 +493,7 @@ def test_multi_step_rollout_equals_single_iterations(name, k, rounds):
 
     cfg = CONFIGS[name]
     kw = cfg.kwargs()
-    if cfg.num_envs > 500:
+    if cfg.num_envs > 500:  # (in crew_env_kernel; SMALL_IN_LARGE_BATCHES has small_env_kernel)
         kw.update(num_envs=203, env_offset=900)
     E, N = kw["num_envs"], cfg.num_agents
     lo = kw.get("env_offset", 0)
@@ -879,7 +895,7 @@ EDGE = {
     # the any-K variant and full observations in 512-thread workgroups
     "k_seventeen_fifteen_hundred": dict(num_envs=3, num_agents=1500, num_taggers=90, grid_size=70, episode_length=4, obs_k=17),
     "full_obs_twelve_hundred": dict(num_envs=2, num_agents=1200, num_taggers=100, grid_size=40, episode_length=3, obs_mode=1),
-    # K = 1, 2, 3 compiled in (one env per 256-thread workgroup, whole 64-row chunks and a ragged last one)
+    # K = 1, 2, 3 compiled in (whole 64-row chunks and a ragged last one)
     "k_one_thousand_agents": dict(num_envs=310, num_agents=1000, num_taggers=100, grid_size=100, episode_length=3, obs_k=1),
     "k_two_thousand_agents": dict(num_envs=305, num_agents=1000, num_taggers=100, grid_size=90, episode_length=3, obs_k=2),
     "k_three_six_hundred_agents": dict(num_envs=190, num_agents=600, num_taggers=50, grid_size=70, episode_length=4, obs_k=3),
@@ -889,8 +905,9 @@ EDGE = {
     "k_six_thousand_agents": dict(num_envs=305, num_agents=1000, num_taggers=100, grid_size=100, episode_length=3, obs_k=6),
     "k_seven_packed_envs": dict(num_envs=30, num_agents=120, num_taggers=12, grid_size=25, episode_length=8, obs_k=7),
     "k_five_odd_agent_count": dict(num_envs=11, num_agents=203, num_taggers=20, grid_size=45, episode_length=8, obs_k=5),
-    # the large-env pair at the smallest agent count it is chosen for
-    "large_env_pair_smallest": dict(num_envs=3, num_agents=384, num_taggers=30, grid_size=50, episode_length=10, obs_k=16),
+    # the large-env pair at the smallest agent count it is chosen for (with 32-bit keys crew_env_kernel serves that one)
+    "large_env_pair_smallest": dict(num_envs=3, num_agents=384, num_taggers=30, grid_size=2000, episode_length=10, obs_k=16, tag_r2=2500),
+    "large_env_pair_smallest_32_bit_keys": dict(num_envs=3, num_agents=384, num_taggers=30, grid_size=50, episode_length=10, obs_k=16),
     "odd_rewards": dict(num_envs=12, num_agents=25, num_taggers=5, grid_size=8, episode_length=20, obs_k=2,
                         tag_reward=0.3, tag_penalty=-2.5),
     # The large-env layout has two forms: few envs get the step spread over a workgroup per 512 agents (the
@@ -903,7 +920,7 @@ EDGE = {
     "large_env_odd_taggers": dict(num_envs=3, num_agents=4099, num_taggers=513, grid_size=210, episode_length=4, obs_k=4,
                                   tag_r2=5),
     "large_env_crowded": dict(num_envs=2, num_agents=4200, num_taggers=100, grid_size=16, episode_length=6, tag_r2=0),
-    # a wave per env (at most 64 agents, 8192 envs, a grid of 4096 cells a side, K <= 16), and the general kernel just beyond
+    # waves without workgroup tables (at most 64 agents, 8192 envs, a grid of 4096 cells a side, K <= 16), and the other kernels just beyond
     "wave_full": dict(num_envs=7, num_agents=64, num_taggers=63, grid_size=30, episode_length=12, obs_k=8),
     "wave_sixty_four_runners": dict(num_envs=5, num_agents=64, num_taggers=1, grid_size=9, episode_length=30, obs_k=4, tag_r2=1),
     "wave_two_agents": dict(num_envs=9, num_agents=2, num_taggers=1, grid_size=3, episode_length=6, obs_k=1),
@@ -918,7 +935,7 @@ EDGE = {
     "beyond_wave_agents": dict(num_envs=300, num_agents=65, num_taggers=7, grid_size=25, episode_length=10, obs_k=4),
     "beyond_wave_grid": dict(num_envs=3, num_agents=40, num_taggers=4, grid_size=4097, episode_length=8, obs_k=4, tag_r2=10**6),
     "many_small_envs_k_two": dict(num_envs=8500, num_agents=30, num_taggers=3, grid_size=12, episode_length=8, obs_k=2),
-    # where the layouts meet: 512- and 1024-thread workgroups of small batches, strips up to the largest grid whose
+    # where the layouts meet: agent counts around the sizes of workgroups, strips up to the largest grid whose
     # scaled positions fit 16 bits (N = 2049: 212 cells a side) and 64-bit keys beyond, few large envs in the pair
     "wide_workgroup_257": dict(num_envs=3, num_agents=257, num_taggers=30, grid_size=50, episode_length=8),
     "wide_workgroup_k_five": dict(num_envs=2, num_agents=600, num_taggers=60, grid_size=80, episode_length=6, obs_k=5),
@@ -926,7 +943,7 @@ EDGE = {
     "strips_largest_grid": dict(num_envs=48, num_agents=2049, num_taggers=200, grid_size=212, episode_length=2),
     "strips_grid_too_large": dict(num_envs=48, num_agents=2049, num_taggers=200, grid_size=213, episode_length=2),
     "strips_three_thousand": dict(num_envs=100, num_agents=3000, num_taggers=300, grid_size=193, episode_length=2),
-    # K = 9 .. 16 with strips: lists of 12 and 16 keys, one env and several envs per workgroup, fewer agents left than K
+    # K = 9 .. 16 with strips: lists of 12 and 16 keys, few and many envs, fewer agents left than K
     "k_nine_strips": dict(num_envs=3, num_agents=300, num_taggers=30, grid_size=40, episode_length=8, obs_k=9),
     "k_twelve_strips_packed": dict(num_envs=300, num_agents=70, num_taggers=9, grid_size=18, episode_length=25, obs_k=12),
     "k_thirteen_strips_crowded": dict(num_envs=3, num_agents=203, num_taggers=20, grid_size=5, episode_length=6, obs_k=13, tag_r2=0),
@@ -975,13 +992,18 @@ def test_full_observation_rows_in_a_launch_of_their_own(num_envs, num_agents):
     a.close(), b.close()
 
 
-ENTERED_DONE = {  # one configuration for every way a roll-out can run
-    "wave_env_kernel": dict(num_envs=9, num_agents=30, num_taggers=4, grid_size=12, obs_k=4),
-    "small_env_kernel": dict(num_envs=9, num_agents=101, num_taggers=9, grid_size=30, obs_k=4),
-    "one_workgroup": dict(num_envs=5, num_agents=300, num_taggers=30, grid_size=50, obs_k=4),
-    "packed_envs": dict(num_envs=301, num_agents=130, num_taggers=13, grid_size=40, obs_k=5),
+ENTERED_DONE = {  # one configuration for every way a roll-out can run (test_routes.py holds which)
+    "quad_env_kernel": dict(num_envs=9, num_agents=30, num_taggers=4, grid_size=12, obs_k=4),
+    "wave_env_kernel": dict(num_envs=8193, num_agents=12, num_taggers=2, grid_size=11, obs_k=4),
+    "crew_env_kernel_two_waves": dict(num_envs=9, num_agents=101, num_taggers=9, grid_size=30, obs_k=4),
+    "crew_env_kernel": dict(num_envs=5, num_agents=300, num_taggers=30, grid_size=50, obs_k=4),
+    "crew_env_kernel_k_five": dict(num_envs=301, num_agents=130, num_taggers=13, grid_size=40, obs_k=5),
+    "crew_env_kernel_k_twelve": dict(num_envs=5, num_agents=300, num_taggers=30, grid_size=50, obs_k=12),
+    "small_env_kernel": dict(num_envs=3001, num_agents=101, num_taggers=9, grid_size=30, obs_k=4),
+    "one_workgroup": dict(num_envs=5, num_agents=1030, num_taggers=90, grid_size=100, obs_k=4),
+    "packed_envs": dict(num_envs=6001, num_agents=200, num_taggers=20, grid_size=45, obs_k=3),
+    "k_twelve_strips": dict(num_envs=9, num_agents=100, num_taggers=9, grid_size=30, obs_k=12),
     "packed_envs_k_run_time": dict(num_envs=33, num_agents=131, num_taggers=13, grid_size=3000, obs_k=3),
-    "k_twelve_strips": dict(num_envs=5, num_agents=300, num_taggers=30, grid_size=50, obs_k=12),
     "k_twelve_64_bit_keys": dict(num_envs=5, num_agents=140, num_taggers=14, grid_size=3000, obs_k=12),
     "any_k": dict(num_envs=5, num_agents=90, num_taggers=9, grid_size=30, obs_k=17),
     "full_views": dict(num_envs=5, num_agents=50, num_taggers=9, grid_size=30, obs_mode=1),
@@ -1030,11 +1052,12 @@ def test_recorded_rewards_of_envs_that_enter_a_roll_out_done(name, k):
     a.close(), b.close()
 
 
-CROWDS = {  # strips in every form: one env and several envs per workgroup, 256 to 1024 threads, whole lists, lists of K + 1
-    "packed_k_one": dict(num_envs=37, num_agents=150, grid_size=40, obs_k=1),
-    "packed_k_five": dict(num_envs=40, num_agents=131, grid_size=36, obs_k=5),
-    "packed_k_eleven": dict(num_envs=300, num_agents=133, grid_size=36, obs_k=11),
-    "compact_ids": dict(num_envs=3, num_agents=600, grid_size=77, obs_k=4),
+CROWDS = {  # sorted lists in every form: in crew_env_kernel for each size of list, then strips in env_kernel and rollout_kernel (one env and
+            # several envs per workgroup, whole lists, lists of K + 1)
+    "k_one": dict(num_envs=37, num_agents=150, grid_size=40, obs_k=1),
+    "k_five": dict(num_envs=40, num_agents=131, grid_size=36, obs_k=5),
+    "k_eleven": dict(num_envs=300, num_agents=133, grid_size=36, obs_k=11),
+    "k_four": dict(num_envs=3, num_agents=600, grid_size=77, obs_k=4),
     "wide_ids": dict(num_envs=9, num_agents=1100, grid_size=100, obs_k=4),
     "k_two_wide_workgroup": dict(num_envs=60, num_agents=1301, grid_size=115, obs_k=2),
     "k_eight": dict(num_envs=3, num_agents=300, grid_size=55, obs_k=8),
@@ -1043,6 +1066,14 @@ CROWDS = {  # strips in every form: one env and several envs per workgroup, 256 
     "hundred_agents": dict(num_envs=5, num_agents=100, grid_size=31, obs_k=4),
     "one_agent_more_than_a_wave": dict(num_envs=3, num_agents=65, grid_size=25, obs_k=1),
     "k_eight_largest_of_two_waves": dict(num_envs=3, num_agents=128, grid_size=35, obs_k=8),
+    "strips_k_one": dict(num_envs=2, num_agents=1026, grid_size=101, obs_k=1),
+    "strips_k_five": dict(num_envs=2, num_agents=1027, grid_size=101, obs_k=5),
+    "strips_k_eight": dict(num_envs=2, num_agents=1033, grid_size=101, obs_k=8),
+    "strips_k_twelve": dict(num_envs=132, num_agents=1026, grid_size=101, obs_k=12),
+    "strips_k_twelve_few_agents": dict(num_envs=9, num_agents=105, grid_size=32, obs_k=12),
+    "strips_k_sixteen": dict(num_envs=200, num_agents=127, grid_size=35, obs_k=16),
+    "strips_of_four_envs": dict(num_envs=6001, num_agents=200, grid_size=45, obs_k=4),
+    "strips_of_two_envs_k_twelve": dict(num_envs=3502, num_agents=200, grid_size=45, obs_k=12),
 }
 
 
@@ -1101,7 +1132,7 @@ def test_crowds(name, where):
     gpu.close(), rec.close()
 
 
-SMALL = [  # up to 128 agents, most of them in a wave per env, two agents per lane (small_env_kernel): edges of its sizes
+SMALL = [  # up to 128 agents in few envs (crew_env_kernel) and in many (small_env_kernel, wave_env_kernel): edges of their sizes
     dict(num_envs=5, num_agents=65, num_taggers=64, grid_size=14, obs_k=1, tag_r2=5),
     dict(num_envs=9, num_agents=66, num_taggers=1, grid_size=20, obs_k=2),
     dict(num_envs=3, num_agents=67, num_taggers=9, grid_size=30, obs_k=3, tag_r2=-1),
@@ -1171,6 +1202,31 @@ def test_env_per_wave(n):
     recorded_against_single_iterations(kw, 500 + n, (1, 4, 4))
 
 
+SMALL_IN_LARGE_BATCHES = [  # 65 to 128 agents in the fewest envs that run in small_env_kernel, two agents per lane: edges of its sizes
+    dict(num_envs=1501, num_agents=65, num_taggers=64, grid_size=14, obs_k=1, tag_r2=5),
+    dict(num_envs=1501, num_agents=66, num_taggers=1, grid_size=20, obs_k=2),
+    dict(num_envs=1501, num_agents=67, num_taggers=9, grid_size=30, obs_k=3, tag_r2=-1),
+    dict(num_envs=3001, num_agents=96, num_taggers=20, grid_size=6, obs_k=4, tag_r2=0),
+    dict(num_envs=4097, num_agents=127, num_taggers=126, grid_size=849, obs_k=5, tag_r2=40000),     # largest grid of its keys
+    dict(num_envs=4097, num_agents=128, num_taggers=13, grid_size=40, obs_k=6, tag_r2=2 * 40 * 40), # everybody tagged at once
+    dict(num_envs=4097, num_agents=128, num_taggers=127, grid_size=1, obs_k=7),                     # one cell
+    dict(num_envs=3001, num_agents=101, num_taggers=10, grid_size=33, obs_k=8),
+]
+
+
+def few_steps_in_a_large_batch(kw, seed):
+    """Separate calls over an episode end, fused ones, and recorded multi-step launches."""
+    kw = dict(kw, seed=seed, episode_length=2)
+    for fused in (False, True):
+        lockstep(kw, 3, seed, fused=fused, sharded=16)
+    recorded_against_single_iterations(kw, seed, (1, 3))
+
+
+@pytest.mark.parametrize("n", range(len(SMALL_IN_LARGE_BATCHES)))
+def test_two_agents_per_lane(n):
+    few_steps_in_a_large_batch(SMALL_IN_LARGE_BATCHES[n], 600 + n)
+
+
 QUAD = [  # four lanes per agent (quad_env_kernel): edges of its waves of sixteen agents, of its key lists and of the rule for it
     dict(num_envs=5, num_agents=2, num_taggers=1, grid_size=4, obs_k=1),
     dict(num_envs=11, num_agents=16, num_taggers=3, grid_size=9, obs_k=4),
@@ -1182,7 +1238,8 @@ QUAD = [  # four lanes per agent (quad_env_kernel): edges of its waves of sixtee
     dict(num_envs=1, num_agents=64, num_taggers=63, grid_size=25, obs_k=12),
     dict(num_envs=2, num_agents=64, num_taggers=6, grid_size=30, obs_k=0),
     dict(num_envs=2001, num_agents=18, num_taggers=2, grid_size=14, obs_k=2),                # wave_env_kernel for one iteration
-    dict(num_envs=2501, num_agents=27, num_taggers=3, grid_size=16, obs_k=4),                # and for several
+    dict(num_envs=2501, num_agents=27, num_taggers=3, grid_size=16, obs_k=4),                # lanes just full enough for several
+    dict(num_envs=2501, num_agents=26, num_taggers=3, grid_size=16, obs_k=4),                # wave_env_kernel for several
     dict(num_envs=8192, num_agents=14, num_taggers=2, grid_size=12, obs_k=4),
 ]
 
@@ -1204,13 +1261,14 @@ CREW = [  # a lane per agent (crew_env_kernel): edges of its workgroups, of list
     dict(num_envs=3, num_agents=129, num_taggers=31, grid_size=9, obs_k=3, tag_r2=300),       # 48 lanes' lists at most: whole after one step
     dict(num_envs=4, num_agents=192, num_taggers=48, grid_size=1, obs_k=8, tag_r2=-1),        # one cell, nobody tagged
     dict(num_envs=4, num_agents=192, num_taggers=47, grid_size=2, obs_k=7, tag_r2=0),
-    dict(num_envs=2, num_agents=255, num_taggers=25, grid_size=844, obs_k=5, tag_r2=40000),   # largest grid of its keys
+    dict(num_envs=2, num_agents=255, num_taggers=25, grid_size=849, obs_k=5, tag_r2=40000),   # largest grid of its keys
+    dict(num_envs=2, num_agents=255, num_taggers=25, grid_size=850, obs_k=5, tag_r2=40000),   # env_kernel takes over
     dict(num_envs=2, num_agents=257, num_taggers=256, grid_size=30, obs_k=6, tag_r2=3000),    # everybody tagged at once
     dict(num_envs=9, num_agents=333, num_taggers=33, grid_size=58, obs_k=4),
     dict(num_envs=257, num_agents=640, num_taggers=60, grid_size=80, obs_k=4),
     dict(num_envs=2, num_agents=1023, num_taggers=100, grid_size=60, obs_k=8),
     dict(num_envs=2, num_agents=1024, num_taggers=300, grid_size=300, obs_k=4, tag_r2=100),
-    # the map of cells in reach: its word edges, its widest reach, the grid just beyond it
+    # a reach of many cells, and many taggers, without the map of cells in reach
     dict(num_envs=3, num_agents=200, num_taggers=16, grid_size=64, obs_k=4, tag_r2=64),
     dict(num_envs=3, num_agents=300, num_taggers=90, grid_size=33, obs_k=2, tag_r2=80),
     dict(num_envs=3, num_agents=300, num_taggers=90, grid_size=345, obs_k=4, tag_r2=81),
@@ -1284,6 +1342,31 @@ def test_full_observations_on_large_grids(n):
     for fused in (False, True):
         lockstep(kw, 6, 940 + n, fused=fused, sharded=8 if kw["num_envs"] > 100 else 0)
     recorded_against_single_iterations(kw, 940 + n, (1, 3))
+
+
+LARGE_BATCHES = [  # 129 to 1024 agents just beyond crew_env_kernel's batches: strips with four, two and one env per workgroup
+    dict(num_envs=6001, num_agents=200, num_taggers=20, grid_size=45, obs_k=4),
+    dict(num_envs=9231, num_agents=130, num_taggers=13, grid_size=36, obs_k=1),
+    dict(num_envs=9161, num_agents=131, num_taggers=1, grid_size=36, obs_k=3),
+    dict(num_envs=6031, num_agents=199, num_taggers=198, grid_size=849, obs_k=5, tag_r2=10000),
+    dict(num_envs=9231, num_agents=130, num_taggers=30, grid_size=3, obs_k=6, tag_r2=0),
+    dict(num_envs=9091, num_agents=132, num_taggers=13, grid_size=37, obs_k=7, tag_r2=-1),
+    dict(num_envs=3604, num_agents=333, num_taggers=33, grid_size=58, obs_k=8),
+    dict(num_envs=2667, num_agents=450, num_taggers=45, grid_size=67, obs_k=2, tag_r2=2 * 67 * 67),
+    dict(num_envs=2746, num_agents=255, num_taggers=25, grid_size=50, obs_k=9),
+    dict(num_envs=3501, num_agents=200, num_taggers=20, grid_size=45, obs_k=12),
+    dict(num_envs=2501, num_agents=200, num_taggers=20, grid_size=45, obs_k=16),
+    dict(num_envs=701, num_agents=1000, num_taggers=100, grid_size=100, obs_k=10),
+    dict(num_envs=501, num_agents=1000, num_taggers=100, grid_size=100, obs_k=16),
+    dict(num_envs=513, num_agents=1000, num_taggers=100, grid_size=100, obs_k=4),
+    dict(num_envs=257, num_agents=1023, num_taggers=100, grid_size=100, obs_k=8),
+    dict(num_envs=513, num_agents=700, num_taggers=70, grid_size=83, obs_k=3),
+]
+
+
+@pytest.mark.parametrize("n", range(len(LARGE_BATCHES)))
+def test_large_batches_of_mid_sized_envs(n):
+    few_steps_in_a_large_batch(LARGE_BATCHES[n], 700 + n)
 
 
 BEYOND_CREW = [  # just beyond what crew_env_kernel serves: small_env_kernel, env_kernel and rollout_kernel for each K

@@ -1,6 +1,7 @@
 """Which kernel serves which configuration (host side only, no GPU)."""
 import pytest
 
+import test_gpu_parity as gpu_tests
 from routes import route
 
 
@@ -61,3 +62,55 @@ def test_map_of_the_cells_that_taggers_reach(taggers, G, tag_r2, reach):
     (101, 700, 600, 342, 16, 9, "env_kernel")])
 def test_many_taggers_without_a_map(E, N, taggers, G, K, tag_r2, kernel):
     assert route(partial(E, N, taggers, G, K=K, tag_r2=tag_r2)).kernel == kernel
+
+
+# ---- what the tables of the GPU tests say of the kernels they run ------------------------------------------------
+def kernels(kw):
+    kw = dict(kw)
+    kw.setdefault("num_taggers", kw["num_agents"] // 12)
+    return route(kw).kernel, route(kw, recording=True).kernel
+
+
+ENTERED_DONE = {  # (single calls and wd_rollout, where one name stands for both)
+    "quad_env_kernel": "quad_env_kernel", "wave_env_kernel": "wave_env_kernel", "small_env_kernel": "small_env_kernel",
+    "crew_env_kernel_two_waves": "crew_env_kernel", "crew_env_kernel": "crew_env_kernel", "crew_env_kernel_k_five": "crew_env_kernel",
+    "crew_env_kernel_k_twelve": "crew_env_kernel", "one_workgroup": "env_kernel rollout_kernel", "packed_envs": "env_kernel rollout_kernel",
+    "packed_envs_k_run_time": "env_kernel rollout_kernel", "k_twelve_strips": "env_kernel rollout_kernel", "k_twelve_64_bit_keys": "env_kernel",
+    "any_k": "env_kernel", "full_views": "crew_env_kernel", "full_views_rows_apart": "crew_env_kernel", "large_env_pair": "big_obs_kernel",
+    "large_env_spread": "spread_obs_kernel"}
+
+
+@pytest.mark.parametrize("name", list(gpu_tests.ENTERED_DONE))
+def test_ways_a_roll_out_can_run(name):
+    served = ENTERED_DONE[name].split()
+    assert kernels(gpu_tests.ENTERED_DONE[name]) == (served[0], served[-1])
+
+
+@pytest.mark.parametrize("name", list(gpu_tests.CROWDS))
+def test_crowds_in_every_form(name):
+    kw = gpu_tests.CROWDS[name]
+    strips = name.startswith("strips") or name in ("wide_ids", "k_two_wide_workgroup")
+    assert kernels(kw) == (("env_kernel", "rollout_kernel") if strips else 2 * ("crew_env_kernel",))
+    r = route(dict(kw, num_taggers=kw["num_agents"] // 12))
+    assert r.strips and r.teams == {"strips_of_four_envs": 4, "strips_of_two_envs_k_twelve": 2}.get(name, 1), r
+
+
+@pytest.mark.parametrize("n", range(len(gpu_tests.SMALL_IN_LARGE_BATCHES)))
+def test_fewest_envs_of_small_env_kernel(n):
+    kw = gpu_tests.SMALL_IN_LARGE_BATCHES[n]
+    assert kernels(kw) == 2 * ("small_env_kernel",)
+    assert kernels(dict(kw, num_envs=kw["num_envs"] - 1)) == 2 * ("crew_env_kernel",)
+
+
+@pytest.mark.parametrize("n", range(len(gpu_tests.LARGE_BATCHES)))
+def test_fewest_envs_beyond_crew_env_kernel(n):
+    kw = gpu_tests.LARGE_BATCHES[n]
+    r = route(kw)
+    assert kernels(kw) == ("env_kernel", "rollout_kernel") and r.strips and r.teams == (4 if n < 6 else 2 if n < 11 else 1), r
+    assert kernels(dict(kw, num_envs=kw["num_envs"] - 2)) == 2 * ("crew_env_kernel",)
+
+
+def test_slices_in_the_kernels_of_whole_workloads():
+    for name, fewest in (("tag_2000x1000", 1025), ("tag_20000x100", 3001)):
+        kw = gpu_tests.CONFIGS[name].kwargs()
+        assert route(dict(kw, num_envs=fewest))[:5] == route(kw)[:5] != route(dict(kw, num_envs=fewest - 1))[:5]
