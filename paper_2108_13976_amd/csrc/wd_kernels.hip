@@ -1819,7 +1819,8 @@ __global__ __launch_bounds__(kWaveSize) void wave_env_kernel(const WaveArgs args
 // four sorted lists (the K smallest of two sorted lists are the smaller ones of opposite pairs, put in order by half a
 // bitonic network), and each lane writes every fourth slot of the row.
 //
-// Bound: still a wave's chain (about 400 instructions per iteration at 50 agents), and for 5 agents the launch.  100 envs x
+// Bound: still a wave's chain (at 50 agents 213 vector and 99 scalar instructions per iteration and 3400 cycles, in 44 % of which it issues), and
+// for 5 agents the launch.  100 envs x
 // 50 agents, twenty recorded iterations, K = 4: 63.3 -> 31.7 us (without a drawing wave 40.9; that and single calls in
 // one kernel 33.7), K = 8 81.5 -> 37.9, K = 16 112 -> 51.3; one iteration per call 6.0 -> 5.3, K = 14, 60 agents 9.0 -> 6.0.
 // ----------------------------------------------------------------------------------
@@ -2476,13 +2477,17 @@ hipError_t launch_small_kernel(const Params& p, int mode, const Roll& roll, cons
 // one agent's work, the tag check comes before the sort (so no entry of the list has to be marked afterwards), and lists
 // of up to a quarter of the lanes are not sorted at all: four lanes per agent compare it with every entry, as
 // quad_env_kernel does.  Longer lists are sorted by strip and column and searched through the windows of wd_dev_strips.h;
-// agents that the windows do not settle get sixteen lanes each, which read the bins within the distance already known.
+// agents that the windows do not settle get sixteen lanes each (four where they are many), which read the bins within the distance already
+// known.
 //
 // Where many taggers have a short reach, they mark the cells that they reach in a bit map, and only runners on marked cells are
 // compared with them, one by one by their wave, or all of the wave's by a lane each where they are many.
 //
-// Bound: the chain of one workgroup (three or four barriers and about 600 instructions up to the rows where the list is compared
-// whole), for larger batches the vector ALUs.  20 envs x 333 agents, K = 4: 18.0 -> 11.0 us per iteration, 777 x 333 25.6 -> 17.3 (its
+// Bound: the chain of one workgroup (four barriers up to the rows where the list is compared whole, eight where it is sorted, one more with
+// the bit map): of 18 200 cycles a wave of 20 envs x 333 agents issues in a quarter, about 950 instructions in all, and waits in two thirds.  For
+// larger batches the issue of instructions, vector and scalar ones in nearly equal numbers (2000 x 200: the SIMDs issue all the time, the vector
+// ALUs are 47 % busy); for the largest envs with K > 4 LDS, which admits one workgroup to a CU (500 x 1000, K = 12: 94 112 bytes, two rounds).
+// 20 envs x 333 agents, K = 4: 18.0 -> 11.0 us per iteration, 777 x 333 25.6 -> 17.3 (its
 // three services one by one 41.1 -> 28.2), 2000 x 200 26.0 -> 20.5, 256 x 1000 23.4 -> 18.3 (without the bit map 20.6; 777 x 333, eight
 // recorded iterations 111 -> 99); 500 x 333, K = 12 39.8 -> 29.7.  Rows stored by each lane (or by four) straight from registers
 // instead of through LDS: 777 x 333 20.1, 2000 x 200 25.2.  At most 64 registers: with 76 in the multi-step form 300 x 333 takes 84 us
@@ -2633,9 +2638,8 @@ crew_env_kernel(const WaveArgs) {
       }
     }
     WD_NEW_PHASE();
-    // lists of up to a quarter of the lanes are compared whole; the table of bins is not needed if no list can be longer
-    const int whole_up_to = threads >> 2;
-    if (KX > 0 && N > whole_up_to) {
+    const int whole_up_to = threads >> 2;  // longer lists are sorted
+    if constexpr (KX > 0) {  // (the table of bins, cleared before the length of the list is known)
       uint32_t* const tw = reinterpret_cast<uint32_t*>(L.starts);
       const int words = (p.strip_rmax * p.strip_C + 2) >> 1;
       for (int j = tid; j < words; j += threads) tw[j] = 0u;
