@@ -596,6 +596,12 @@ bool tag_check_elsewhere(const wd_config& c, const wd::Params& p) {
 //   Four recorded iterations: K = 4: 100 x 200 57.6 -> 33.1, 1200 x 333 109 -> 75, 2700 x 200 146 -> 95; K = 12: 500 x 333 169 -> 103.
 //   Full observations whose rows have a launch of their own (the step alone; bucket rings before): 20 x 100 15.5 -> 9.8, 400 x 150 29.7 ->
 // 22.1, 200 x 500 93.9 -> 87.9, 250 x 1000 351 -> 344, 8000 x 64 124 -> 117.
+//   What bounds it beyond 768 agents with K > 4 is LDS: one workgroup fits a CU (500 x 1000, K = 8 99 232 bytes).  The limits on agents below
+// (500 000 for K > 12, 700 000 for K > 8, 1 200 000 for 129 to 480 agents) are where measuring ended, with the kernel still ahead, and no crossovers.
+//   Crowds, the other kernel / this: three clusters per env in mid-training: K = 4 100 x 100 13.1 / 11.9, 1500 x 66 15.2 / 13.6 (every agent in play 12.7 /
+// 13.6), 2000 x 200 48.5 / 23.4, 777 x 333 54.3 / 20.4, 256 x 1000 64.3 / 25.7; K = 8 2000 x 128 24.1 / 23.9 (21.9 / 23.5), 4000 x 128 30.8 / 33.4 (30.9 / 37.4), 256 x
+// 1000 89.4 / 40.1; K = 12 500 x 1000 173 / 83, K = 16 250 / 106.  Most of them on one cell: K = 4 256 x 1000 467 / 78, K = 16 500 x 1000 571 / 220, but
+// 65 to 128 agents, which small_env_kernel compares whole whatever they do: K = 4 2000 x 128 17.4 / 22.1, 1000 x 100 14.4 / 17.9, K = 8 2000 x 128 22.0 / 25.6.
 bool crew_serves(const wd_config& c, const wd::Params& p) {
   const int N = c.num_agents, E = c.num_envs, K = p.K;
   if (p.big || N > wd::kMaxEnvWorkgroupSize) return false;
